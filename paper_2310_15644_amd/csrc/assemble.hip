@@ -52,12 +52,12 @@
 namespace efie {
 
 template <typename R, bool CK, bool PARTS>
-__global__ __launch_bounds__(FAR_BLOCK) void far_pairs_kernel(DevMesh m, Tables<R> tb, R kphase, R ki,
+__global__ __launch_bounds__(FAR_BLOCK) void far_pairs_kernel(DevMesh m, Tables<R> tb, Phase<R> ph,
                                                               Scale sc, void* Z, void* Z2, int nqblk) {
     const int p = blockIdx.x / nqblk;
     const int q = (blockIdx.x - p * nqblk) * FAR_BLOCK + threadIdx.x;
     if (q >= m.T) return;
-    far_pair<R, CK, PARTS>(m, tb, p, q, kphase, ki, sc, Z, Z2);
+    far_pair<R, CK, PARTS>(m, tb, p, q, ph, sc, Z, Z2);
 }
 
 template <typename ZT, bool PARTS>
@@ -73,7 +73,7 @@ __global__ __launch_bounds__(128) void near_pairs_kernel(DevMesh m, double kr, d
 // the pair rows of a chunk of test triangles (the first step of the Calderon
 // build): the bodies live in rows_kernels.h
 template <typename R, bool CK, bool UPPER>
-__global__ __launch_bounds__(FAR_BLOCK) void far_rows_kernel(DevMesh m, Tables<R> tb, R kphase, R ki, Scale sc,
+__global__ __launch_bounds__(FAR_BLOCK, sizeof(R) == 4 ? 3 : 2) void far_rows_kernel(DevMesh m, Tables<R> tb, Phase<R> ph, Scale sc,
                                                              typename Cplx<R>::T* __restrict__ W, int c0, int np,
                                                              int nqblk) {
     // blocks are dealt to the 8 XCDs round-robin: remap so that each XCD runs the
@@ -82,7 +82,7 @@ __global__ __launch_bounds__(FAR_BLOCK) void far_rows_kernel(DevMesh m, Tables<R
     const int xcd = int(blockIdx.x) & 7, idx = int(blockIdx.x) >> 3;
     const int per = nblk >> 3, rem = nblk & 7;
     const int logical = xcd * per + min(xcd, rem) + idx;
-    far_rows_block<R, CK, UPPER>(m, tb, kphase, ki, sc, W, c0, np, nqblk, logical);
+    far_rows_block<R, CK, UPPER>(m, tb, ph, sc, W, c0, np, nqblk, logical);
 }
 
 template <typename R>
@@ -107,14 +107,17 @@ __global__ __launch_bounds__(256) void near_blocks_kernel(DevMesh m, double kr, 
     near_block_one<R>(m, kr, ki, sc, NB, m.near_up[u], t % NEAR_G);
 }
 
-// one block per tile of Z (tiles on and above the diagonal); complex64: three
-// blocks per CU (the LDS allows three), so at most 168 VGPRs
-template <typename R, bool CK>
-__global__ __launch_bounds__(256, sizeof(R) == 4 ? 3 : 1) void tile_kernel(DevMesh m, Tables<R> tb, R kphase, R ki, Scale sc,
+// One block per tile of Z (tiles on and above the diagonal); complex64: three
+// blocks per CU (the LDS allows three), so at most 168 VGPRs; complex128: two.
+// Bound by the vector ALU: about 55 FP64 operations per Green's function (26 FP32).
+// N = 7680 in complex128: 10.3 ms with the library's sincos, Cartesian moments and
+// 32-wide tiles of half-filled waves, 3.9 ms now; N = 30720 in complex64: 23.7 -> 22.1 ms.
+template <typename R, bool CK, int TS>
+__global__ __launch_bounds__(256, sizeof(R) == 4 ? 3 : 2) void tile_kernel(DevMesh m, Tables<R> tb, Phase<R> ph, Scale sc,
                                                    const typename Cplx<R>::T* __restrict__ NB,
                                                    typename Cplx<R>::T* __restrict__ Z) {
-    __shared__ TileLds<R> L;
-    tile_block<R, CK>(m, tb, kphase, ki, sc, NB, Z, (long long)blockIdx.x, L);
+    __shared__ TileLds<R, TS> L;
+    tile_block<R, CK, TS>(m, tb, ph, sc, NB, Z, (long long)blockIdx.x, L);
 }
 
 template <typename R>
@@ -139,14 +142,14 @@ void launch_far(const DevMesh& m, double kr, double ki, const Scale& sc, void* Z
     const size_t nblk = size_t(m.T) * nqblk;
     EFIE_REQUIRE(nblk < (size_t(1) << 31), EFIE_ERR_ARG, "assemble: mesh too large for one launch");
     const bool ck = ki != 0.0;
-    const R kphase = std::is_same<R, float>::value ? R(kr / (2.0 * PI)) : R(kr);
+    const Phase<R> ph = make_phase<R>(kr, ki);
     prof_begin(PROF_FAR, s);
     if (ck)
         hipLaunchKernelGGL((far_pairs_kernel<R, true, PARTS>), dim3(unsigned(nblk)), dim3(FAR_BLOCK), 0, s, m,
-                           tables_of<R>(m), kphase, R(ki), sc, Z, Z2, nqblk);
+                           tables_of<R>(m), ph, sc, Z, Z2, nqblk);
     else
         hipLaunchKernelGGL((far_pairs_kernel<R, false, PARTS>), dim3(unsigned(nblk)), dim3(FAR_BLOCK), 0, s, m,
-                           tables_of<R>(m), kphase, R(ki), sc, Z, Z2, nqblk);
+                           tables_of<R>(m), ph, sc, Z, Z2, nqblk);
     prof_end(PROF_FAR, s);
 }
 
@@ -197,6 +200,18 @@ static void near_beside_far(hipStream_t s, NearF near, FarF far) {
     EFIE_HIP_CHECK(hipStreamWaitEvent(s, x.join, 0));
 }
 
+// The tile edge by the order of Z, measured on geodesic spheres (microseconds for
+// the whole assembly with edge 16 / 32 / 64, complex128; complex64 in brackets):
+//   N =  480    78 /  104 /  310   [ 66 /  90 / 243]
+//   N = 1080   228 /  209 /  343   [124 / 132 / 269]
+//   N = 3000  1117 /  806 /  862   [490 / 448 / 503]
+//   N = 4320  2198 / 1477 / 1426   [911 / 766 / 753]
+//   N = 7680  6641 / 4143 / 3885
+// Below about a thousand unknowns the wider tiles leave CUs without a block; above
+// some 3600 there are blocks enough for every edge and the widest evaluates the
+// fewest pairs twice.
+int tile_edge(int N) { return N <= 1024 ? 16 : (N <= 3600 ? 32 : TILE_LARGE); }
+
 // Z by tiles: the near blocks into the workspace, then one block per tile (each
 // launch bracketed for efie_prof_read)
 template <typename R>
@@ -205,8 +220,6 @@ void launch_tiles(const DevMesh& m, double kr, double ki, const Scale& sc, void*
     using C2 = typename Cplx<R>::T;
     EFIE_REQUIRE(ws_bytes >= size_t(m.n_near) * 9 * sizeof(C2), EFIE_ERR_ARG,
                  "assemble_ws: workspace smaller than the near-pair blocks");
-    const long long ntiles = tile_count<R>(m.N);
-    EFIE_REQUIRE(ntiles < (1ll << 31), EFIE_ERR_ARG, "assemble_ws: N too large");
     C2* NB = static_cast<C2*>(ws);
     if (m.n_up > 0) {
         prof_begin(PROF_NEAR, s);
@@ -214,14 +227,24 @@ void launch_tiles(const DevMesh& m, double kr, double ki, const Scale& sc, void*
                            0, s, m, kr, ki, sc, NB);
         prof_end(PROF_NEAR, s);
     }
-    const R kphase = std::is_same<R, float>::value ? R(kr / (2.0 * PI)) : R(kr);
+    const Phase<R> ph = make_phase<R>(kr, ki);
+    auto tiles = [&](auto edge) {
+        constexpr int TS = decltype(edge)::value;
+        const long long nt = tile_count(m.N, TS);
+        EFIE_REQUIRE(nt < (1ll << 31), EFIE_ERR_ARG, "assemble_ws: N too large");
+        if (ki != 0.0)
+            hipLaunchKernelGGL((tile_kernel<R, true, TS>), dim3(unsigned(nt)), dim3(256), 0, s, m, tables_of<R>(m), ph,
+                               sc, NB, static_cast<C2*>(Z));
+        else
+            hipLaunchKernelGGL((tile_kernel<R, false, TS>), dim3(unsigned(nt)), dim3(256), 0, s, m, tables_of<R>(m), ph,
+                               sc, NB, static_cast<C2*>(Z));
+    };
     prof_begin(PROF_FAR, s);
-    if (ki != 0.0)
-        hipLaunchKernelGGL((tile_kernel<R, true>), dim3(unsigned(ntiles)), dim3(256), 0, s, m, tables_of<R>(m),
-                           kphase, R(ki), sc, NB, static_cast<C2*>(Z));
-    else
-        hipLaunchKernelGGL((tile_kernel<R, false>), dim3(unsigned(ntiles)), dim3(256), 0, s, m, tables_of<R>(m),
-                           kphase, R(ki), sc, NB, static_cast<C2*>(Z));
+    switch (tile_edge(m.N)) {
+        case 16: tiles(std::integral_constant<int, 16>{}); break;
+        case 32: tiles(std::integral_constant<int, 32>{}); break;
+        default: tiles(std::integral_constant<int, TILE_LARGE>{}); break;
+    }
     prof_end(PROF_FAR, s);
 }
 
@@ -264,21 +287,21 @@ void pair_rows_chunk(const DevMesh& m, double kr, double ki, double eta, int dty
     auto run = [&](auto tag) {
         using R = decltype(tag);
         using C2 = typename Cplx<R>::T;
-        const R kphase = std::is_same<R, float>::value ? R(kr / (2.0 * PI)) : R(kr);
+        const Phase<R> ph = make_phase<R>(kr, ki);
         C2* w = static_cast<C2*>(W);
         auto far = [&](hipStream_t st) {
             if (ck && upper)
                 hipLaunchKernelGGL((far_rows_kernel<R, true, true>), g1, dim3(FAR_BLOCK), 0, st, m, tables_of<R>(m),
-                                   kphase, R(ki), sc, w, c0, np, nqblk);
+                                   ph, sc, w, c0, np, nqblk);
             else if (ck)
                 hipLaunchKernelGGL((far_rows_kernel<R, true, false>), g1, dim3(FAR_BLOCK), 0, st, m, tables_of<R>(m),
-                                   kphase, R(ki), sc, w, c0, np, nqblk);
+                                   ph, sc, w, c0, np, nqblk);
             else if (upper)
                 hipLaunchKernelGGL((far_rows_kernel<R, false, true>), g1, dim3(FAR_BLOCK), 0, st, m, tables_of<R>(m),
-                                   kphase, R(ki), sc, w, c0, np, nqblk);
+                                   ph, sc, w, c0, np, nqblk);
             else
                 hipLaunchKernelGGL((far_rows_kernel<R, false, false>), g1, dim3(FAR_BLOCK), 0, st, m, tables_of<R>(m),
-                                   kphase, R(ki), sc, w, c0, np, nqblk);
+                                   ph, sc, w, c0, np, nqblk);
         };
         auto near = [&](hipStream_t st) {
             hipLaunchKernelGGL((near_rows_kernel<R>), dim3(unsigned((int64_t(e1 - e0) * NEAR_G + 127) / 128)), dim3(128),

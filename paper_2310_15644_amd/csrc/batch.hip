@@ -102,16 +102,16 @@ __global__ __launch_bounds__(256) void batch_near_kernel(DevMesh cat, const Batc
 
 // the tiles of every mesh's Z: persistent, tile t by block t mod gridDim.x
 template <typename R>
-__global__ __launch_bounds__(256, sizeof(R) == 4 ? 3 : 1) void batch_tiles_kernel(
+__global__ __launch_bounds__(256, sizeof(R) == 4 ? 3 : 2) void batch_tiles_kernel(
     DevMesh cat, const BatchItem* __restrict__ items, int nm, int64_t ntiles,
     const typename Cplx<R>::T* __restrict__ NB, typename Cplx<R>::T* __restrict__ Z) {
-    __shared__ TileLds<R> L;
+    __shared__ TileLds<R, TILE_LARGE> L;
     for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
         const int r = item_of<&BatchItem::tile0>(items, nm, t);
         const BatchItem& it = items[r];
         const DevMesh v = mesh_view(cat, it);
-        const R kphase = std::is_same<R, float>::value ? R(it.kr / (2.0 * PI)) : R(it.kr);
-        tile_block<R, false>(v, tables_of<R>(v), kphase, R(0), it.sc, NB + it.nboff, Z + it.zoff, t - it.tile0, L);
+        const Phase<R> ph = make_phase<R>(it.kr, 0.0);
+        tile_block<R, false, TILE_LARGE>(v, tables_of<R>(v), ph, it.sc, NB + it.nboff, Z + it.zoff, t - it.tile0, L);
     }
 }
 
@@ -139,8 +139,10 @@ __global__ __launch_bounds__(256) void grouped_gemv_kernel(const ZT* __restrict_
     for (int k = lane; k < n; k += 64) {
         const ZT z = zr[k];
         const double2 v = xs[k];
-        ar += double(z.x) * v.x - double(z.y) * v.y;
-        ai += double(z.x) * v.y + double(z.y) * v.x;
+        ar = fma(double(z.x), v.x, ar);
+        ar = fma(-double(z.y), v.y, ar);
+        ai = fma(double(z.x), v.y, ai);
+        ai = fma(double(z.y), v.x, ai);
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
@@ -153,7 +155,9 @@ __global__ __launch_bounds__(256) void grouped_gemv_kernel(const ZT* __restrict_
 // ------------------------------------------------------------- grouped COCG
 // One block per mesh; vectors of mesh s at [voff[s], voff[s+1]).  Same recurrences
 // as the single-mesh COCG (CG with the unconjugated bilinear form).
-constexpr int BKB = 256;
+// The products, the block size and the order of every sum are those of the
+// single-mesh solver's one-column path, so that both take the same steps.
+constexpr int BKB = 512;
 
 __device__ void bsum(double (&v)[4], double* sh) {
 #pragma unroll
@@ -437,7 +441,7 @@ extern "C" int efie_batch_sizes(efie_batch b, size_t* table_bytes, size_t* ws_by
         if (v_elems) *v_elems = b->v_total;
         if (items) {   // work items of the persistent assembly launch: complex64 tiles of all meshes
             int64_t t = 0;
-            for (size_t i = 0; i < nm; ++i) t += tile_count<float>(int(b->meshes[i]->N));
+            for (size_t i = 0; i < nm; ++i) t += tile_count(int(b->meshes[i]->N), TILE_LARGE);
             *items = t;
         }
         return int(EFIE_OK);
@@ -527,7 +531,7 @@ extern "C" int efie_batch_assemble(efie_batch b, const double* k, double eta, in
             it.nf = m.near_factor;
             it.far3 = m.far3;
             it.sc = operator_scale(k[i], 0.0, eta);
-            tile += dtype == EFIE_C64 ? tile_count<float>(int(m.N)) : tile_count<double>(int(m.N));
+            tile += tile_count(int(m.N), TILE_LARGE);
             nblk += (int64_t(m.near_up.size()) + NEAR_PER_BLOCK - 1) / NEAR_PER_BLOCK;
         }
         EFIE_REQUIRE(nblk < (int64_t(1) << 31), EFIE_ERR_ARG, "batch_assemble: too many near pairs");

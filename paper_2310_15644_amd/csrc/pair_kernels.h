@@ -9,6 +9,7 @@
 #include <cmath>
 
 #include "efie_internal.h"
+#include "phase_math.h"
 
 namespace efie {
 
@@ -67,105 +68,141 @@ __device__ __forceinline__ void atomic_add_c<float>(void* Z, size_t idx, float r
     atomicAdd(z + 1, im);
 }
 
-// exp(-j k R) / R for k = kr + j ki.  FP64: library sincos/exp.
-__device__ __forceinline__ void green_far(double kr, double ki, bool ck, double R2, double& gr, double& gi) {
-    double rinv = rsqrt(R2);
-    double R = R2 * rinv;
-    double s, c;
-    sincos(kr * R, &s, &c);
-    double e = ck ? exp(ki * R) * rinv : rinv;
-    gr = c * e;
-    gi = -s * e;
-}
-// FP32: the phase is passed in revolutions (k / 2 pi) and evaluated with the
-// hardware sine/cosine, whose input is in revolutions (valid for |x| < 256).
-__device__ __forceinline__ void green_far(float krev, float ki, bool ck, float R2, float& gr, float& gi) {
-    float rinv = __builtin_amdgcn_rsqf(R2);
-    float R = R2 * rinv;
-    float x = krev * R;
-    float s = __builtin_amdgcn_sinf(x);
-    float c = __builtin_amdgcn_cosf(x);
-    float e = ck ? __expf(ki * R) * rinv : rinv;
-    gr = c * e;
-    gi = -s * e;
-}
-
 // -------------------------------------------------------- far-pair kernel
-// The pair (p, q) of one mesh (not near): the 7 x 7 Green's function moments and
-// the nine half-function products.  emit(i, j, zr, zi) receives the Z
-// contribution of test edge i of p and source edge j of q (PARTS: zr, zi are the
-// T_A part and emit2 gets the T_Phi part).
-// The product rule of NP points per triangle, point offsets and weights from the
-// tables (qx, qy, qz, qw), [NP][T].
-// PRE: the source triangle's points and weights come from pre[4][NP] (x, y, z, w)
-// already in registers instead of the tables
+// The two product rules in barycentric form.  The points of the 7-point rule are
+// the centroid and two orbits (1 - 2 b, b, b) and permutations, those of the
+// 3-point rule one orbit; the weight times barycentric coordinate k of a point is
+// then a constant, and the moments
+//   M_kl = sum_ab w_a lambda_k(a) w_b lambda_l(b) G_ab
+// take the sums of an orbit first (13 operations per seven Green's functions and
+// part, against 28 with Cartesian moments and weights of the triangle).
+template <int NP>
+struct Bary;
+template <>
+struct Bary<7> {
+    static constexpr double S15 = 3.872983346207417;
+    static constexpr double W0 = 9.0 / 40.0, W1 = (155.0 + S15) / 1200.0, W2 = (155.0 - S15) / 1200.0;
+    static constexpr double B1 = (6.0 + S15) / 21.0, B2 = (6.0 - S15) / 21.0;
+    static constexpr double D1 = (9.0 - 2.0 * S15) / 21.0 - B1, D2 = (9.0 + 2.0 * S15) / 21.0 - B2;
+    template <typename R>
+    static __device__ __forceinline__ void fold(const R (&g)[7], R (&s)[3]) {
+        const R o1 = g[1] + g[2] + g[3], o2 = g[4] + g[5] + g[6];
+        const R t = R(W0 / 3.0) * g[0] + R(W1 * B1) * o1 + R(W2 * B2) * o2;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) s[k] = t + R(W1 * D1) * g[1 + k] + R(W2 * D2) * g[4 + k];
+    }
+    static constexpr double coef(int a, int k) {   // weight of point a times its coordinate k
+        return a == 0 ? W0 / 3.0 : (a < 4 ? W1 * (B1 + (k == a - 1 ? D1 : 0.0)) : W2 * (B2 + (k == a - 4 ? D2 : 0.0)));
+    }
+};
+template <>
+struct Bary<3> {
+    template <typename R>
+    static __device__ __forceinline__ void fold(const R (&g)[3], R (&s)[3]) {
+        const R t = R(1.0 / 18.0) * (g[0] + g[1] + g[2]);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) s[k] = t + R(1.0 / 6.0) * g[k];
+    }
+    static constexpr double coef(int a, int k) { return 1.0 / 18.0 + (k == a ? 1.0 / 6.0 : 0.0); }
+};
+
+// the coefficients as a table, read with scalar loads by the (uniform) test point
+template <int NP, typename R>
+struct BaryTable {
+    R c[NP][3];
+    constexpr BaryTable() : c{} {
+        for (int a = 0; a < NP; ++a)
+            for (int k = 0; k < 3; ++k) c[a][k] = R(Bary<NP>::coef(a, k));
+    }
+};
+template <int NP, typename R>
+__device__ constexpr BaryTable<NP, R> bary_table{};
+
+// The pair (p, q) of one mesh (not near): the NP x NP Green's function moments in
+// barycentric form and the nine half-function products.  emit(i, j, zr, zi)
+// receives the Z contribution of test edge i of p and source edge j of q (PARTS:
+// zr, zi are the T_A part and emit2 gets the T_Phi part).
+// (qx, qy, qz): the point offsets of the product rule, [NP][T].
+// PRE: the source triangle's points come from pre[3][NP] already in registers
+// instead of the tables
 template <int NP, typename R, bool CK, bool PARTS, bool PRE = false, typename Emit, typename Emit2>
 __device__ __forceinline__ void far_pair_rule(const DevMesh& m, const Tables<R>& tb, const R* __restrict__ qx,
-                                              const R* __restrict__ qy, const R* __restrict__ qz,
-                                              const R* __restrict__ qw, int p, int q, R kphase, R ki,
-                                              const Scale& sc, Emit emit, Emit2 emit2,
+                                              const R* __restrict__ qy, const R* __restrict__ qz, int p, int q,
+                                              const Phase<R>& ph, const Scale& sc, Emit emit, Emit2 emit2,
                                               const R (*pre)[NP] = nullptr) {
     const int T = m.T;
     const R Dx = R(m.cx[p] - m.cx[q]);
     const R Dy = R(m.cy[p] - m.cy[q]);
     const R Dz = R(m.cz[p] - m.cz[q]);
-    R sx[NP], sy[NP], sz[NP], sw[NP];
+    R sx[NP], sy[NP], sz[NP];
 #pragma unroll
     for (int b = 0; b < NP; ++b) {
         sx[b] = PRE ? pre[0][b] : qx[b * T + q];
         sy[b] = PRE ? pre[1][b] : qy[b * T + q];
         sz[b] = PRE ? pre[2][b] : qz[b * T + q];
-        sw[b] = PRE ? pre[3][b] : qw[b * T + q];
     }
-    R m0r = 0, m0i = 0;
-    R mdr[3] = {0, 0, 0}, mdi[3] = {0, 0, 0};     // sum W W G d_a
-    R mpr[3] = {0, 0, 0}, mpi[3] = {0, 0, 0};     // sum W W G d'_b
-    R mmr = 0, mmi = 0;                             // sum W W G d_a . d'_b
+    R Mr[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}}, Mi[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
 #pragma unroll 1
     for (int a = 0; a < NP; ++a) {
-        const R ax = qx[a * T + p], ay = qy[a * T + p], az = qz[a * T + p], wa = qw[a * T + p];
-        const R ox = Dx + ax, oy = Dy + ay, oz = Dz + az;
-        R s0r = 0, s0i = 0, s1r[3] = {0, 0, 0}, s1i[3] = {0, 0, 0};
+        const R ox = Dx + qx[a * T + p], oy = Dy + qy[a * T + p], oz = Dz + qz[a * T + p];
+        R gr[NP], gi[NP];
 #pragma unroll
         for (int b = 0; b < NP; ++b) {
             const R dx = ox - sx[b], dy = oy - sy[b], dz = oz - sz[b];
-            const R R2 = dx * dx + dy * dy + dz * dz;
-            R gr, gi;
-            green_far(kphase, ki, CK, R2, gr, gi);
-            gr *= sw[b];
-            gi *= sw[b];
-            s0r += gr;
-            s0i += gi;
-            s1r[0] += gr * sx[b]; s1i[0] += gi * sx[b];
-            s1r[1] += gr * sy[b]; s1i[1] += gi * sy[b];
-            s1r[2] += gr * sz[b]; s1i[2] += gi * sz[b];
+            green_far(ph, CK, dx * dx + dy * dy + dz * dz, gr[b], gi[b]);
         }
-        m0r += wa * s0r;
-        m0i += wa * s0i;
-        const R av[3] = {ax, ay, az};
+        R sr[3], si[3];
+        Bary<NP>::fold(gr, sr);
+        Bary<NP>::fold(gi, si);
+        const R(&ca)[3] = bary_table<NP, R>.c[a];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            mdr[d] += wa * av[d] * s0r;
-            mdi[d] += wa * av[d] * s0i;
-            mpr[d] += wa * s1r[d];
-            mpi[d] += wa * s1i[d];
-        }
-        mmr += wa * (ax * s1r[0] + ay * s1r[1] + az * s1r[2]);
-        mmi += wa * (ax * s1i[0] + ay * s1i[1] + az * s1i[2]);
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int l = 0; l < 3; ++l) {
+                Mr[k][l] += ca[k] * sr[l];
+                Mi[k][l] += ca[k] * si[l];
+            }
     }
-    // nine half-function products
-    R uq[3][3], cq[3], gq[3];
+    // nine half-function products from M0 = sum M_kl, Md = sum M_kl v_k,
+    // Md' = sum M_kl v'_l and Mdd' = sum M_kl v_k . v'_l (vertex offsets)
+    R up[3][3], uq[3][3], cq[3], gq[3];
+    const R area2 = (tb.qw[p] * tb.qw[q]) * R(1.0 / (Bary<7>::W0 * Bary<7>::W0));   // the areas' product
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
         uq[j][0] = tb.vx[j * T + q];
         uq[j][1] = tb.vy[j * T + q];
         uq[j][2] = tb.vz[j * T + q];
-        cq[j] = tb.cf[j * T + q];
-        gq[j] = tb.dv[j * T + q];
+        cq[j] = tb.cf[j * T + q] * area2;
+        gq[j] = tb.dv[j * T + q] * area2;
+        up[j][0] = tb.vx[j * T + p];
+        up[j][1] = tb.vy[j * T + p];
+        up[j][2] = tb.vz[j * T + p];
+    }
+    R m0r = 0, m0i = 0, mmr = 0, mmi = 0;
+    R mdr[3] = {0, 0, 0}, mdi[3] = {0, 0, 0}, mpr[3] = {0, 0, 0}, mpi[3] = {0, 0, 0};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const R rr = Mr[k][0] + Mr[k][1] + Mr[k][2], ri = Mi[k][0] + Mi[k][1] + Mi[k][2];
+        const R cr = Mr[0][k] + Mr[1][k] + Mr[2][k], ci = Mi[0][k] + Mi[1][k] + Mi[2][k];
+        m0r += rr;
+        m0i += ri;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            mdr[d] += rr * up[k][d];
+            mdi[d] += ri * up[k][d];
+            mpr[d] += cr * uq[k][d];
+            mpi[d] += ci * uq[k][d];
+        }
+#pragma unroll
+        for (int l = 0; l < 3; ++l) {
+            const R dot = up[k][0] * uq[l][0] + up[k][1] * uq[l][1] + up[k][2] * uq[l][2];
+            mmr += Mr[k][l] * dot;
+            mmi += Mi[k][l] * dot;
+        }
     }
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-        const R ux = tb.vx[i * T + p], uy = tb.vy[i * T + p], uz = tb.vz[i * T + p];
+        const R ux = up[i][0], uy = up[i][1], uz = up[i][2];
         const R ci = tb.cf[i * T + p], gi_ = tb.dv[i * T + p];
         // terms that depend on i only
         const R bir = mmr - (ux * mpr[0] + uy * mpr[1] + uz * mpr[2]);
@@ -194,17 +231,17 @@ __device__ __forceinline__ void far_pair_rule(const DevMesh& m, const Tables<R>&
 // The far pair (p, q) by the 7x7 rule, or by the 3x3 rule where the adaptive far
 // rule is on (m.far3 > 0) and the pair is far enough.
 template <typename R, bool CK, bool PARTS, typename Emit, typename Emit2>
-__device__ __forceinline__ void far_pair_emit(const DevMesh& m, const Tables<R>& tb, int p, int q, R kphase, R ki,
+__device__ __forceinline__ void far_pair_emit(const DevMesh& m, const Tables<R>& tb, int p, int q, const Phase<R>& ph,
                                               const Scale& sc, Emit emit, Emit2 emit2) {
     if (m.far3 > 0.0 && far3_pair(m, p, q))
-        far_pair_rule<3, R, CK, PARTS>(m, tb, tb.q3x, tb.q3y, tb.q3z, tb.q3w, p, q, kphase, ki, sc, emit, emit2);
+        far_pair_rule<3, R, CK, PARTS>(m, tb, tb.q3x, tb.q3y, tb.q3z, p, q, ph, sc, emit, emit2);
     else
-        far_pair_rule<NQ, R, CK, PARTS>(m, tb, tb.qx, tb.qy, tb.qz, tb.qw, p, q, kphase, ki, sc, emit, emit2);
+        far_pair_rule<NQ, R, CK, PARTS>(m, tb, tb.qx, tb.qy, tb.qz, p, q, ph, sc, emit, emit2);
 }
 
 // The pair (p, q) added to Z (and Z2 in parts mode) with atomics; near pairs skipped.
 template <typename R, bool CK, bool PARTS>
-__device__ __forceinline__ void far_pair(const DevMesh& m, const Tables<R>& tb, int p, int q, R kphase, R ki,
+__device__ __forceinline__ void far_pair(const DevMesh& m, const Tables<R>& tb, int p, int q, const Phase<R>& ph,
                                          const Scale& sc, void* Z, void* Z2) {
     const int T = m.T;
     if (is_near(m, p, q)) return;
@@ -214,7 +251,7 @@ __device__ __forceinline__ void far_pair(const DevMesh& m, const Tables<R>& tb, 
             atomic_add_c<R>(dst, size_t(m.te[i * T + p]) * N + size_t(m.te[j * T + q]), re, im);
         };
     };
-    far_pair_emit<R, CK, PARTS>(m, tb, p, q, kphase, ki, sc, at(Z), at(Z2));
+    far_pair_emit<R, CK, PARTS>(m, tb, p, q, ph, sc, at(Z), at(Z2));
 }
 
 // ----------------------------------------------------- closed-form potentials
@@ -300,22 +337,26 @@ static __device__ void singular_point(const DevMesh& m, int t, int s, int a, dou
 
 // (exp(-jkR) - 1)/R with exp(z) - 1 = expm1(x) cos y - 2 sin^2(y/2) + j exp(x) sin y,
 // z = -j k R = x + j y; value -j k at R = 0.
-static __device__ __forceinline__ void green_smooth(double kr, double ki, double R2, double& gr, double& gi) {
+static __device__ __forceinline__ void green_smooth(const Phase<double>& ph, double kr, double ki, double R2,
+                                                    double& gr, double& gi) {
     if (R2 == 0.0) {
         gr = ki;
         gi = -kr;
         return;
     }
-    const double R = sqrt(R2);
-    const double x = ki * R, y = -kr * R;
+    const double rinv = rsqrt_fast(R2);
+    const double R = R2 * rinv;
     double s2, c2;
-    sincos(0.5 * y, &s2, &c2);
+    sincos_quarter(R, -0.5 * ph.khi, -0.5 * ph.klo, s2, c2);   // of y / 2
     const double siny = 2.0 * s2 * c2;
-    const double cosy = 1.0 - 2.0 * s2 * s2;
-    const double nr = expm1(x) * cosy - 2.0 * s2 * s2;
-    const double ni = exp(x) * siny;
-    gr = nr / R;
-    gi = ni / R;
+    double nr = -2.0 * s2 * s2, ni = siny;
+    if (ki != 0.0) {   // uniform over the launch
+        const double x = ki * R;
+        nr = expm1(x) * (1.0 + nr) + nr;
+        ni *= exp2_scaled(R, ph.ehi, ph.elo);
+    }
+    gr = nr * rinv;
+    gi = ni * rinv;
 }
 
 // Near pair e of the ordered list, computed by a group of NEAR_G = 8 consecutive
@@ -346,12 +387,13 @@ __device__ void near_pair_group(const DevMesh& m, int e, int g, double kr, doubl
         const double D[3] = {m.cx[p] - m.cx[q], m.cy[p] - m.cy[q], m.cz[p] - m.cz[q]};
         const double ax = m.qx[a * T + p], ay = m.qy[a * T + p], az = m.qz[a * T + p], wa = m.qw[a * T + p];
         double s0r = 0, s0i = 0, s1r[3] = {0, 0, 0}, s1i[3] = {0, 0, 0};
+        const Phase<double> ph = make_phase<double>(kr, ki);
 #pragma unroll 1
         for (int b = 0; b < NQ; ++b) {
             const double bx = m.qx[b * T + q], by = m.qy[b * T + q], bz = m.qz[b * T + q], wb = m.qw[b * T + q];
             const double dx = D[0] + ax - bx, dy = D[1] + ay - by, dz = D[2] + az - bz;
             double gr, gi;
-            green_smooth(kr, ki, dx * dx + dy * dy + dz * dz, gr, gi);
+            green_smooth(ph, kr, ki, dx * dx + dy * dy + dz * dz, gr, gi);
             gr *= wb;
             gi *= wb;
             s0r += gr; s0i += gi;

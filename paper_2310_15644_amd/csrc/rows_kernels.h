@@ -55,18 +55,24 @@ __host__ __device__ inline Tables<float> tables_of<float>(const DevMesh& m) {
 // entries of triangles q >= p and restores the other half from the symmetry of
 // the operator).
 template <typename R, bool CK, bool UPPER>
-__device__ __forceinline__ void far_rows_block(const DevMesh& m, const Tables<R>& tb, R kphase, R ki, const Scale& sc,
+__device__ __forceinline__ void far_rows_block(const DevMesh& m, const Tables<R>& tb, const Phase<R>& ph, const Scale& sc,
                                                typename Cplx<R>::T* __restrict__ W, int c0, int np, int nqblk,
                                                int logical) {
     using C2 = typename Cplx<R>::T;
     const int pg = logical / nqblk, qb = logical - pg * nqblk;
-    const int q = qb * FAR_BLOCK + int(threadIdx.x);
+    const int q0 = qb * FAR_BLOCK + int(threadIdx.x);
     const int T = m.T;
-    if (q >= T) return;
+    if (q0 >= T) return;
     const size_t N = size_t(m.N);
     const int pl1 = min(np, (pg + 1) * FAR_PB);
+#pragma unroll 1
     for (int pl = pg * FAR_PB; pl < pl1; ++pl) {
         const int p = c0 + pl;
+        // the source index is opaque to the compiler in each turn: it would keep the
+        // source triangle's tables of both rules in registers across the turns (256
+        // VGPRs and one wave per SIMD in FP64; reread, they are cache hits)
+        int q = q0;
+        asm volatile("" : "+v"(q));
         C2* rows = W + size_t(pl) * 3 * 2 * N;
         auto put = [&](int i, int j, R re, R im) {
             const size_t n = size_t(m.te[j * T + q]);
@@ -83,7 +89,7 @@ __device__ __forceinline__ void far_rows_block(const DevMesh& m, const Tables<R>
                 for (int j = 0; j < 3; ++j) put(i, j, R(0), R(0));
             continue;
         }
-        far_pair_emit<R, CK, false>(m, tb, p, q, kphase, ki, sc, put, put);
+        far_pair_emit<R, CK, false>(m, tb, p, q, ph, sc, put, put);
     }
 }
 
