@@ -36,6 +36,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK_FP32_MFMA = 157.3      # TFLOP/s, MI355X dense FP32 matrix
+PEAK_FP16_MFMA = 2500.0     # TFLOP/s, MI355X dense fp16 matrix
 PEAK_HBM = 8000.0           # GB/s
 PEAK_FP32_VALU = 78.6       # TFLOP/s with FMA = 2 flops, packed FP32 disabled (256 CU x 64 lanes x 2.4 GHz x 2)
 VALU_LANE_SLOTS = 256 * 64 * 2.4e9   # vector-ALU lane-instructions per second
@@ -115,6 +116,7 @@ def cpu_baseline(level, n_sample_rows, nrhs, k, seconds):
 TRAFFIC_FILES = {False: os.path.join(ROOT, "profiles", "cgemm_planar_fp32acc_l5_k10_512rhs_hbm_traffic.md"),
                  True: os.path.join(ROOT, "profiles", "cgemm_planar_flush64_l5_k10_512rhs_hbm_traffic.md")}
 GEMM_SOURCE = os.path.join(ROOT, "paper_2310_15644_amd", "csrc", "gemm_mfma.hip")
+SPLIT_SOURCE = os.path.join(ROOT, "paper_2310_15644_amd", "csrc", "gemm_split.h")
 
 
 def gemm_code_sha256(path=None):
@@ -148,9 +150,11 @@ def measured_traffic(tiles, acc64, n, nrhs, solver):
             key, val = line[2:].split(": ", 1)
             entries[-1][key.strip()] = val.strip().strip("`")
     sha = gemm_code_sha256()
+    split = gemm_code_sha256(SPLIT_SOURCE)
     want = gemm_kernel_name(tiles, acc64)
     for kv in entries:
-        if (kv.get("gemm_code_sha256") == sha and kv.get("kernel") == want
+        # an entry of the split kernel names its own source's hash as well
+        if (kv.get("gemm_code_sha256") == sha and kv.get("split_code_sha256", split) == split and kv.get("kernel") == want
                 and kv.get("workload") == f"n={n} nrhs={nrhs} solver={solver}"):
             return float(kv["hbm_bytes_per_launch"]), os.path.relpath(path, ROOT)
     return None, None
@@ -1015,6 +1019,11 @@ def main():
     }
     tiles = None if tuning is None else tuning["tiles"][tuning["acc32" if args.fp32_acc else "acc64"]]
     out["roofline"]["kernel"] = None if tiles is None else P.gemm_kernel_name(tiles, not args.fp32_acc)
+    if tiles is not None and tiles[2] == 64:
+        # the split kernel: three fp16 products for each FP32 one, against the fp16 matrix peak
+        out["roofline"]["peak"] = round(PEAK_FP16_MFMA / 3.0, 1)
+        out["roofline"]["frac"] = round(out["roofline"]["achieved"] * 3.0 / PEAK_FP16_MFMA, 4)
+        out["roofline"]["executed_flop_fraction"] = 3.0
     out["roofline"]["traffic"], out["roofline"]["traffic_source"] = measured_traffic(
         tiles, not args.fp32_acc, out["config"]["n_unknowns"], S, args.solver)
     # the assembly's HBM bytes (rocprofv3 counters) against Z's and the 8 TB/s peak

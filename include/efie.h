@@ -254,8 +254,12 @@ int efie_vertex_grad(efie_mesh mesh, double k, double eta, const void* J, const 
  * Y = Z X for a dense complex matrix Z (n x n, row-major, either dtype) and
  * nrhs vectors X (nrhs, n).  X and Y have the dtype of Z.
  *   nrhs == 1: HBM-bound GEMV (accumulation in FP64 for both dtypes);
- *   nrhs > 1 : EFIE_C64 -> FP32 matrix-core (MFMA) GEMM with FP32 accumulation,
- *              EFIE_C128 -> FP64 GEMM.
+ *   nrhs > 1 : EFIE_C64 -> matrix-core (MFMA) GEMM: by default the fp16 split product
+ *              (each operand in two fp16 parts, three products, sums of at most 64
+ *              terms added in FP64: an FP32 product's accuracy or better), or a
+ *              selected FP32 tile with FP32 accumulation; EFIE_C128 -> FP64 GEMM.
+ *              A row of X or of Z that holds a non-finite value gives non-finite
+ *              results there (an infinity may give NaN).
  */
 int efie_zx(const void* Z, int dtype, int64_t n, const void* X, void* Y, int64_t nrhs,
             hipStream_t stream);
@@ -263,8 +267,9 @@ int efie_zx(const void* Z, int dtype, int64_t n, const void* X, void* Y, int64_t
 /*
  * The mixed solves' product as a call of its own: Y = Z X with Z complex64
  * (n x n) and X, Y complex128 (nrhs, n).  X is rounded to complex64 and
- * multiplied on the FP32 matrix cores with the partial sums of every two K
- * chunks (at most 64 complex terms) flushed into FP64 accumulators; Y is
+ * multiplied on the matrix cores (the default fp16 split product, or a selected FP32
+ * tile) with partial sums of at most 64 complex terms
+ * flushed into FP64 accumulators; Y is
  * written in complex128.  Any nrhs >= 1
  * takes the matrix cores here.  ws: dev scratch of at least
  * efie_zx_flush64_workspace_size bytes, 16-byte aligned.  Y must not overlap X.
@@ -295,7 +300,10 @@ int efie_zx_flush64_noalloc(const void* Z, int64_t n, const void* X, void* Y, in
 /* ------------------------------------------------------- GEMM autotuning */
 
 /*
- * The complex64 matrix-core GEMM has several tile shapes (block tile of BM
+ * The complex64 matrix-core GEMM has several variants: FP32 tiles and, last in the
+ * table and selected by default, the fp16 split product (listed by its widest tile,
+ * K chunk 64; narrower ones are taken where those would leave CUs idle).  A variant
+ * has a tile shape (block tile of BM
  * right-hand sides x BN unknowns, K chunk KC of complex elements), for two
  * paths: complex64
  * output (efie_zx) and FP64-flushed output into the Krylov vectors (solves).

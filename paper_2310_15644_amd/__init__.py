@@ -542,6 +542,8 @@ def gemm_variants():
 def gemm_kernel_name(variant, acc64: bool) -> str:
     """The kernel's name as profilers print it (template arguments included)."""
     bm, bn, kc = variant[:3]
+    if kc == 64:   # the fp16 split kernel, by its widest tile
+        return f"cgemm_split_kernel<{bm // 32}, {bn // 32}, 1, {kc}, {'true' if acc64 else 'false'}, 2>"
     return f"cgemm_planar_kernel<{bm}, {bn}, {kc}, {'true' if acc64 else 'false'}>"
 
 

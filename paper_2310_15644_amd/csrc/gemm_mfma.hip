@@ -1,4 +1,6 @@
-// Complex64 Y = X Z^T on FP32 matrix cores (MFMA).
+// Complex64 Y = X Z^T on matrix cores (MFMA): the dispatch, and the kernels on the
+// FP32 matrix cores (the default is the fp16 split kernel of gemm_split.h; these stay
+// selectable by efie_gemm_select and the autotuner).
 //
 // Planar complex form: the K chunks of X (right-hand sides) and Z (the
 // symmetric operator, whose rows are the output unknowns) are staged in LDS as
@@ -40,6 +42,7 @@
 
 #include "efie_internal.h"
 #include "linalg.h"
+#include "gemm_split.h"
 
 namespace efie {
 
@@ -275,9 +278,13 @@ struct Variant {
     int bm, bn, kc;
 };
 static constexpr Variant kVariants[] = {{64, 32, 32}, {64, 64, 16}, {64, 64, 32}, {128, 32, 16},
-                                    {32, 64, 16}, {128, 64, 16}, {64, 32, 16}, {64, 128, 16}};
+                                    {32, 64, 16}, {128, 64, 16}, {64, 32, 16}, {64, 128, 16},
+                                    {64, 64, 64}};
 static constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
-static int g_variant[2] = {1, 2};   // defaults: complex64 output, FP64-flush output
+// the last: the fp16 split kernel with the tile of launch_split_rule; the default of
+// both paths (complex64 output, FP64-flush output)
+static constexpr int kSplitVariant = kNumVariants - 1;
+static int g_variant[2] = {kSplitVariant, kSplitVariant};
 
 // X rows readable: mcap >= M; the kernel reads up to the tile's multiple of M
 // within them, so that a ragged last tile still takes the unchecked loads
@@ -291,6 +298,36 @@ static void launch_v(const void* X, const void* Z, void* Y, const int* yrow, int
                        static_cast<const float2*>(X), static_cast<const float2*>(Z), Y, M, mrows, n, yrow);
 }
 
+template <int WM, int WN, int WK, int KC, bool A64, int MINW>
+static void launch_split(const void* X, const void* Z, void* Y, const int* yrow, int M, int n, hipStream_t s) {
+    const size_t nblk = size_t((M + 32 * WM - 1) / (32 * WM)) * ((n + 32 * WN - 1) / (32 * WN));
+    EFIE_REQUIRE(nblk < (size_t(1) << 31), EFIE_ERR_ARG, "cgemm: problem too large");
+    hipLaunchKernelGGL((cgemm_split_kernel<WM, WN, WK, KC, A64, MINW>), dim3(unsigned(nblk)), dim3(64 * WM * WN * WK), 0,
+                       s, static_cast<const float2*>(X), static_cast<const float2*>(Z), Y, M, n, yrow);
+}
+
+// The tile of the split kernel by the number of blocks (256 CUs; times in us with
+// 32 x 32 tiles and 4 K groups / 64 x 32 and 4 groups / 64 x 64 / 32 x 32 and 2 groups of
+// 64-term chunks):
+//   n = 1920,  M = 100:   41 /  48 /  80 /  56        n =  1920, M = 16:  36 /  45 /  76 /  53
+//   n = 4317,  M = 45:   172 / 102 / 176 / 121        n =  4320, M = 64: 160 /  98 / 175 / 119
+//   n = 12000, M = 33:   695 / 541 / 499 / 671        n = 12000, M = 20: 457 / 530 / 487 / 332
+//   n = 7679,  M = 200: 1062 / 712 / 489 / 840        n = 30720, M = 512: 34.5 / 20.9 / 14.6 / 25.3 ms
+// A matrix that gives at most one block per CU is split over K inside the block, by the
+// smallest tile that still does; otherwise the widest tile converts the least.
+template <bool A64>
+static void launch_split_rule(const void* X, const void* Z, void* Y, const int* yrow, int M, int n, hipStream_t s) {
+    const int64_t m32 = (M + 31) / 32, m64 = (M + 63) / 64, n32 = (int64_t(n) + 31) / 32;
+    if (m32 * n32 <= 256)
+        launch_split<1, 1, 4, 32, A64, 2>(X, Z, Y, yrow, M, n, s);
+    else if (M <= 32)
+        launch_split<1, 1, 2, 64, A64, 2>(X, Z, Y, yrow, M, n, s);
+    else if (m64 * n32 <= 256)
+        launch_split<2, 1, 4, 32, A64, 2>(X, Z, Y, yrow, M, n, s);
+    else
+        launch_split<2, 2, 1, 64, A64, 2>(X, Z, Y, yrow, M, n, s);
+}
+
 template <bool A64>
 static void launch_variant(int v, const void* X, const void* Z, void* Y, const int* yrow, int M, int mcap, int n,
                            hipStream_t s) {
@@ -302,7 +339,8 @@ static void launch_variant(int v, const void* X, const void* Z, void* Y, const i
         case 4: launch_v<32, 64, 16, A64>(X, Z, Y, yrow, M, mcap, n, s); break;
         case 5: launch_v<128, 64, 16, A64>(X, Z, Y, yrow, M, mcap, n, s); break;
         case 6: launch_v<64, 32, 16, A64>(X, Z, Y, yrow, M, mcap, n, s); break;
-        default: launch_v<64, 128, 16, A64>(X, Z, Y, yrow, M, mcap, n, s); break;
+        case 7: launch_v<64, 128, 16, A64>(X, Z, Y, yrow, M, mcap, n, s); break;
+        default: launch_split_rule<A64>(X, Z, Y, yrow, M, n, s); break;
     }
 }
 
@@ -320,9 +358,10 @@ void cgemm_mfma(const void* X, const void* Z, void* Y, int M, int n, hipStream_t
 void cgemm_mfma_acc64(const void* X, const void* Z, double2* Y, const int* yrow, int M, int n, hipStream_t s,
                       int mcap, bool small_tile) {
     const bool small = small_tile && M <= kVariants[kSmallVariant].bm;
+    const int v = small && g_variant[1] != kSplitVariant ? kSmallVariant : g_variant[1];
     const ProfId id = small ? PROF_MFMA_SMALL : PROF_MFMA;   // timed apart from the selected tile
     prof_begin(id, s);
-    launch_variant<true>(small ? kSmallVariant : g_variant[1], X, Z, Y, yrow, M, std::max(M, mcap), n, s);
+    launch_variant<true>(v, X, Z, Y, yrow, M, std::max(M, mcap), n, s);
     prof_end(id, s, 8.0 * M * double(n) * n);
 }
 

@@ -1,0 +1,262 @@
+// Complex64 Y = X Z^T on the fp16 matrix cores, every operand in two fp16 parts.
+//
+// Splitting.  A row's chunk of KC complex elements is scaled by the power of two that
+// takes its largest real or imaginary part to [2^14, 2^15); each scaled value x is
+// h + l with h the nearest fp16 number and l the nearest to the (exact) remainder:
+// |x - h - l| <= 2^-23 |x| down to 2^-17 of the chunk's largest part, below that at most
+// 2^-40 of the largest part.  A product takes three fp16 products, h h', h l' and l h',
+// each exact in the matrix core's FP32 accumulator; l l' is below 2^-22 of the product
+// and left out.  Non-finite values stay non-finite (an infinity gives NaN).
+// Accumulation.  The FP32 sums of one chunk (at most 64 complex terms) are scaled back
+// and added to FP64 accumulators, for complex64 and complex128 results alike.  Measured
+// against the FP64 product of the stored values (2-norm): 1.0e-7 to 1.4e-7 for orders
+// 300 to 30720, where the FP32 matrix cores give 1.6e-7 to 2.4e-7 with FP64 flushes
+// and 4.4e-7 to 6.0e-6 with FP32 sums.
+//
+// Why.  The FP32 matrix cores reach 157 TFLOP/s: the planar kernels ran at 0.85 to
+// 0.95 of that, 25.8 to 28.8 ms for 30720 x 30720 times 512.  Three fp16 products take
+// 3/16 of the time of one FP32 product.  This kernel takes 14.6 ms (265 TFLOP/s of
+// complex products, 0.32 of the fp16 peak over three).  Bound by instruction issue: of
+// the cycles of a SIMD about 0.45 hold matrix instructions and 0.45 vector ones (splits,
+// scaling back), which hardly overlap, and the clock falls below 2.4 GHz under the
+// matrix load.  Three bf16 parts need no scaling but six products: 22.4 ms at 1.9 GHz.
+// Parts by mixed-precision fused multiply-adds to fp16 (half rate): 15.4 ms.
+//
+// Layout.  Per chunk and group: the rows' h and l planes of the real and imaginary
+// parts in LDS, rows padded by 8 values (16-byte reads without bank conflicts), one
+// buffer; the next chunk's global loads are in flight during the multiply.  Eight lanes
+// hold a row's chunk, so that its maximum takes three lane exchanges.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include "efie_internal.h"
+
+namespace efie {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
+typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+// two complex64 values, 8-byte aligned (rows of odd order)
+typedef float floatx4u __attribute__((ext_vector_type(4), aligned(8)));
+
+// max(m, |a|, |b|) (the compiler's fmaxf adds a canonicalization for each operand)
+__device__ __forceinline__ float max3_abs(float m, float a, float b) {
+    float r;
+    asm("v_max3_f32 %0, %1, |%2|, |%3|" : "=v"(r) : "v"(m), "v"(a), "v"(b));
+    return r;
+}
+// maximum of non-negative floats over aligned groups of 8 lanes (their bits compare
+// as unsigned integers)
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_max(uint32_t v) {
+    return max(v, uint32_t(__builtin_amdgcn_update_dpp(0, int(v), CTRL, 0xf, 0xf, true)));
+}
+__device__ __forceinline__ uint32_t max8(float m) {
+    uint32_t v = dpp_max<0xb1>(__builtin_bit_cast(uint32_t, m));   // quad_perm [1, 0, 3, 2]
+    v = dpp_max<0x4e>(v);                                          // quad_perm [2, 3, 0, 1]
+    return dpp_max<0x141>(v);                                      // row_half_mirror
+}
+// a sc and b sc (sc a power of two) in two fp16 parts each, packed: the nearest fp16
+// values, and those of the exact remainders
+__device__ __forceinline__ void split2(float a, float b, float sc, halfx2& h, halfx2& l) {
+    h = __builtin_convertvector(floatx2{a * sc, b * sc}, halfx2);
+    l = __builtin_convertvector(floatx2{__builtin_fmaf(a, sc, -float(h.x)), __builtin_fmaf(b, sc, -float(h.y))}, halfx2);
+}
+
+// Block: WK groups of WM x WN waves; a wave owns a 32 x 32 tile of complex outputs
+// (rows: right-hand sides, columns: unknowns), the groups share the block's tile and
+// take the K chunks in turn.
+template <int WM, int WN, int WK, int KC, bool OUT64, int MINW>
+__global__ __launch_bounds__(64 * WM * WN * WK, MINW) void cgemm_split_kernel(const float2* __restrict__ X,
+                                                                              const float2* __restrict__ Z,
+                                                                              void* __restrict__ Yv, int M, int n,
+                                                                              const int* __restrict__ yrow) {
+    constexpr int GT = 64 * WM * WN;                  // threads of a group
+    constexpr int BM = 32 * WM, BN = 32 * WN;
+    constexpr int RS = KC + 8;                        // fp16 per LDS row
+    constexpr int PC = KC / 16;                       // 16-byte pieces of a lane: 8 lanes hold a row's chunk
+    constexpr int RP = GT / 8;                        // rows of a pass
+    constexpr int NA = BM / RP, NB = BN / RP;
+    static_assert(BM % RP == 0 && BN % RP == 0, "tile not divisible by the group");
+    constexpr int PLANES = 4 * (BM + BN) * RS;        // fp16 of a group's planes
+    constexpr int STAGE = 2 * PLANES + 4 * (BM + BN); // bytes: the planes and the rows' exponents
+    constexpr int RED = WK > 1 ? (WK - 1) * GT * 16 * 16 : 0;
+    constexpr int LDSB = STAGE * WK > RED ? STAGE * WK : RED;
+    __shared__ __attribute__((aligned(16))) char lds[LDSB];
+    const int tid = threadIdx.x % GT;
+    const int g = WK > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / GT) : 0;
+    const int lane = tid & 63, w = tid >> 6;
+    const int wm = w / WN, wn = w % WN;
+    const int nbm = (M + BM - 1) / BM;
+    const int nblk = int(gridDim.x);
+    const int xcd = int(blockIdx.x) & 7, idx = int(blockIdx.x) >> 3;
+    const int per = nblk >> 3, rem = nblk & 7;
+    const int logical = xcd * per + min(xcd, rem) + idx;
+    const int bm = logical % nbm, bn = logical / nbm;
+    const int s0 = bm * BM, i0 = bn * BN;
+    _Float16* Xs = reinterpret_cast<_Float16*>(lds + g * STAGE);
+    _Float16* Zs = Xs + 4 * BM * RS;
+    int* ex = reinterpret_cast<int*>(lds + g * STAGE + 2 * PLANES);
+    int* ez = ex + BM;
+
+    double dr[16], di[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) dr[r] = di[r] = 0.0;
+    floatx4u ra[NA][PC], rb[NB][PC];
+    const int lr = tid >> 3, lc = tid & 7;
+    // chunk c into registers (rows past the end: the last row again, never written
+    // out); a uniform base and 32-bit byte offsets of the thread's rows
+    uint32_t oa[NA], ob[NB];
+#pragma unroll
+    for (int q = 0; q < NA; ++q) oa[q] = (uint32_t(min(lr + RP * q, M - 1 - s0)) * uint32_t(n) + 2 * lc) * 8u;
+#pragma unroll
+    for (int q = 0; q < NB; ++q) ob[q] = (uint32_t(min(lr + RP * q, n - 1 - i0)) * uint32_t(n) + 2 * lc) * 8u;
+    const char* xb = reinterpret_cast<const char*>(X + size_t(s0) * n);
+    const char* zb = reinterpret_cast<const char*>(Z + size_t(i0) * n);
+    auto gload = [&](int c) {
+        const char *xc = xb + size_t(c) * (KC * 8), *zc = zb + size_t(c) * (KC * 8);
+        if (c * KC + KC <= n) {
+#pragma unroll
+            for (int q = 0; q < NA; ++q)
+#pragma unroll
+                for (int p = 0; p < PC; ++p) ra[q][p] = *reinterpret_cast<const floatx4u*>(xc + oa[q] + 128 * p);
+#pragma unroll
+            for (int q = 0; q < NB; ++q)
+#pragma unroll
+                for (int p = 0; p < PC; ++p) rb[q][p] = *reinterpret_cast<const floatx4u*>(zc + ob[q] + 128 * p);
+        } else {
+            const int j = c * KC + 2 * lc;
+            auto tail = [&](const char* row, int jj) {   // columns past the end: zero
+                floatx4u v{0.f, 0.f, 0.f, 0.f};
+                if (jj < n) {
+                    v.x = reinterpret_cast<const float*>(row)[0];
+                    v.y = reinterpret_cast<const float*>(row)[1];
+                }
+                if (jj + 1 < n) {
+                    v.z = reinterpret_cast<const float*>(row)[2];
+                    v.w = reinterpret_cast<const float*>(row)[3];
+                }
+                return v;
+            };
+#pragma unroll
+            for (int q = 0; q < NA; ++q)
+#pragma unroll
+                for (int p = 0; p < PC; ++p) ra[q][p] = tail(xc + oa[q] + 128 * p, j + 16 * p);
+#pragma unroll
+            for (int q = 0; q < NB; ++q)
+#pragma unroll
+                for (int p = 0; p < PC; ++p) rb[q][p] = tail(zc + ob[q] + 128 * p, j + 16 * p);
+        }
+    };
+    // a row's chunk, scaled by the power of two that takes its largest part to [2^14, 2^15), into the planes
+    auto put = [&](_Float16* planes, int* e, int rows, int row, const floatx4u (&v)[PC]) {
+        float m = 0.f;
+#pragma unroll
+        for (int p = 0; p < PC; ++p)
+            m = max3_abs(max3_abs(m, v[p].x, v[p].y), v[p].z, v[p].w);
+        const int b = max(int(max8(m) >> 23), 14);
+        const float sc = __builtin_bit_cast(float, uint32_t(268 - b) << 23);
+        if (lc == 0) e[row] = (b - 141) * (1 << 20);
+#pragma unroll
+        for (int p = 0; p < PC; ++p) {
+            halfx2 rh, rl, ih, il;
+            split2(v[p].x, v[p].z, sc, rh, rl);
+            split2(v[p].y, v[p].w, sc, ih, il);
+            _Float16* d = planes + row * RS + 2 * lc + 16 * p;
+            *reinterpret_cast<halfx2*>(d) = rh;
+            *reinterpret_cast<halfx2*>(d + rows * RS) = rl;
+            *reinterpret_cast<halfx2*>(d + 2 * rows * RS) = ih;
+            *reinterpret_cast<halfx2*>(d + 3 * rows * RS) = il;
+        }
+    };
+    auto lstore = [&]() {
+#pragma unroll
+        for (int q = 0; q < NA; ++q) put(Xs, ex, BM, lr + RP * q, ra[q]);
+#pragma unroll
+        for (int q = 0; q < NB; ++q) put(Zs, ez, BN, lr + RP * q, rb[q]);
+    };
+    const int l32 = lane & 31, kh = lane >> 5;
+    const _Float16* xp = Xs + (wm * 32 + l32) * RS + 8 * kh;
+    const _Float16* zp = Zs + (wn * 32 + l32) * RS + 8 * kh;
+    auto multiply = [&]() {
+        floatx16 rr{}, ii{}, ri{};   // sum xr zr, sum xi zi, sum xr zi + xi zr
+#pragma unroll
+        for (int ks = 0; ks < KC / 16; ++ks) {
+            halfx8 x[4], z[4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                x[s] = *reinterpret_cast<const halfx8*>(xp + s * BM * RS + 16 * ks);
+                z[s] = *reinterpret_cast<const halfx8*>(zp + s * BN * RS + 16 * ks);
+            }
+            constexpr int PI_[3] = {1, 0, 0}, PJ[3] = {0, 1, 0};   // the small products first
+#pragma unroll
+            for (int t = 0; t < 3; ++t) {
+                const int i = PI_[t], j = PJ[t];
+                rr = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[i], z[j], rr, 0, 0, 0);
+                ri = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[i], z[2 + j], ri, 0, 0, 0);
+                ii = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[2 + i], z[2 + j], ii, 0, 0, 0);
+                ri = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[2 + i], z[j], ri, 0, 0, 0);
+            }
+        }
+        // the chunk's sums, scaled back, into the FP64 accumulators: 2^e as the high
+        // word of a double from the exponents kept shifted
+        const int c = ez[wn * 32 + l32] + (1023 << 20);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int4 e4 = *reinterpret_cast<const int4*>(ex + wm * 32 + 8 * q + 4 * kh);
+            const int e[4] = {e4.x + c, e4.y + c, e4.z + c, e4.w + c};
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const double s2 = __hiloint2double(e[r], 0);
+                dr[4 * q + r] = fma(double(rr[4 * q + r] - ii[4 * q + r]), s2, dr[4 * q + r]);
+                di[4 * q + r] = fma(double(ri[4 * q + r]), s2, di[4 * q + r]);
+            }
+        }
+    };
+    const int nch = (n + KC - 1) / KC;
+    const int turns = (nch + WK - 1) / WK;
+    if (g < nch) gload(g);
+    for (int i = 0; i < turns; ++i) {
+        const int c = g + WK * i;
+        __syncthreads();
+        if (c < nch) lstore();
+        __syncthreads();
+        if (c + WK < nch) gload(c + WK);
+        if (c < nch) multiply();
+    }
+    if constexpr (WK > 1) {
+        // the groups' sums into group 0, in order
+        double2* red = reinterpret_cast<double2*>(lds);
+        __syncthreads();
+        if (g > 0) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) red[((g - 1) * 16 + r) * GT + tid] = make_double2(dr[r], di[r]);
+        }
+        __syncthreads();
+        if (g > 0) return;
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+#pragma unroll
+            for (int o = 0; o < WK - 1; ++o) {
+                const double2 v = red[(o * 16 + r) * GT + tid];
+                dr[r] += v.x;
+                di[r] += v.y;
+            }
+    }
+    // D of the 32x32x16 instruction: lane l holds column l % 32, rows 8 (r / 4) + 4 (l / 32) + r % 4
+    const int col = i0 + wn * 32 + l32;
+    if (col >= n) return;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int row = s0 + wm * 32 + 8 * (r >> 2) + 4 * kh + (r & 3);
+        if (row >= M) continue;
+        if constexpr (OUT64)
+            reinterpret_cast<double2*>(Yv)[size_t(yrow[row]) * n + col] = make_double2(dr[r], di[r]);
+        else
+            reinterpret_cast<float2*>(Yv)[size_t(row) * n + col] = make_float2(float(dr[r]), float(di[r]));
+    }
+}
+
+}  // namespace efie

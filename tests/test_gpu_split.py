@@ -1,0 +1,68 @@
+"""The fp16 split product: every tile of its rule at ragged rows, unknowns and K, badly scaled and special values.
+
+Tolerance: both operands are within 2^-23 of the stored values in each part and l l' is below 2^-22 of a product, so that
+sum |z| |x| 2^-21 bounds the error of a complex output before the FP32 sums of at most 64 terms, whose roundings (three
+products of sixteen terms each, 12 per 64 terms and part) add less than 2^-20 of it: 3e-6 of sum |z| |x|.
+"""
+import numpy as np
+import pytest
+
+from .gpu_common import flush
+
+torch = pytest.importorskip("torch")
+P = pytest.importorskip("paper_2310_15644_amd")
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def split():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    v = [t[2] for t in P.gemm_variants()].index(64)
+    prev = P.gemm_select(False, v), P.gemm_select(True, v)
+    yield v
+    P.gemm_select(False, prev[0])
+    P.gemm_select(True, prev[1])
+
+
+def operands(n, m, seed, spread):
+    rng = np.random.default_rng(seed)
+    Z = rng.standard_normal((n, n)) + 1j * rng.standard_normal((n, n))
+    X = rng.standard_normal((m, n)) + 1j * rng.standard_normal((m, n))
+    # rows (and parts of rows) of very different magnitude
+    Z *= 10.0 ** rng.uniform(-spread, spread, (n, 1)) * 10.0 ** rng.uniform(-2, 2, (n, n))
+    X *= 10.0 ** rng.uniform(-spread, spread, (m, 1)) * 10.0 ** rng.uniform(-2, 2, (m, n))
+    return (torch.as_tensor(Z, device="cuda").to(torch.complex64), torch.as_tensor(X, device="cuda").to(torch.complex64))
+
+
+# one block of 32 x 32 and its neighbours, K tails of 16, 32 and 64 terms, the four tiles of the rule
+@pytest.mark.parametrize("n,m", [(1, 2), (15, 9), (31, 33), (33, 32), (63, 31), (64, 64), (65, 65), (129, 2), (1025, 97),
+                                 (8230, 20), (4097, 40), (4130, 130)])
+def test_split_tiles(split, n, m):
+    flush(f"split product n={n} nrhs={m}")
+    Z, X = operands(n, m, 31 * n + m, 8.0)
+    Zd, Xd = Z.to(torch.complex128), X.to(torch.complex128)
+    ref = Xd @ Zd.T.contiguous()
+    bound = Xd.abs() @ Zd.abs().T.contiguous()
+    for Y in (P.zx(Z, X).to(torch.complex128), P.zx_flush64(Z, Xd)):
+        assert float(((Y - ref).abs() / bound).max()) <= 3e-6
+
+
+def test_split_special_values(split):
+    n, m = 200, 40
+    Z, X = operands(n, m, 5, 0.0)
+    X[3] = 0.0                       # a zero row
+    X[5, 64:128] = 0.0               # a zero chunk
+    X[7, 150] = float("inf")
+    X[9, 10] = float("nan")
+    Z[:, 17] *= 1e-30
+    Z[11] = 1e-38 * Z[11]            # near the smallest normal numbers
+    Y = P.zx(Z, X)
+    assert bool((Y[3] == 0).all())
+    for r in (7, 9):
+        assert not bool(torch.isfinite(Y[r].abs()).any())
+    keep = [r for r in range(m) if r not in (7, 9)]
+    Xd, Zd = X[keep].to(torch.complex128), Z.to(torch.complex128)
+    bound = Xd.abs() @ Zd.abs().T.contiguous() + 1e-36
+    assert float(((Y[keep].to(torch.complex128) - Xd @ Zd.T.contiguous()).abs() / bound).max()) <= 3e-6
