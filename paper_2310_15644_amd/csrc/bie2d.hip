@@ -24,15 +24,7 @@
 //    h_i = (lambda_i, H_t) with H_t = -(khat . n) E_z / eta; the right-hand side of
 //    the stabilized system b_p = N_k~ G^-1 e/(j k eta) + (G/2 - D*_k~) G^-1 h.
 //
-// Hankel functions of complex argument (Im z <= 0), FP64, own implementation:
-// for |z| >= 17 the Hankel asymptotic expansion H_nu^(2)(z) ~ (2/(pi z))^(1/2)
-// exp(-j(z - nu pi/2 - pi/4)) sum_k (-j)^k a_k(nu) / z^k, a_k(nu) =
-// prod_{m<=k} (4 nu^2 - (2m-1)^2) / (k! 8^k), summed up to its smallest term or
-// until the terms fall below 1e-17 of the sum (error below 4e-15 for |z| >= 17); below, J_n(z) by Miller's backward recurrence from
-// n = 2 floor(|z|/2) + 30, normalized by J_0 + 2 sum J_2k = 1, and
-// Y_0 = (2/pi)(ln(z/2) + gamma) J_0 - (4/pi) sum_k (-1)^k J_2k / k,
-// Y_1 = -Y_0' = (2/pi)[(ln(z/2) + gamma) J_1 - J_0 / z] + (2/pi) sum_k (-1)^k (J_2k-1 - J_2k+1) / k
-// (Neumann series; Abramowitz and Stegun 9.1.88, 9.1.27).
+// The Green's function and its derivative: hankel2d.h.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -41,6 +33,7 @@
 #include <vector>
 
 #include "bie2d.h"
+#include "hankel2d.h"
 #include "linalg.h"
 
 namespace efie {
@@ -68,142 +61,7 @@ __device__ __forceinline__ double2 crcp(double2 a) {
     return make_double2(r / d, -1.0 / d);
 }
 __device__ __forceinline__ double2 cdiv(double2 a, double2 b) { return cmul(a, crcp(b)); }
-__device__ __forceinline__ double2 cexp_(double2 a) {
-    double s, c;
-    sincos(a.y, &s, &c);
-    const double e = exp(a.x);
-    return make_double2(e * c, e * s);
-}
-__device__ __forceinline__ double2 clog_(double2 a) { return make_double2(log(hypot(a.x, a.y)), atan2(a.y, a.x)); }
-__device__ __forceinline__ double2 csqrt_(double2 a) {
-    const double r = hypot(a.x, a.y);
-    if (r == 0.0) return make_double2(0.0, 0.0);
-    if (a.x >= 0.0) {
-        const double t = sqrt(0.5 * (r + a.x));
-        return make_double2(t, 0.5 * a.y / t);
-    }
-    const double t = sqrt(0.5 * (r - a.x));
-    return make_double2(0.5 * fabs(a.y) / t, a.y >= 0.0 ? t : -t);
-}
 __device__ __forceinline__ double cabs_(double2 a) { return hypot(a.x, a.y); }
-
-struct H01 {
-    double2 h0, h1;
-};
-
-// Miller's backward recurrence: the normalized J_0, J_1 and the Neumann sums
-// (Y-parts without the logarithmic terms), z not 0.
-struct Jsums {
-    double2 j0, j1, ysum0, ysum1;   // ysum0 = -(4/pi) sum (-1)^k J_2k/k, ysum1 = (2/pi) sum (-1)^k (J_2k-1 - J_2k+1)/k
-};
-
-__device__ Jsums bessel_small(double2 z) {
-    const double az = cabs_(z);
-    const int M = 2 * (int(0.5 * az) + 15);
-    const double2 iz = crcp(z);
-    double2 jn1 = make_double2(0.0, 0.0);           // J_{m+1}
-    double2 jn = make_double2(1e-30, 0.0);          // J_m, unnormalized
-    double2 norm = make_double2(0.0, 0.0), s0 = norm, s1 = norm, j1 = norm, j0 = norm;
-    for (int m = M; m >= 0; --m) {
-        // contributions of J_m
-        if (m == 0) {
-            norm = cadd(norm, jn);
-            j0 = jn;
-        } else if ((m & 1) == 0) {
-            const int k = m >> 1;
-            norm = cadd(norm, cscale(jn, 2.0));
-            s0 = cadd(s0, cscale(jn, ((k & 1) ? -1.0 : 1.0) / k));
-        } else {
-            // odd m: + (-1)^((m+1)/2) / ((m+1)/2) from J_{2k-1}, - (-1)^((m-1)/2) / ((m-1)/2) from J_{2k+1}
-            const int ka = (m + 1) >> 1;
-            double c = ((ka & 1) ? -1.0 : 1.0) / ka;
-            if (m >= 3) {
-                const int kb = (m - 1) >> 1;
-                c -= ((kb & 1) ? -1.0 : 1.0) / kb;
-            }
-            s1 = cadd(s1, cscale(jn, c));
-            if (m == 1) j1 = jn;
-        }
-        if (m == 0) break;
-        // J_{m-1} = (2m / z) J_m - J_{m+1}
-        const double2 jm = csub(cscale(cmul(iz, jn), 2.0 * m), jn1);
-        jn1 = jn;
-        jn = jm;
-        // keep the unnormalized sequence in range (every accumulated quantity is linear in it)
-        const double mag = fabs(jn.x) + fabs(jn.y);
-        if (mag > 1e200) {
-            const double f = 1e-200;
-            jn = cscale(jn, f);
-            jn1 = cscale(jn1, f);
-            norm = cscale(norm, f);
-            s0 = cscale(s0, f);
-            s1 = cscale(s1, f);
-            j1 = cscale(j1, f);
-        }
-    }
-    const double2 inv = crcp(norm);
-    Jsums r;
-    r.j0 = cmul(j0, inv);
-    r.j1 = cmul(j1, inv);
-    r.ysum0 = cscale(cmul(s0, inv), -4.0 / PI2D);
-    r.ysum1 = cscale(cmul(s1, inv), 2.0 / PI2D);
-    return r;
-}
-
-// H0^(2)(z) and H1^(2)(z), Re z > 0, Im z <= 0
-__device__ H01 hankel2_01(double2 z) {
-    const double az = cabs_(z);
-    H01 h;
-    if (az >= 17.0) {
-        const double2 m = cmul(make_double2(0.0, -1.0), crcp(z));   // -j / z
-        double2 s0 = make_double2(1.0, 0.0), s1 = s0, t0 = s0, t1 = s0;
-        double prev = 2.0;
-        for (int k = 1; k <= 60; ++k) {
-            // an asymptotic series: summed up to its smallest term (or to 1e-17 of the sum)
-            const double f = double(2 * k - 1) * double(2 * k - 1);
-            const double2 n0 = cscale(cmul(t0, m), (0.0 - f) / (8.0 * k));
-            const double2 n1 = cscale(cmul(t1, m), (4.0 - f) / (8.0 * k));
-            const double mag = cabs_(n0) + cabs_(n1);
-            if (mag > prev) break;
-            t0 = n0;
-            t1 = n1;
-            prev = mag;
-            s0 = cadd(s0, t0);
-            s1 = cadd(s1, t1);
-            if (mag < 1e-17 * cabs_(s0)) break;
-        }
-        // (2/(pi z))^(1/2) exp(-j (z - pi/4)); the order-1 phase adds exp(j pi/2) = j
-        const double2 pre = cmul(csqrt_(cscale(crcp(z), 2.0 / PI2D)),
-                                 cexp_(make_double2(z.y, -(z.x - 0.25 * PI2D))));
-        h.h0 = cmul(pre, s0);
-        h.h1 = cmul(cmul(pre, make_double2(0.0, 1.0)), s1);
-        return h;
-    }
-    const Jsums b = bessel_small(z);
-    const double2 lg = cadd(clog_(cscale(z, 0.5)), make_double2(EULER, 0.0));
-    const double2 y0 = cadd(cscale(cmul(lg, b.j0), 2.0 / PI2D), b.ysum0);
-    const double2 y1 = cadd(cscale(csub(cmul(lg, b.j1), cmul(b.j0, crcp(z))), 2.0 / PI2D), b.ysum1);
-    h.h0 = make_double2(b.j0.x + y0.y, b.j0.y - y0.x);          // J0 - j Y0
-    h.h1 = make_double2(b.j1.x + y1.y, b.j1.y - y1.x);
-    return h;
-}
-
-// G_reg(R) = G(R) + ln(R) / (2 pi) for the self pair (|kappa R| small), from the
-// series without cancellation: G = -(j/4) J0 - (1/(2 pi))(ln(kappa R/2) + gamma) J0 - ysum0/4
-__device__ double2 green_reg(double2 kap, double R) {
-    const double2 lk = cadd(clog_(cscale(kap, 0.5)), make_double2(EULER, 0.0));   // ln(kappa/2) + gamma
-    if (R == 0.0) {
-        return make_double2(-lk.x / (2.0 * PI2D), -0.25 - lk.y / (2.0 * PI2D));
-    }
-    const Jsums b = bessel_small(cscale(kap, R));
-    const double lr = log(R);
-    // -(j/4) J0 - (1/2pi) [lk J0 + ln R (J0 - 1)] - ysum0 / 4
-    double2 g = make_double2(0.25 * b.j0.y, -0.25 * b.j0.x);
-    const double2 t = cadd(cmul(lk, b.j0), cscale(make_double2(b.j0.x - 1.0, b.j0.y), lr));
-    g = csub(g, cscale(t, 1.0 / (2.0 * PI2D)));
-    g = csub(g, cscale(b.ysum0, 0.25));
-    return g;
-}
 
 // moments of one segment pair: mS[alpha][beta] = int int G phi_alpha phi_beta dx dy,
 // mD likewise with dG/dn_test, m0 = int int G (no segment lengths)
@@ -211,17 +69,16 @@ struct PairMom {
     double2 s[2][2], d[2][2], m0;
 };
 
-__device__ __forceinline__ void accum(PairMom& pm, double2 kap, double rx, double ry, double px, double py,
+template <bool CK>
+__device__ __forceinline__ void accum(PairMom& pm, const Kern2d& K, double rx, double ry, double px, double py,
                                       double nx, double ny, double xa, double yb, double w) {
     const double dx = rx - px, dy = ry - py;
-    const double R = sqrt(dx * dx + dy * dy);
-    const H01 h = hankel2_01(cscale(kap, R));
-    // G = -(j/4) H0, dG/dR = (j kappa / 4) H1
-    const double2 G = make_double2(0.25 * h.h0.y, -0.25 * h.h0.x);
-    const double2 jk = make_double2(-0.25 * kap.y, 0.25 * kap.x);
-    const double2 dG = cscale(cmul(jk, h.h1), (dx * nx + dy * ny) / R);
+    const double R2[1] = {dx * dx + dy * dy};
+    double2 g[1], d[1];
+    double ri[1];
+    green2d<1, CK>(K, R2, g, d, ri);
     const double pa[2] = {1.0 - xa, xa}, pb[2] = {1.0 - yb, yb};
-    const double2 Gw = cscale(G, w), dGw = cscale(dG, w);
+    const double2 Gw = cscale(g[0], w), dGw = cscale(d[0], w * (dx * nx + dy * ny) * ri[0]);
 #pragma unroll
     for (int al = 0; al < 2; ++al)
 #pragma unroll
@@ -233,8 +90,14 @@ __device__ __forceinline__ void accum(PairMom& pm, double2 kap, double rx, doubl
     pm.m0 = cadd(pm.m0, Gw);
 }
 
-template <int Q>
-__device__ PairMom pair_moments(const DevContour& c, double2 kap, int a, int b) {
+// Of a segment with itself or a neighbour (a, b uniform over the wave, every lane
+// active): 64 lanes take the 8 x 8 points (both triangles of the Duffy rule on a
+// neighbour) and add up their moments by a butterfly.  One thread per pair, as for the
+// regular pairs, was the tail of every launch: 192 evaluations in a row, 1 ms.
+// (A call of its own: inlined, its registers would halve the waves of the regular pairs.)
+template <bool CK>
+__device__ __attribute__((noinline)) void near_moments(const DevContour c, const Kern2d& K, int a, int b, int lane,
+                                                       PairMom& out) {
     PairMom pm;
 #pragma unroll
     for (int al = 0; al < 2; ++al)
@@ -242,88 +105,144 @@ __device__ PairMom pair_moments(const DevContour& c, double2 kap, int a, int b) 
         for (int be = 0; be < 2; ++be) pm.s[al][be] = pm.d[al][be] = make_double2(0.0, 0.0);
     pm.m0 = make_double2(0.0, 0.0);
     const int n = c.n;
-    const double nxa = c.nx[a], nya = c.ny[a];
+    const int p = lane >> 3, q = lane & 7;
     if (a == b) {
-        const double L = c.len[a];
-#pragma unroll 1
-        for (int p = 0; p < NQN; ++p)
-#pragma unroll 1
-            for (int q = 0; q < NQN; ++q) {
-                const double xp = c.hx[p], xq = c.hx[q], w = c.hw[p] * c.hw[q];
-                const double2 g = cscale(green_reg(kap, L * fabs(xp - xq)), w);
-                const double pa[2] = {1.0 - xp, xp}, pb[2] = {1.0 - xq, xq};
-                for (int al = 0; al < 2; ++al)
-                    for (int be = 0; be < 2; ++be) pm.s[al][be] = cadd(pm.s[al][be], cscale(g, pa[al] * pb[be]));
-                pm.m0 = cadd(pm.m0, g);
-            }
-        // -(1/2 pi) [ln L int int phi phi + int int phi phi ln|x - y|]
-        const double lnL = log(L), f = -1.0 / (2.0 * PI2D);
-        const double lm[2][2] = {{-7.0 / 16.0, -5.0 / 16.0}, {-5.0 / 16.0, -7.0 / 16.0}};
+        const double xp = c.hx[p], xq = c.hx[q], w = c.hw[p] * c.hw[q];
+        const double2 g = cscale(green2d_reg<CK>(K, c.len[a] * fabs(xp - xq)), w);
+        const double pa[2] = {1.0 - xp, xp}, pb[2] = {1.0 - xq, xq};
+#pragma unroll
         for (int al = 0; al < 2; ++al)
-            for (int be = 0; be < 2; ++be) pm.s[al][be].x += f * (0.25 * lnL + lm[al][be]);
-        pm.m0.x += f * (lnL - 1.5);
-        return pm;
-    }
-    const bool next = b == (a + 1) % n, prev = b == (a + n - 1) % n;
-    if (next || prev) {
+#pragma unroll
+            for (int be = 0; be < 2; ++be) pm.s[al][be] = cscale(g, pa[al] * pb[be]);
+        pm.m0 = g;
+    } else {
         // V shared node; Pa, Pb the other ends of a and b
+        const bool next = b == (a + 1) % n;
         double vx, vy, pax, pay, pbx, pby;
         if (next) {
             vx = c.bx[a]; vy = c.by[a]; pax = c.ax[a]; pay = c.ay[a]; pbx = c.bx[b]; pby = c.by[b];
         } else {
             vx = c.ax[a]; vy = c.ay[a]; pax = c.bx[a]; pay = c.by[a]; pbx = c.ax[b]; pby = c.ay[b];
         }
+        const double sg = c.hx[p], t = c.hx[q];
+        const double w = c.hw[p] * c.hw[q] * 2.0 * sg * sg * sg;
+        const double s = sg * sg;
 #pragma unroll 1
-        for (int p = 0; p < NQN; ++p)
-#pragma unroll 1
-            for (int q = 0; q < NQN; ++q) {
-                const double sg = c.hx[p], t = c.hx[q];
-                const double w = c.hw[p] * c.hw[q] * 2.0 * sg * sg * sg;
-                const double s = sg * sg;
-#pragma unroll 1
-                for (int tri = 0; tri < 2; ++tri) {
-                    const double u = tri == 0 ? s : s * t, v = tri == 0 ? s * t : s;
-                    const double rx = vx + u * (pax - vx), ry = vy + u * (pay - vy);
-                    const double px = vx + v * (pbx - vx), py = vy + v * (pby - vy);
-                    const double xa = next ? 1.0 - u : u, yb = next ? v : 1.0 - v;
-                    accum(pm, kap, rx, ry, px, py, nxa, nya, xa, yb, w);
-                }
-            }
-        return pm;
-    }
-    const double ax = c.ax[a], ay = c.ay[a], bx = c.bx[a] - ax, by = c.by[a] - ay;
-    const double qx = c.ax[b], qy = c.ay[b], sx = c.bx[b] - qx, sy = c.by[b] - qy;
-#pragma unroll
-    for (int p = 0; p < Q; ++p) {
-        const double xp = c.gx[p];
-        const double rx = ax + xp * bx, ry = ay + xp * by;
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            const double yq = c.gx[q];
-            accum(pm, kap, rx, ry, qx + yq * sx, qy + yq * sy, nxa, nya, xp, yq, c.gw[p] * c.gw[q]);
+        for (int tri = 0; tri < 2; ++tri) {
+            const double u = tri == 0 ? s : s * t, v = tri == 0 ? s * t : s;
+            const double rx = vx + u * (pax - vx), ry = vy + u * (pay - vy);
+            const double px = vx + v * (pbx - vx), py = vy + v * (pby - vy);
+            const double xa = next ? 1.0 - u : u, yb = next ? v : 1.0 - v;
+            accum<CK>(pm, K, rx, ry, px, py, c.nx[a], c.ny[a], xa, yb, w);
         }
     }
-    return pm;
+    double* v = reinterpret_cast<double*>(&pm);
+#pragma unroll
+    for (int x = 0; x < int(sizeof(PairMom) / sizeof(double)); ++x)
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) v[x] += __shfl_xor(v[x], o, 64);
+    if (a == b) {
+        // -(1/2 pi) [ln L int int phi phi + int int phi phi ln|x - y|]
+        const double lnL = log(c.len[a]), f = -1.0 / (2.0 * PI2D);
+#pragma unroll
+        for (int al = 0; al < 2; ++al)
+#pragma unroll
+            for (int be = 0; be < 2; ++be) pm.s[al][be].x += f * (0.25 * lnL + (al == be ? -7.0 / 16.0 : -5.0 / 16.0));
+        pm.m0.x += f * (lnL - 1.5);
+    }
+    if (lane == 0) out = pm;
+}
+
+// of two segments that share no node
+template <int Q, bool CK>
+__device__ __forceinline__ void regular_moments(const DevContour& c, const Kern2d& K, int a, int b, PairMom& out) {
+    PairMom pm;
+#pragma unroll
+    for (int al = 0; al < 2; ++al)
+#pragma unroll
+        for (int be = 0; be < 2; ++be) pm.s[al][be] = pm.d[al][be] = make_double2(0.0, 0.0);
+    pm.m0 = make_double2(0.0, 0.0);
+    const double nxa = c.nx[a], nya = c.ny[a];
+    const double ax = c.ax[a], ay = c.ay[a], bx = c.bx[a] - ax, by = c.by[a] - ay;
+    const double qx = c.ax[b], qy = c.ay[b], sx = c.bx[b] - qx, sy = c.by[b] - qy;
+    // two source points at a time (four take the registers of a third wave)
+#pragma unroll 1
+    for (int p = 0; p < Q; ++p) {
+        const double xp = c.gx[p], wp = c.gw[p];
+        const double rx = ax + xp * bx - qx, ry = ay + xp * by - qy;
+        // sums over the source points, weighted 1 and y; then over the test points
+        double2 g0 = make_double2(0.0, 0.0), g1 = g0, h0 = g0, h1 = g0;
+#pragma unroll 1
+        for (int q0 = 0; q0 < Q; q0 += 2) {
+            double R2[2], ri[2], f[2];
+            double2 g[2], d[2];
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                const double yq = c.gx[min(q0 + x, Q - 1)];
+                const double dx = rx - yq * sx, dy = ry - yq * sy;
+                R2[x] = dx * dx + dy * dy;
+                f[x] = dx * nxa + dy * nya;
+            }
+            green2d<2, CK>(K, R2, g, d, ri);
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                if (q0 + x >= Q) break;   // odd Q
+                const double wq = c.gw[q0 + x], wy = wq * c.gx[q0 + x];
+                const double2 h = cscale(d[x], f[x] * ri[x]);
+                g0 = cadd(g0, cscale(g[x], wq));
+                g1 = cadd(g1, cscale(g[x], wy));
+                h0 = cadd(h0, cscale(h, wq));
+                h1 = cadd(h1, cscale(h, wy));
+            }
+        }
+        const double w1 = wp * xp, w0 = wp - w1;
+        pm.m0 = cadd(pm.m0, cscale(g0, wp));
+        g0 = csub(g0, g1);
+        h0 = csub(h0, h1);
+        pm.s[0][0] = cadd(pm.s[0][0], cscale(g0, w0));
+        pm.s[0][1] = cadd(pm.s[0][1], cscale(g1, w0));
+        pm.s[1][0] = cadd(pm.s[1][0], cscale(g0, w1));
+        pm.s[1][1] = cadd(pm.s[1][1], cscale(g1, w1));
+        pm.d[0][0] = cadd(pm.d[0][0], cscale(h0, w0));
+        pm.d[0][1] = cadd(pm.d[0][1], cscale(h1, w0));
+        pm.d[1][0] = cadd(pm.d[1][0], cscale(h0, w1));
+        pm.d[1][1] = cadd(pm.d[1][1], cscale(h1, w1));
+    }
+    out = pm;
 }
 
 // One block: entries (i, j), i in [i0, i0 + TILE), j in [j0, j0 + TILE) of the
 // requested window; its 16 x 16 segment pairs (a in i0-1 .. i0+14, b in j0-1 ..
 // j0+14, mod n) are evaluated once, one per thread, into LDS and each entry adds
 // its four.  Out: S, Dm, Nm (any may be null) at [(i - row0) * ld + (j - col0)].
-template <int Q>
-__global__ __launch_bounds__(256) void assemble2d_kernel(DevContour c, double kr, double ki, int row0, int nrows,
+// Bound by the vector ALU (about 165 FP64 operations per Green's function and its
+// derivative, 16 of each per pair), at two waves per SIMD: with three the spilled
+// registers cost more than the third wave gives (16.3 against 6.0 ms).  Three operators at
+// n = 6007, 18 nodes per wavelength: 54.9 ms with asymptotic series, backward
+// recurrences and one thread per neighbouring pair; 4.1 ms now.  n = 150: 3.1 ms -> 0.12 ms.
+template <int Q, bool CK>
+__global__ __launch_bounds__(256, 2) void assemble2d_kernel(DevContour c, Kern2d Karg, double kr, double ki, int row0, int nrows,
                                                          int col0, int ncols, int ld, double2* __restrict__ S,
                                                          double2* __restrict__ Dm, double2* __restrict__ Nm) {
     __shared__ PairMom pm[16 * 16];
+    __shared__ Kern2d K;
+    static_assert(sizeof(Kern2d) <= 256 * sizeof(double), "one double for each thread");
+    if (threadIdx.x < sizeof(Kern2d) / sizeof(double))
+        reinterpret_cast<double*>(&K)[threadIdx.x] = reinterpret_cast<const double*>(&Karg)[threadIdx.x];
+    __syncthreads();
     const int n = c.n;
     const int tcols = (ncols + TILE - 1) / TILE;
     const int ti = int(blockIdx.x) / tcols, tj = int(blockIdx.x) - ti * tcols;
     const int i0 = row0 + ti * TILE, j0 = col0 + tj * TILE;
-    const double2 kap = make_double2(kr, ki);
     {
         const int t = threadIdx.x;
         const int a = (i0 - 1 + t / 16 + n) % n, b = (j0 - 1 + t % 16 + n) % n;
-        pm[t] = pair_moments<Q>(c, kap, a, b);
+        const bool near = a == b || b == (a + 1) % n || a == (b + 1) % n;
+        if (!near) regular_moments<Q, CK>(c, K, a, b, pm[t]);
+        for (uint64_t m = __ballot(near); m; m &= m - 1) {
+            const int src = __builtin_ctzll(m);
+            near_moments<CK>(c, K, __shfl(a, src), __shfl(b, src), t & 63, pm[(t & ~63) + src]);
+        }
     }
     __syncthreads();
     const int t = threadIdx.x;
@@ -916,10 +835,15 @@ void launch_assemble(const DevContour& c, double kr, double ki, int row0, int nr
     const size_t nblk = size_t(tr) * size_t(tc);
     EFIE_REQUIRE(nblk < (size_t(1) << 31), EFIE_ERR_ARG, "bie2d_assemble: window too large");
     efie::prof_begin(efie::PROF_FAR, s);
+    const efie::Kern2d K = efie::make_kern2d(kr, ki);
 #define B2D_Q(QQ)                                                                                                 \
     case QQ:                                                                                                      \
-        hipLaunchKernelGGL((efie::assemble2d_kernel<QQ>), dim3(unsigned(nblk)), dim3(256), 0, s, c, kr, ki, row0, \
-                           nrows, col0, ncols, ld, S, D, N);                                                      \
+        if (ki != 0.0)                                                                                            \
+            hipLaunchKernelGGL((efie::assemble2d_kernel<QQ, true>), dim3(unsigned(nblk)), dim3(256), 0, s, c, K,  \
+                               kr, ki, row0, nrows, col0, ncols, ld, S, D, N);                                    \
+        else                                                                                                      \
+            hipLaunchKernelGGL((efie::assemble2d_kernel<QQ, false>), dim3(unsigned(nblk)), dim3(256), 0, s, c, K, \
+                               kr, ki, row0, nrows, col0, ncols, ld, S, D, N);                                    \
         break
     switch (q) {
         B2D_Q(2); B2D_Q(3); B2D_Q(4); B2D_Q(5); B2D_Q(6); B2D_Q(8);
