@@ -12,6 +12,7 @@
 
 #include "efie_internal.h"
 #include "linalg.h"
+#include "phase_math.h"
 
 namespace efie {
 
@@ -24,6 +25,7 @@ __global__ __launch_bounds__(256) void excite_kernel(DevMesh m, double k, const 
     const int s = idx / N, n = idx - s * N;
     const double kx = khat[3 * s], ky = khat[3 * s + 1], kz = khat[3 * s + 2];
     const double px = pol[3 * s], py = pol[3 * s + 1], pz = pol[3 * s + 2];
+    const Phase<double> pk = make_phase<double>(-k, 0.0);
     double vr = 0, vi = 0;
     for (int h = 0; h < 2; ++h) {
         const int t = m.et[h * N + n], l = m.el[h * N + n];
@@ -34,7 +36,7 @@ __global__ __launch_bounds__(256) void excite_kernel(DevMesh m, double k, const 
             const double dx = m.qx[a * T + t], dy = m.qy[a * T + t], dz = m.qz[a * T + t];
             const double fp = c * ((dx - ux) * px + (dy - uy) * py + (dz - uz) * pz);
             double sn, cs;
-            sincos(-k * (ph0 + kx * dx + ky * dy + kz * dz), &sn, &cs);
+            sincos_quarter(ph0 + kx * dx + ky * dy + kz * dz, pk.khi, pk.klo, sn, cs);
             const double w = m.qw[a * T + t] * fp;
             vr += w * cs;
             vi += w * sn;
@@ -59,6 +61,7 @@ __global__ __launch_bounds__(256) void radiation_kernel(DevMesh m, double k, dou
     sincos(phv, &sp, &cp);
     const double tx = ct * cp, ty = ct * sp, tz = -st;
     const double qx_ = -sp, qy_ = cp, qz_ = 0.0;
+    const Phase<double> pk = make_phase<double>(k, 0.0);
     double ar[3] = {0, 0, 0}, ai[3] = {0, 0, 0};
     for (int h = 0; h < 2; ++h) {
         const int t = m.et[h * N + n], l = m.el[h * N + n];
@@ -68,7 +71,7 @@ __global__ __launch_bounds__(256) void radiation_kernel(DevMesh m, double k, dou
         for (int a = 0; a < NQ; ++a) {
             const double dx = m.qx[a * T + t], dy = m.qy[a * T + t], dz = m.qz[a * T + t];
             double sn, cs;
-            sincos(k * (ph0 + rx * dx + ry * dy + rz * dz), &sn, &cs);
+            sincos_quarter(ph0 + rx * dx + ry * dy + rz * dz, pk.khi, pk.klo, sn, cs);
             const double w = m.qw[a * T + t] * c;
             const double f[3] = {dx - ux, dy - uy, dz - uz};
 #pragma unroll

@@ -399,7 +399,7 @@ void gemv(const void* Z, int zdt, int n, const void* x, int xdt, void* y, int yd
 
 // ------------------------------------------------- FP64 matrix-core product
 // C[crow[s]][i] = sum_k A[arow[s]][k] B[i][k] (complex128 A and C, complex128 or
-// complex64 B; B square n x n with K = n here) on v_mfma_f64_16x16x4f64, in the
+// complex64 B) on v_mfma_f64_16x16x4f64, in the
 // planar complex form of the complex64 kernel: the K chunks of A and B sit in LDS
 // as complex rows, a lane's operand element is one complex value (one 16-byte LDS
 // read), and each 16 x 16 complex output block takes four real instructions per 4
@@ -411,26 +411,37 @@ void gemv(const void* Z, int zdt, int n, const void* x, int xdt, void* y, int yd
 // 4/WGM along the columns), a BM x BNC complex tile, K chunks of KC complex
 // elements double-buffered in LDS with register prefetch, XCD-aware block order.
 // LDS rows hold KC + 1 complex values, which keeps the 16-byte reads of a
-// wavefront free of bank conflicts.  Few right-hand sides (the residual products
-// of a handful of columns) use a 16-row tile with all four wavefronts along the
-// columns, so Z is read once.
+// wavefront free of bank conflicts.  Few right-hand sides of a large matrix use a
+// 16-row tile with all four wavefronts along the columns, so Z is read once.
+// Rectangular: C[s][i], i < Nc, sums K terms of A (lda) and B (ldb).
+// Few tiles are split over K inside the block: WK groups of four wavefronts share the
+// tile, take the K chunks in turn and add their sums in order at the end.  One group
+// per CU leaves a wavefront per SIMD, whose loads show through: 7679 x 7679 times 64
+// took 736 us that way and takes 570 to 645 us with four (47 to 53 TFLOP/s of 78.6); the
+// far field of 512 currents in 512 directions at N = 7680 (512 x 1024 x 7680), before on
+// the vector kernel below, 2.9 ms -> 0.7 ms.
 typedef double doublex4 __attribute__((ext_vector_type(4)));
 
-template <int BM, int BNC, int KC, int WGM, typename BT>
-__global__ __launch_bounds__(256) void zgemm_mfma_kernel(const double2* __restrict__ A, const BT* __restrict__ B,
-                                                         double2* __restrict__ C, int M, int n, int lda, int ldc,
-                                                         const int* __restrict__ arow, const int* __restrict__ crow) {
+template <int BM, int BNC, int KC, int WGM, int WK, typename BT>
+__global__ __launch_bounds__(256 * WK) void zgemm_mfma_kernel(const double2* __restrict__ A, const BT* __restrict__ B,
+                                                              double2* __restrict__ C, int M, int Nc, int K, int lda,
+                                                              int ldb, int ldc, const int* __restrict__ arow,
+                                                              const int* __restrict__ crow) {
     constexpr int AS = KC + 1;         // double2 per LDS row
     constexpr int WGN = 4 / WGM;
     constexpr int WM = BM / WGM, WN = BNC / WGN;
     constexpr int TM = WM / 16, TN = WN / 16;
     constexpr int NA = BM * KC / 256, NB = BNC * KC / 256;
     static_assert(WGM * WGN == 4 && TM >= 1 && TN >= 1, "bad wavefront arrangement");
-    static_assert(BM * KC % 256 == 0 && BNC * KC % 256 == 0, "tile not divisible by the block");
-    __shared__ double2 As[2][BM * AS];
-    __shared__ double2 Bs[2][BNC * AS];
+    static_assert(BM * KC % 256 == 0 && BNC * KC % 256 == 0, "tile not divisible by a group");
+    constexpr int STAGE = 2 * (BM + BNC) * AS;                 // double2 of a group's two buffers
+    constexpr int RED = (WK - 1) * 256 * TM * TN * 4;
+    __shared__ double2 lds[STAGE * WK > RED ? STAGE * WK : RED];
 
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x & 255;
+    const int g = WK > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0;
+    double2* As = lds + g * STAGE;
+    double2* Bs = As + 2 * BM * AS;
     const int lane = tid & 63, w = tid >> 6;
     const int wm = w / WGN, wn = w % WGN;
     const int nbm = (M + BM - 1) / BM;
@@ -452,67 +463,104 @@ __global__ __launch_bounds__(256) void zgemm_mfma_kernel(const double2* __restri
 
     double2 ra[NA];
     BT rb[NB];   // raw storage type: converted when written to LDS, so the loads stay in flight
+    // one group: elements tested one by one; K groups: rows clamped (the last row again,
+    // never written out) and columns tested in the last chunk alone -- each the faster
+    // there (7679 times 64: 662 -> 645 us with four groups, 728 -> 779 us with one)
+    size_t oa[NA], ob[NB];
+#pragma unroll
+    for (int q = 0; q < NA; ++q) {
+        const int r = min(s0 + (tid + 256 * q) / KC, M - 1);
+        oa[q] = size_t(arow ? arow[r] : r) * lda + (tid + 256 * q) % KC;
+    }
+#pragma unroll
+    for (int q = 0; q < NB; ++q) ob[q] = size_t(min(i0 + (tid + 256 * q) / KC, Nc - 1)) * ldb + (tid + 256 * q) % KC;
     auto gload = [&](int j0) {
+        if (WK > 1 && j0 + KC <= K) {
+#pragma unroll
+            for (int q = 0; q < NA; ++q) ra[q] = A[oa[q] + j0];
+#pragma unroll
+            for (int q = 0; q < NB; ++q) rb[q] = B[ob[q] + j0];
+            return;
+        }
 #pragma unroll
         for (int q = 0; q < NA; ++q) {
             const int e = tid + 256 * q, r = e / KC, c = e % KC;
             const int srow = s0 + r, j = j0 + c;
-            ra[q] = (srow < M && j < n) ? A[size_t(arow ? arow[srow] : srow) * lda + j] : make_double2(0.0, 0.0);
+            ra[q] = (srow < M && j < K) ? A[size_t(arow ? arow[srow] : srow) * lda + j] : make_double2(0.0, 0.0);
         }
 #pragma unroll
         for (int q = 0; q < NB; ++q) {
             const int e = tid + 256 * q, r = e / KC, c = e % KC;
             const int i = i0 + r, j = j0 + c;
-            rb[q] = (i < n && j < n) ? B[size_t(i) * n + j] : BT{0, 0};
+            rb[q] = (i < Nc && j < K) ? B[size_t(i) * ldb + j] : BT{0, 0};
         }
     };
     auto lstore = [&](int buf) {
 #pragma unroll
         for (int q = 0; q < NA; ++q) {
             const int e = tid + 256 * q, r = e / KC, c = e % KC;
-            As[buf][r * AS + c] = ra[q];
+            As[(buf * BM + r) * AS + c] = ra[q];
         }
 #pragma unroll
         for (int q = 0; q < NB; ++q) {
             const int e = tid + 256 * q, r = e / KC, c = e % KC;
-            Bs[buf][r * AS + c] = to_d2(rb[q]);
+            Bs[(buf * BNC + r) * AS + c] = to_d2(rb[q]);
         }
     };
 
     const int kq = lane >> 4, l16 = lane & 15;
-    const int nch = (n + KC - 1) / KC;
-    gload(0);
-    lstore(0);
+    const int nch = (K + KC - 1) / KC;
+    const int turns = (nch + WK - 1) / WK;
+    if (g < nch) {
+        gload(g * KC);
+        lstore(0);
+    }
     __syncthreads();
-    for (int ch = 0; ch < nch; ++ch) {
-        const int buf = ch & 1;
-        if (ch + 1 < nch) gload((ch + 1) * KC);
-        const double2* A_ = As[buf] + (wm * WM + l16) * AS + kq;
-        const double2* B_ = Bs[buf] + (wn * WN + l16) * AS + kq;
+    for (int i = 0; i < turns; ++i) {
+        const int ch = g + WK * i, buf = i & 1;
+        if (ch + WK < nch) gload((ch + WK) * KC);
+        if (ch < nch) {
+            const double2* A_ = As + (buf * BM + wm * WM + l16) * AS + kq;
+            const double2* B_ = Bs + (buf * BNC + wn * WN + l16) * AS + kq;
 #pragma unroll
-        for (int kk = 0; kk < KC; kk += 4) {
-            double2 xa[TM], zb[TN];
+            for (int kk = 0; kk < KC; kk += 4) {
+                double2 xa[TM], zb[TN];
 #pragma unroll
-            for (int a = 0; a < TM; ++a) xa[a] = A_[a * 16 * AS + kk];
+                for (int a = 0; a < TM; ++a) xa[a] = A_[a * 16 * AS + kk];
 #pragma unroll
-            for (int b = 0; b < TN; ++b) zb[b] = B_[b * 16 * AS + kk];
+                for (int b = 0; b < TN; ++b) zb[b] = B_[b * 16 * AS + kk];
 #pragma unroll
-            for (int a = 0; a < TM; ++a)
+                for (int a = 0; a < TM; ++a)
 #pragma unroll
-                for (int b = 0; b < TN; ++b) {
-                    accr[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[a].x, zb[b].x, accr[a][b], 0, 0, 0);
-                    acci[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[a].x, zb[b].y, acci[a][b], 0, 0, 0);
-                }
+                    for (int b = 0; b < TN; ++b) {
+                        accr[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[a].x, zb[b].x, accr[a][b], 0, 0, 0);
+                        acci[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[a].x, zb[b].y, acci[a][b], 0, 0, 0);
+                    }
 #pragma unroll
-            for (int a = 0; a < TM; ++a)
+                for (int a = 0; a < TM; ++a)
 #pragma unroll
-                for (int b = 0; b < TN; ++b) {
-                    accr[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(-xa[a].y, zb[b].y, accr[a][b], 0, 0, 0);
-                    acci[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[a].y, zb[b].x, acci[a][b], 0, 0, 0);
-                }
+                    for (int b = 0; b < TN; ++b) {
+                        accr[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(-xa[a].y, zb[b].y, accr[a][b], 0, 0, 0);
+                        acci[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(xa[a].y, zb[b].x, acci[a][b], 0, 0, 0);
+                    }
+            }
         }
-        if (ch + 1 < nch) lstore(buf ^ 1);
+        if (ch + WK < nch) lstore(buf ^ 1);
         __syncthreads();
+    }
+    if constexpr (WK > 1) {
+        if (g > 0) {
+#pragma unroll
+            for (int a = 0; a < TM; ++a)
+#pragma unroll
+                for (int b = 0; b < TN; ++b)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        lds[(((g - 1) * TM + a) * TN + b) * 1024 + r * 256 + tid] =
+                            make_double2(accr[a][b][r], acci[a][b][r]);
+        }
+        __syncthreads();
+        if (g > 0) return;
     }
 #pragma unroll
     for (int a = 0; a < TM; ++a)
@@ -522,30 +570,44 @@ __global__ __launch_bounds__(256) void zgemm_mfma_kernel(const double2* __restri
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int row = s0 + wm * WM + a * 16 + kq + 4 * r;
-                if (row < M && col < n)
-                    C[size_t(crow ? crow[row] : row) * ldc + col] = make_double2(accr[a][b][r], acci[a][b][r]);
+                double2 v = make_double2(accr[a][b][r], acci[a][b][r]);
+#pragma unroll
+                for (int o = 0; o < WK - 1; ++o) {
+                    const double2 u = lds[((o * TM + a) * TN + b) * 1024 + r * 256 + tid];
+                    v.x += u.x;
+                    v.y += u.y;
+                }
+                if (row < M && col < Nc) C[size_t(crow ? crow[row] : row) * ldc + col] = v;
             }
         }
 }
 
-template <int BM, int BNC, int KC, int WGM, typename BT>
-static void launch_zgemm_tile(const double2* A, const BT* B, double2* C, int M, int n, int lda, int ldc,
-                              const int* arow, const int* crow, hipStream_t s) {
-    const size_t nblk = size_t((M + BM - 1) / BM) * size_t((n + BNC - 1) / BNC);
+template <int BM, int BNC, int KC, int WGM, int WK, typename BT>
+static void launch_zgemm_tile(const double2* A, const BT* B, double2* C, int M, int Nc, int K, int lda, int ldb,
+                              int ldc, const int* arow, const int* crow, hipStream_t s) {
+    const size_t nblk = size_t((M + BM - 1) / BM) * size_t((Nc + BNC - 1) / BNC);
     EFIE_REQUIRE(nblk < (size_t(1) << 31), EFIE_ERR_ARG, "zgemm: problem too large");
-    hipLaunchKernelGGL((zgemm_mfma_kernel<BM, BNC, KC, WGM, BT>), dim3(unsigned(nblk)), dim3(256), 0, s, A, B, C, M,
-                       n, lda, ldc, arow, crow);
+    hipLaunchKernelGGL((zgemm_mfma_kernel<BM, BNC, KC, WGM, WK, BT>), dim3(unsigned(nblk)), dim3(256 * WK), 0, s, A, B,
+                       C, M, Nc, K, lda, ldb, ldc, arow, crow);
 }
 
 template <typename BT>
-static void launch_zgemm_mfma(const double2* A, const BT* B, double2* C, int M, int n, int lda, int ldc,
-                              const int* arow, const int* crow, hipStream_t s) {
-    if (M <= 16)
-        launch_zgemm_tile<16, 64, 16, 1>(A, B, C, M, n, lda, ldc, arow, crow, s);
-    else if (M <= 64)
-        launch_zgemm_tile<32, 64, 16, 1>(A, B, C, M, n, lda, ldc, arow, crow, s);
+static void launch_zgemm_mfma(const double2* A, const BT* B, double2* C, int M, int Nc, int K, int lda, int ldb,
+                              int ldc, const int* arow, const int* crow, hipStream_t s) {
+    // Measured (us): 16 x 64 / 64 x 64 tiles of one group / 32 x 32 tiles of four groups:
+    //   7679 x 64:     728 / 1148 / 645     4320 x 64:    355 /  639 / 305     1920 x 100: 107 / 288 / 85
+    //   4320 x 12:     239 /  619 / 171     7680 x 16:    437 / 1107 / 313     20000 x 40: 3589 / 5143 / 3497
+    //   30000 x 12:   2844 / 7445 / 4208    7680 x 512:  4351 / 3936 / 3918
+    // Sixteen waves per CU hide the loads; few rows of a large matrix are bound by
+    // reading it once, and many blocks fill the chip with the widest tile as well.
+#define ZT(...) launch_zgemm_tile<__VA_ARGS__>(A, B, C, M, Nc, K, lda, ldb, ldc, arow, crow, s)
+    if (M <= 16 && Nc >= 16384)
+        ZT(16, 64, 16, 1, 1, BT);
+    else if (int64_t((M + 63) / 64) * ((Nc + 63) / 64) >= 1024)
+        ZT(64, 64, 16, 2, 1, BT);
     else
-        launch_zgemm_tile<64, 64, 16, 2>(A, B, C, M, n, lda, ldc, arow, crow, s);
+        ZT(32, 32, 8, 2, 4, BT);
+#undef ZT
 }
 
 void zgemm_nt(const void* A, int adt, const void* B, int bdt, void* C, int cdt, int M, int Nc, int K, int lda,
@@ -554,15 +616,15 @@ void zgemm_nt(const void* A, int adt, const void* B, int bdt, void* C, int cdt, 
     dim3 grid((Nc + GT - 1) / GT, (M + GT - 1) / GT), blk(256);
     EFIE_REQUIRE(grid.y <= 65535, EFIE_ERR_ARG, "zgemm: too many rows");
     prof_begin(PROF_ZGEMM, s);
-    // the operator products (B square, K = n, plain product): FP64 matrix cores
-    if (adt == EFIE_C128 && cdt == EFIE_C128 && (bdt == EFIE_C128 || bdt == EFIE_C64) && Nc == K && ldb == K &&
-        alr == 1.0 && ali == 0.0 && !accumulate && M >= 9) {
+    // plain products of at least nine rows: FP64 matrix cores
+    if (adt == EFIE_C128 && cdt == EFIE_C128 && (bdt == EFIE_C128 || bdt == EFIE_C64) && alr == 1.0 && ali == 0.0 &&
+        !accumulate && M >= 9) {
         if (bdt == EFIE_C128)
             launch_zgemm_mfma(static_cast<const double2*>(A), static_cast<const double2*>(B), static_cast<double2*>(C), M,
-                              K, lda, ldc, arow, crow, s);
+                              Nc, K, lda, ldb, ldc, arow, crow, s);
         else
             launch_zgemm_mfma(static_cast<const double2*>(A), static_cast<const float2*>(B), static_cast<double2*>(C), M,
-                              K, lda, ldc, arow, crow, s);
+                              Nc, K, lda, ldb, ldc, arow, crow, s);
         prof_end(PROF_ZGEMM, s, 8.0 * M * double(Nc) * K);
         return;
     }
