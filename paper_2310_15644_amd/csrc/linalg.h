@@ -16,9 +16,9 @@ void zgemm_nt(const void* A, int adt, const void* B, int bdt, void* C, int cdt, 
 
 // Y[idx[c]] = Z X[idx[c]] for c < m <= 8 FP64 vectors (device idx), FP64 accumulation.
 // part: FP64 partial sums of the K-split product, gemv_multi_part_bytes(n) bytes
-// (nullptr: no split)
+// (nullptr: no split).  live: device count, nothing is done when it is 0 (nullptr: always done)
 void gemv_multi(const void* Z, int zdt, int n, const double2* X, const int* idx, int m, double2* Y, hipStream_t s,
-                double2* part);
+                double2* part, const int* live = nullptr);
 size_t gemv_multi_part_bytes(int n);
 
 // complex64 staging of selected FP64 rows and the way back

@@ -114,8 +114,11 @@ __global__ __launch_bounds__(256) void gemv_c64_kernel(const float2* __restrict_
 // read once for all m columns, FP64 accumulation with explicit FMAs, and the loads
 // of the next K step issued before the arithmetic of the current one.
 constexpr int GEMV_SLABS = 8;   // K slabs of the split product (three or more columns)
+// rows of a wave: an X element loaded serves all of them; one where several would leave
+// CUs idle (n = 480: 30 blocks with four, 120 with one)
 template <int MC>
 constexpr int gemv_rw() { return MC >= 8 ? 2 : 4; }
+constexpr int GEMV_ONE_ROW = 4096;   // orders below take one row a wave for one column
 
 template <typename ZT>
 __device__ __forceinline__ double2 to_d2(ZT v) { return make_double2(double(v.x), double(v.y)); }
@@ -124,12 +127,13 @@ __device__ __forceinline__ double2 to_d2(ZT v) { return make_double2(double(v.x)
 // go to part[(slab * MC + c) * n + row] (added by gemv_multi_reduce_kernel); the
 // row blocks of one slab are dispatched together, so the slab of X they all read
 // stays in L2.
-template <typename ZT, int MC, bool SPLIT>
+// live: nothing is done once *live is 0 (no column of the solve is active any more)
+template <typename ZT, int MC, bool SPLIT, int RW>
 __global__ __launch_bounds__(256) void gemv_multi_kernel(const ZT* __restrict__ Z, const double2* __restrict__ X,
                                                          const int* __restrict__ idx, int m,
                                                          double2* __restrict__ Y, int n, int kslab,
-                                                         double2* __restrict__ part) {
-    constexpr int RW = gemv_rw<MC>();
+                                                         double2* __restrict__ part, const int* __restrict__ live) {
+    if (live && *live == 0) return;
     const int row0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * RW;
     const int lane = threadIdx.x & 63;
     if (row0 >= n) return;
@@ -330,9 +334,10 @@ void cast_c64_to_c128(const void* a, void* b, size_t n, hipStream_t s) {
 size_t gemv_multi_part_bytes(int n) { return size_t(GEMV_SLABS) * 8 * size_t(n) * sizeof(double2); }
 
 void gemv_multi(const void* Z, int zdt, int n, const double2* X, const int* idx, int m, double2* Y, hipStream_t s,
-                double2* part) {
+                double2* part, const int* live) {
     EFIE_REQUIRE(m >= 1 && m <= 8, EFIE_ERR_ARG, "gemv_multi: 1..8 columns");
-    const int rw = m > 4 ? gemv_rw<8>() : gemv_rw<4>();
+    const bool one = m == 1 && n < GEMV_ONE_ROW;
+    const int rw = one ? 1 : (m > 4 ? gemv_rw<8>() : gemv_rw<4>());
     const int rb = (n + 4 * rw - 1) / (4 * rw);
     // three or more columns: split K so that the X slab in use stays in L2
     const bool split = part != nullptr && m >= 3 && n >= 64 * GEMV_SLABS;
@@ -343,13 +348,16 @@ void gemv_multi(const void* Z, int zdt, int n, const double2* X, const int* idx,
 #define GM(ZTy, MC)                                                                                                \
     do {                                                                                                           \
         if (split) {                                                                                               \
-            hipLaunchKernelGGL((gemv_multi_kernel<ZTy, MC, true>), grid, blk, 0, s, static_cast<const ZTy*>(Z), X, \
-                               idx, m, Y, n, kslab, part);                                                         \
+            hipLaunchKernelGGL((gemv_multi_kernel<ZTy, MC, true, gemv_rw<MC>()>), grid, blk, 0, s,                 \
+                               static_cast<const ZTy*>(Z), X, idx, m, Y, n, kslab, part, live);                    \
             hipLaunchKernelGGL((gemv_multi_reduce_kernel<MC>), dim3((n + 255) / 256, m), dim3(256), 0, s, part, idx, \
                                m, n, ns, Y);                                                                       \
+        } else if (MC == 1 && one) {                                                                               \
+            hipLaunchKernelGGL((gemv_multi_kernel<ZTy, MC, false, 1>), grid, blk, 0, s,                            \
+                               static_cast<const ZTy*>(Z), X, idx, m, Y, n, n, nullptr, live);                     \
         } else {                                                                                                   \
-            hipLaunchKernelGGL((gemv_multi_kernel<ZTy, MC, false>), grid, blk, 0, s, static_cast<const ZTy*>(Z),   \
-                               X, idx, m, Y, n, n, nullptr);                                                       \
+            hipLaunchKernelGGL((gemv_multi_kernel<ZTy, MC, false, gemv_rw<MC>()>), grid, blk, 0, s,                \
+                               static_cast<const ZTy*>(Z), X, idx, m, Y, n, n, nullptr, live);                     \
         }                                                                                                          \
     } while (0)
     if (zdt == EFIE_C128) {
