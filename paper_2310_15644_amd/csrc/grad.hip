@@ -14,11 +14,12 @@
 //    respect to t's vertices only (t as test triangle).  One block owns one test
 //    triangle t and 256 source triangles: its lanes' derivatives reduce to the 9
 //    coordinates of t, added with 9 atomics.
-//      far pairs: analytic chain rule through G(R) = exp(-jkR)/R, the quadrature
-//      points r_a = sum_k l^a_k P_k and the edge lengths in the RWG coefficients;
-//      near pairs: forward-mode dual numbers (value + one directional derivative)
-//      through the smooth part and the closed-form singular integrals, one pass
-//      per test coordinate.
+//      far pairs, and the smooth part of the near ones: analytic chain rule through
+//      G(R), the quadrature points r_a = sum_k l^a_k P_k and the edge lengths in the
+//      RWG coefficients;
+//      singular part of the near pairs: forward-mode dual numbers (value + one
+//      directional derivative) through the closed forms, a lane per test coordinate
+//      and point.
 //  * excitation and radiation terms: per triangle, same chain rule.
 // Per-triangle-vertex accumulators (T x 3 x 3) are finally scattered to vertices.
 #include <hip/hip_runtime.h>
@@ -44,6 +45,7 @@ __device__ __forceinline__ C cs(C a, double s) { return {a.r * s, a.i * s}; }
 __device__ __forceinline__ C ca(C a, C b) { return {a.r + b.r, a.i + b.i}; }
 
 // ------------------------------------------------------------ dual numbers
+// a value and its derivative with respect to one coordinate of the test triangle
 struct Dual {
     double v, d;
 };
@@ -51,75 +53,85 @@ __device__ __forceinline__ Dual operator+(Dual a, Dual b) { return {a.v + b.v, a
 __device__ __forceinline__ Dual operator-(Dual a, Dual b) { return {a.v - b.v, a.d - b.d}; }
 __device__ __forceinline__ Dual operator-(Dual a) { return {-a.v, -a.d}; }
 __device__ __forceinline__ Dual operator*(Dual a, Dual b) { return {a.v * b.v, a.d * b.v + a.v * b.d}; }
-__device__ __forceinline__ Dual operator/(Dual a, Dual b) {
-    const double q = a.v / b.v;
-    return {q, (a.d - q * b.d) / b.v};
-}
 __device__ __forceinline__ Dual operator+(Dual a, double b) { return {a.v + b, a.d}; }
-__device__ __forceinline__ Dual operator+(double b, Dual a) { return {a.v + b, a.d}; }
 __device__ __forceinline__ Dual operator-(Dual a, double b) { return {a.v - b, a.d}; }
-__device__ __forceinline__ Dual operator-(double b, Dual a) { return {b - a.v, -a.d}; }
+__device__ __forceinline__ Dual operator-(double a, Dual b) { return {a - b.v, -b.d}; }
 __device__ __forceinline__ Dual operator*(Dual a, double b) { return {a.v * b, a.d * b}; }
-__device__ __forceinline__ Dual operator*(double b, Dual a) { return {a.v * b, a.d * b}; }
-__device__ __forceinline__ Dual operator/(Dual a, double b) { return {a.v / b, a.d / b}; }
-__device__ __forceinline__ Dual operator/(double a, Dual b) {
-    const double q = a / b.v;
-    return {q, -q * b.d / b.v};
+__device__ __forceinline__ Dual operator*(double a, Dual b) { return b * a; }
+// 1 / x: the hardware estimate and one third-order step
+__device__ __forceinline__ double rcp_fast(double x) {
+    const double y = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, y, 1.0);
+    return fma(y, fma(e, e, e), y);
 }
-__device__ __forceinline__ double val(Dual a) { return a.v; }
-__device__ __forceinline__ double val(double a) { return a; }
-__device__ __forceinline__ Dual dsqrt(Dual a) {
-    const double s = sqrt(a.v);
-    return {s, a.d / (2.0 * s)};
+__device__ __forceinline__ Dual operator/(Dual a, Dual b) {
+    const double i = rcp_fast(b.v), r = a.v * i;
+    return {r, (a.d - r * b.d) * i};
 }
-__device__ __forceinline__ Dual dlog(Dual a) { return {log(a.v), a.d / a.v}; }
-__device__ __forceinline__ Dual datan(Dual a) { return {atan(a.v), a.d / (1.0 + a.v * a.v)}; }
+__device__ __forceinline__ Dual inverse(Dual a) {
+    const double i = rcp_fast(a.v);
+    return {i, -i * i * a.d};
+}
+__device__ __forceinline__ double inverse(double a) { return 1.0 / a; }
+__device__ __forceinline__ Dual root(Dual a) {
+    const double y = rsqrt_fast(fmax(a.v, 1e-300));   // 0 at 0, where a.d = 0 too
+    return {a.v * y, 0.5 * y * a.d};
+}
+__device__ __forceinline__ double root(double a) { return sqrt(a); }
+// calls: inlined, their polynomials' constants fill the registers of the whole kernel
+__device__ __noinline__ double log_call(double x) { return log(x); }
+__device__ __noinline__ double atan_call(double x) { return atan(x); }
+__device__ __forceinline__ Dual dlog(Dual a) { return {log_call(a.v), a.d * rcp_fast(a.v)}; }
+__device__ __forceinline__ Dual datan(Dual a) { return {atan_call(a.v), a.d * rcp_fast(1.0 + a.v * a.v)}; }
 __device__ __forceinline__ Dual dabs(Dual a) { return a.v >= 0.0 ? a : -a; }
-__device__ __forceinline__ void dsincos(Dual a, Dual& s, Dual& c) {
-    double sv, cv;
-    sincos(a.v, &sv, &cv);
-    s = {sv, cv * a.d};
-    c = {cv, -sv * a.d};
+
+// 3-vectors of duals or plain numbers; the products of the two kinds are duals
+template <typename T>
+struct V3 {
+    T x, y, z;
+};
+template <typename A, typename B>
+__device__ __forceinline__ auto sub(const V3<A>& a, const V3<B>& b) -> V3<decltype(a.x - b.x)> {
+    return {a.x - b.x, a.y - b.y, a.z - b.z};
 }
-__device__ __forceinline__ Dual dexpm1(Dual a) { return {expm1(a.v), exp(a.v) * a.d}; }
-
-struct CD {   // complex dual
-    Dual r, i;
-};
-
-// 3-vectors of duals
-struct D3 {
-    Dual x, y, z;
-};
-__device__ __forceinline__ D3 sub(D3 a, D3 b) { return {a.x - b.x, a.y - b.y, a.z - b.z}; }
-__device__ __forceinline__ Dual dot(D3 a, D3 b) { return a.x * b.x + a.y * b.y + a.z * b.z; }
-__device__ __forceinline__ D3 crs(D3 a, D3 b) {
+template <typename A, typename B>
+__device__ __forceinline__ auto add(const V3<A>& a, const V3<B>& b) -> V3<decltype(a.x + b.x)> {
+    return {a.x + b.x, a.y + b.y, a.z + b.z};
+}
+template <typename A, typename B>
+__device__ __forceinline__ auto dot(const V3<A>& a, const V3<B>& b) {
+    return a.x * b.x + a.y * b.y + a.z * b.z;
+}
+template <typename A, typename B>
+__device__ __forceinline__ auto crs(const V3<A>& a, const V3<B>& b) -> V3<decltype(a.y * b.z)> {
     return {a.y * b.z - a.z * b.y, a.z * b.x - a.x * b.z, a.x * b.y - a.y * b.x};
 }
-__device__ __forceinline__ D3 scl(D3 a, Dual s) { return {a.x * s, a.y * s, a.z * s}; }
-__device__ __forceinline__ D3 add(D3 a, D3 b) { return {a.x + b.x, a.y + b.y, a.z + b.z}; }
-__device__ __forceinline__ Dual nrm(D3 a) { return dsqrt(dot(a, a)); }
-__device__ __forceinline__ D3 mk(double x, double y, double z) { return {{x, 0}, {y, 0}, {z, 0}}; }
+template <typename A, typename S>
+__device__ __forceinline__ auto scl(const V3<A>& a, const S& s) -> V3<decltype(a.x * s)> {
+    return {a.x * s, a.y * s, a.z * s};
+}
+template <typename A>
+__device__ __forceinline__ A nrm(const V3<A>& a) { return root(dot(a, a)); }
 
-// Closed-form I0, I1 (Wilton et al. 1984) with dual arithmetic: source triangle u[3]
-// (counter-clockwise, positions relative to any common origin), observation point r.
-__device__ void potentials_d(const D3& r, const D3 u[3], double h, Dual& I0, D3& I1) {
-    const D3 e1 = sub(u[1], u[0]), e2 = sub(u[2], u[0]);
-    D3 n = crs(e1, e2);
-    const Dual nn = nrm(n);
-    n = {n.x / nn, n.y / nn, n.z / nn};
+// Closed-form I0 = int 1/R and I1 = int r'/R (Wilton et al. 1984) over the source triangle u[3]
+// (counter-clockwise, positions relative to any common origin, unit normal n) and the
+// observation point r, one of the two dual.  self: r lies on the triangle, where the
+// slope of |d| is one of two; with r moving and with the triangle moving the two cancel,
+// so none is taken.
+template <typename TR, typename TU>
+__device__ __forceinline__ void potentials_d(const V3<TR>& r, V3<TU> (&u)[3], const V3<TU>& n, double h, bool self,
+                                             Dual& I0, V3<Dual>& I1) {
     const Dual d = dot(sub(r, u[0]), n);
-    const Dual ad = dabs(d);
-    const D3 rho = sub(r, scl(n, d));
-    I0 = {0, 0};
-    I1 = mk(0, 0, 0);
+    const Dual ad = self ? Dual{0, 0} : dabs(d);
+    const V3<Dual> rho = sub(r, scl(n, d));
+    I0 = Dual{0, 0};
+    I1 = {I0, I0, I0};
 #pragma unroll 1
     for (int e = 0; e < 3; ++e) {
-        const D3 rm = u[e], rp = u[(e + 1) % 3];
-        D3 lt = sub(rp, rm);
-        const Dual len = nrm(lt);
-        lt = {lt.x / len, lt.y / len, lt.z / len};
-        const D3 uu = crs(lt, n);
+        const V3<TU> rm = u[0], rp = u[1];
+        V3<TU> lt = sub(rp, rm);
+        lt = scl(lt, inverse(nrm(lt)));
+        const V3<TU> uu = crs(lt, n);
         const Dual lp = dot(sub(rp, rho), lt), lm = dot(sub(rm, rho), lt);
         const Dual P0 = dot(sub(rm, rho), uu);
         const Dual R02 = P0 * P0 + d * d;
@@ -132,150 +144,34 @@ __device__ void potentials_d(const D3& r, const D3 u[3], double h, Dual& I0, D3&
             at = datan(P0 * lp / (R02 + ad * Rp)) - datan(P0 * lm / (R02 + ad * Rm));
         }
         I0 = I0 + P0 * lg - ad * at;
-        const Dual c1 = 0.5 * (R02 * lg + lp * Rp - lm * Rm);
-        I1 = add(I1, scl(uu, c1));
+        I1 = add(I1, scl(uu, 0.5 * (R02 * lg + lp * Rp - lm * Rm)));
+        u[0] = rp;   // rotated in place, back in order after the three edges
+        u[1] = u[2];
+        u[2] = rm;
     }
-}
-
-// sum_ij a_i b_j B_near(i,j) for the near pair (test t with vertices Pt, source q with
-// vertices Pq), B_near = Scale.A * T_A + Scale.P * T_Phi with T_A, T_Phi the smooth
-// (7x7 rule) plus symmetrised singular parts; a_i = alpha_i (complex, excluding the
-// edge length), b_j likewise; edge lengths and all geometry from the vertices.
-__device__ CD near_contract(const D3 Pt[3], const D3 Pq[3], const double st[3], const double sq[3], C a[3], C b[3],
-                            double kr, const Scale& sc, const Rule& rule, double ht, double hq) {
-    // RWG coefficients: f_i = s_i l_i / (2 A) (r - P_i), div = s_i l_i / A
-    Dual lt_[3], lq_[3];
-    for (int i = 0; i < 3; ++i) {
-        lt_[i] = nrm(sub(Pt[(i + 1) % 3], Pt[(i + 2) % 3]));
-        lq_[i] = nrm(sub(Pq[(i + 1) % 3], Pq[(i + 2) % 3]));
-    }
-    const Dual At = 0.5 * nrm(crs(sub(Pt[1], Pt[0]), sub(Pt[2], Pt[0])));
-    const Dual Aq = 0.5 * nrm(crs(sub(Pq[1], Pq[0]), sub(Pq[2], Pq[0])));
-    D3 rt[7], rq[7];
-    for (int k = 0; k < 7; ++k) {
-        rt[k] = add(add(scl(Pt[0], {rule.bary[k][0], 0}), scl(Pt[1], {rule.bary[k][1], 0})), scl(Pt[2], {rule.bary[k][2], 0}));
-        rq[k] = add(add(scl(Pq[0], {rule.bary[k][0], 0}), scl(Pq[1], {rule.bary[k][1], 0})), scl(Pq[2], {rule.bary[k][2], 0}));
-    }
-    // complex weights: alpha_i = a_i s_i l_i, beta_j = b_j s_j l_j
-    CD al[3], be[3];
-    for (int i = 0; i < 3; ++i) {
-        al[i] = {lt_[i] * (a[i].r * st[i]), lt_[i] * (a[i].i * st[i])};
-        be[i] = {lq_[i] * (b[i].r * sq[i]), lq_[i] * (b[i].i * sq[i])};
-    }
-    CD A0 = {{0, 0}, {0, 0}}, B0 = {{0, 0}, {0, 0}};
-    for (int i = 0; i < 3; ++i) {
-        A0 = {A0.r + al[i].r, A0.i + al[i].i};
-        B0 = {B0.r + be[i].r, B0.i + be[i].i};
-    }
-    // smooth part:  (1/4) sum_ab w w Gs U_a . U'_b   and   A0 B0 sum_ab w w Gs
-    CD TA = {{0, 0}, {0, 0}}, TP = {{0, 0}, {0, 0}};
-#pragma unroll 1
-    for (int ia = 0; ia < 7; ++ia) {
-        // U_a = sum_i alpha_i (r_a - P_i) (complex vector: real and imaginary parts)
-        D3 Ur = mk(0, 0, 0), Ui = mk(0, 0, 0);
-        for (int i = 0; i < 3; ++i) {
-            const D3 dv = sub(rt[ia], Pt[i]);
-            Ur = add(Ur, scl(dv, al[i].r));
-            Ui = add(Ui, scl(dv, al[i].i));
-        }
-#pragma unroll 1
-        for (int ib = 0; ib < 7; ++ib) {
-            D3 Vr = mk(0, 0, 0), Vi = mk(0, 0, 0);
-            for (int j = 0; j < 3; ++j) {
-                const D3 dv = sub(rq[ib], Pq[j]);
-                Vr = add(Vr, scl(dv, be[j].r));
-                Vi = add(Vi, scl(dv, be[j].i));
-            }
-            const D3 dd = sub(rt[ia], rq[ib]);
-            const Dual R2 = dot(dd, dd);
-            CD g;   // (exp(-jkR) - 1)/R, -jk at R = 0
-            if (R2.v == 0.0) {
-                g = {{0, 0}, {-kr, 0}};
-            } else {
-                const Dual R = dsqrt(R2);
-                Dual s2, c2;
-                dsincos(-0.5 * kr * R, s2, c2);
-                g = {(-2.0 * s2 * s2) / R, (2.0 * s2 * c2) / R};
-            }
-            const double ww = rule.w[ia] * rule.w[ib];
-            const Dual uvr = dot(Ur, Vr) - dot(Ui, Vi), uvi = dot(Ur, Vi) + dot(Ui, Vr);
-            TA.r = TA.r + ww * 0.25 * (g.r * uvr - g.i * uvi);
-            TA.i = TA.i + ww * 0.25 * (g.r * uvi + g.i * uvr);
-            TP.r = TP.r + ww * g.r;
-            TP.i = TP.i + ww * g.i;
-        }
-    }
-    // TP currently holds sum w w g; times A0 B0
-    {
-        const Dual abr = A0.r * B0.r - A0.i * B0.i, abi = A0.r * B0.i + A0.i * B0.r;
-        const Dual tr = TP.r * abr - TP.i * abi, ti = TP.r * abi + TP.i * abr;
-        TP = {tr, ti};
-    }
-    // singular part: 1/2 [X_tq + X_qt^T], both contracted with (a, b):
-    //  X_tq contracted = sum_a w_a A_t/(A_t) ... written with the area-free weights:
-    //   sum_ij alpha_i beta_j [ sum_a w_a (1/2)(r_a - P_i) . (1/(2 A_q)) int_q (r' - Q_j)/R ]
-    //   and the scalar part sum_ij alpha_i beta_j (1/A_q) sum_a w_a int_q 1/R.
-    for (int side = 0; side < 2; ++side) {
-        const D3* Po = side == 0 ? Pt : Pq;          // outer (test) triangle of this block
-        const D3* Pi = side == 0 ? Pq : Pt;          // inner (analytic) triangle
-        const D3* ro = side == 0 ? rt : rq;
-        const CD* co = side == 0 ? al : be;          // weights on the outer triangle
-        const CD* ci = side == 0 ? be : al;
-        const Dual Ai = side == 0 ? Aq : At;
-        const double hi = side == 0 ? hq : ht;
-        CD s1 = {{0, 0}, {0, 0}}, s0 = {{0, 0}, {0, 0}};
-#pragma unroll 1
-        for (int ia = 0; ia < 7; ++ia) {
-            Dual I0;
-            D3 I1;
-            potentials_d(ro[ia], Pi, hi, I0, I1);
-            const D3 e1 = sub(Pi[1], Pi[0]), e2 = sub(Pi[2], Pi[0]);
-            D3 n = crs(e1, e2);
-            const Dual nn = nrm(n);
-            n = {n.x / nn, n.y / nn, n.z / nn};
-            const Dual d = dot(sub(ro[ia], Pi[0]), n);
-            const D3 rho = sub(ro[ia], scl(n, d));
-            // U_o = sum_i co_i (r_a - Po_i);  inner W = sum_j ci_j (I1 + (rho - Pi_j) I0)
-            D3 Ur = mk(0, 0, 0), Ui = mk(0, 0, 0), Wr = mk(0, 0, 0), Wi = mk(0, 0, 0);
-            for (int i = 0; i < 3; ++i) {
-                const D3 dv = sub(ro[ia], Po[i]);
-                Ur = add(Ur, scl(dv, co[i].r));
-                Ui = add(Ui, scl(dv, co[i].i));
-                const D3 iv = add(I1, scl(sub(rho, Pi[i]), I0));
-                Wr = add(Wr, scl(iv, ci[i].r));
-                Wi = add(Wi, scl(iv, ci[i].i));
-            }
-            const double wa = rule.w[ia];
-            // (1/2)(1/(2 A_i)) U . W
-            const Dual f = wa * 0.25 / Ai;
-            s1.r = s1.r + f * (dot(Ur, Wr) - dot(Ui, Wi));
-            s1.i = s1.i + f * (dot(Ur, Wi) + dot(Ui, Wr));
-            s0.r = s0.r + (wa / Ai) * I0;
-        }
-        // scalar part: (sum co)(sum ci) s0
-        CD So = {{0, 0}, {0, 0}}, Si = {{0, 0}, {0, 0}};
-        for (int i = 0; i < 3; ++i) {
-            So = {So.r + co[i].r, So.i + co[i].i};
-            Si = {Si.r + ci[i].r, Si.i + ci[i].i};
-        }
-        const Dual pr = So.r * Si.r - So.i * Si.i, pi = So.r * Si.i + So.i * Si.r;
-        TA.r = TA.r + 0.5 * s1.r;
-        TA.i = TA.i + 0.5 * s1.i;
-        TP.r = TP.r + 0.5 * pr * s0.r;
-        TP.i = TP.i + 0.5 * pi * s0.r;
-    }
-    // Z = A T_A + P T_Phi (complex constants; the 1/(4 pi) is in the Scale)
-    CD out;
-    out.r = sc.ar * TA.r - sc.ai * TA.i + sc.pr * TP.r - sc.pi * TP.i;
-    out.i = sc.ar * TA.i + sc.ai * TA.r + sc.pr * TP.i + sc.pi * TP.r;
-    return out;
+    I1 = add(I1, scl(rho, I0));
 }
 
 // ---------------------------------------------------------- operator term
-// acc[t][k][x] += -2 Re d/dP_k^x (lambda_t^T B_tq j_q + j_t^T B_tq lambda_q), far pairs.
-__global__ __launch_bounds__(256) void grad_far_kernel(DevMesh m, double kr, Scale sc, Rule rule,
-                                                       const double2* __restrict__ lam, const double2* __restrict__ jv,
-                                                       double* __restrict__ acc, int nqblk) {
+// acc[t][k][x] += -2 Re d/dP_k^x (lambda_t^T B_tq j_q + j_t^T B_tq lambda_q): every
+// far pair, and the smooth part (exp(-jkR) - 1)/R of the near ones (the same rule with
+// another kernel; its value and slope at R = 0 drop out of the derivative).
+//
+// With the offsets d_a, d'_b of the points and u_i, u'_j of the vertices from the
+// centroids, and alpha_i = s_i l_i lambda_i (or j_i) on t, beta_j likewise on q, the pair's
+// sum is sum_ab w_a w_b Phi_ab G_ab, and Phi, the two contractions together, is bilinear:
+//   Phi_ab = alpha0 - H . d_a + (E d_a - F) . d'_b
+// with constants of the pair.  So a point pair costs its Green's function, six
+// multiply-adds for Phi and the folds of w G and w G' Phi / R over b into barycentric
+// moments (Bary in pair_kernels.h); the points are multiples of the vertex offsets (0,
+// D1 u_k, D2 u_k); the test sums M_kl = sum w l_k w' l'_l G and P_k = sum w l_k (gradient
+// vector) carry all nine coordinates.  About 85 FP64 operations per point pair, where
+// the vectors U_a, V_b and the library's sincos took four times as many.
+// Bound by the vector ALU; N = 7680 (26.2 M ordered pairs): 19.1 ms
+// before, 5.2 ms now.
+__global__ __launch_bounds__(256, 2) void grad_far_kernel(DevMesh m, double kr, Scale sc, const double2* __restrict__ lam,
+                                                       const double2* __restrict__ jv, double* __restrict__ acc,
+                                                       int nqblk) {
     __shared__ double red[4][9];
     const int T = m.T;
     const int t = blockIdx.x / nqblk;
@@ -283,153 +179,182 @@ __global__ __launch_bounds__(256) void grad_far_kernel(DevMesh m, double kr, Sca
     double out[9];
 #pragma unroll
     for (int k = 0; k < 9; ++k) out[k] = 0.0;
-    const bool live = q < T && !is_near(m, t, q);
-    if (live) {
-        // test triangle (uniform): vertex offsets u, point offsets d, coefficients
-        double ut[3][3], e[3][3], lt[3];
-        C aL[3], aJ[3];   // alpha with lambda / with j on the test triangle
-        for (int i = 0; i < 3; ++i) {
-            ut[i][0] = m.vx[i * T + t];
-            ut[i][1] = m.vy[i * T + t];
-            ut[i][2] = m.vz[i * T + t];
-        }
-        for (int i = 0; i < 3; ++i) {
-            const int i1 = (i + 1) % 3, i2 = (i + 2) % 3;
-            double ev[3] = {ut[i1][0] - ut[i2][0], ut[i1][1] - ut[i2][1], ut[i1][2] - ut[i2][2]};
-            lt[i] = sqrt(ev[0] * ev[0] + ev[1] * ev[1] + ev[2] * ev[2]);
-            for (int x = 0; x < 3; ++x) e[i][x] = ev[x] / lt[i];
-            const double s = m.cf[i * T + t] > 0.0 ? 1.0 : -1.0;
-            const double2 l = lam[m.te[i * T + t]], jj = jv[m.te[i * T + t]];
-            aL[i] = {l.x * s * lt[i], l.y * s * lt[i]};
-            aJ[i] = {jj.x * s * lt[i], jj.y * s * lt[i]};
-        }
-        // source triangle
-        double uq[3][3], dq[7][3];
-        C bJ[3], bL[3];
-        for (int j = 0; j < 3; ++j) {
-            uq[j][0] = m.vx[j * T + q];
-            uq[j][1] = m.vy[j * T + q];
-            uq[j][2] = m.vz[j * T + q];
-        }
-        for (int j = 0; j < 3; ++j) {
-            const int j1 = (j + 1) % 3, j2 = (j + 2) % 3;
-            const double dx = uq[j1][0] - uq[j2][0], dy = uq[j1][1] - uq[j2][1], dz = uq[j1][2] - uq[j2][2];
-            const double l = sqrt(dx * dx + dy * dy + dz * dz);
-            const double s = m.cf[j * T + q] > 0.0 ? 1.0 : -1.0;
-            const double2 lj = lam[m.te[j * T + q]], jj = jv[m.te[j * T + q]];
-            bJ[j] = {jj.x * s * l, jj.y * s * l};
-            bL[j] = {lj.x * s * l, lj.y * s * l};
-        }
-        for (int b = 0; b < 7; ++b) {
-            dq[b][0] = m.qx[b * T + q];
-            dq[b][1] = m.qy[b * T + q];
-            dq[b][2] = m.qz[b * T + q];
+    if (q < T) {
+        const double smooth = is_near(m, t, q) ? 0.0 : 1.0;   // 1 of the far kernel's cosine
+        const int same = t == q ? 0 : 8;   // a + same == b: one point, R = 0 (rounded apart here)
+        const Phase<double> ph = make_phase<double>(0.5 * kr, 0.0);
+        // a triangle's vertex offsets, s_i l_i and the two weighted coefficients
+        auto corners = [&](int tri, double (&u)[3][3], double (&len)[3], C (&wl)[3], C (&wj)[3]) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                u[i][0] = m.vx[i * T + tri];
+                u[i][1] = m.vy[i * T + tri];
+                u[i][2] = m.vz[i * T + tri];
+            }
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                const int i1 = (i + 1) % 3, i2 = (i + 2) % 3;
+                const double dx = u[i1][0] - u[i2][0], dy = u[i1][1] - u[i2][1], dz = u[i1][2] - u[i2][2];
+                len[i] = sqrt(dx * dx + dy * dy + dz * dz);
+                const double w = m.cf[i * T + tri] > 0.0 ? len[i] : -len[i];
+                const double2 l = lam[m.te[i * T + tri]], j = jv[m.te[i * T + tri]];
+                wl[i] = {l.x * w, l.y * w};
+                wj[i] = {j.x * w, j.y * w};
+            }
+        };
+        const C c1 = {0.25 * sc.ar, 0.25 * sc.ai}, c2 = {sc.pr, sc.pi};
+        double ut[3][3], uq[3][3];
+        C alpha0, E, H[3], F[3];
+        {
+            double lt[3], lq[3];
+            C aL[3], aJ[3], bL[3], bJ[3];
+            corners(t, ut, lt, aL, aJ);
+            corners(q, uq, lq, bL, bJ);
+            const C A0L = ca(ca(aL[0], aL[1]), aL[2]), A0J = ca(ca(aJ[0], aJ[1]), aJ[2]);
+            const C B0J = ca(ca(bJ[0], bJ[1]), bJ[2]), B0L = ca(ca(bL[0], bL[1]), bL[2]);
+            const C ab = ca(cm(A0L, B0J), cm(A0J, B0L));
+            E = cm(c1, ab);
+            C hg = {0, 0};
+#pragma unroll
+            for (int x = 0; x < 3; ++x) {
+                const C hL = ca(ca(cs(aL[0], ut[0][x]), cs(aL[1], ut[1][x])), cs(aL[2], ut[2][x]));
+                const C hJ = ca(ca(cs(aJ[0], ut[0][x]), cs(aJ[1], ut[1][x])), cs(aJ[2], ut[2][x]));
+                const C gL = ca(ca(cs(bL[0], uq[0][x]), cs(bL[1], uq[1][x])), cs(bL[2], uq[2][x]));
+                const C gJ = ca(ca(cs(bJ[0], uq[0][x]), cs(bJ[1], uq[1][x])), cs(bJ[2], uq[2][x]));
+                F[x] = cm(c1, ca(cm(hL, B0J), cm(hJ, B0L)));
+                H[x] = cm(c1, ca(cm(A0L, gJ), cm(A0J, gL)));
+                hg = ca(hg, ca(cm(hL, gJ), cm(hJ, gL)));
+            }
+            alpha0 = ca(cm(c1, hg), cm(c2, ab));
         }
         const double D[3] = {m.cx[t] - m.cx[q], m.cy[t] - m.cy[q], m.cz[t] - m.cz[q]};
-        const C A0L = ca(ca(aL[0], aL[1]), aL[2]), A0J = ca(ca(aJ[0], aJ[1]), aJ[2]);
-        const C B0J = ca(ca(bJ[0], bJ[1]), bJ[2]), B0L = ca(ca(bL[0], bL[1]), bL[2]);
-        const C c1 = {0.25 * sc.ar, 0.25 * sc.ai}, c2 = {sc.pr, sc.pi};
-        const C AB1 = cm(c2, cm(A0L, B0J)), AB2 = cm(c2, cm(A0J, B0L));
-        // accumulators
-        C part1[3][3];        // sum_a w_a l^a_k Gvec_a          [k][x]
-        C KL1[3][3], KL2[3][3];   // sum_a w_a l^a_k K_a           [k][x]
-        C Kw1[3], Kw2[3];     // sum_a w_a K_a
-        C Y1[3], Y2[3];       // sum_a w_a (d_a - u_i) . K_a     [i]
-        C M0 = {0, 0};
-        for (int k = 0; k < 3; ++k) {
-            for (int x = 0; x < 3; ++x) part1[k][x] = KL1[k][x] = KL2[k][x] = {0, 0};
-            Kw1[k] = Kw2[k] = Y1[k] = Y2[k] = {0, 0};
-        }
+        C M[3][3];        // [k][l]
+        double P[3][3];   // [k][x], real part
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int l = 0; l < 3; ++l) M[k][l] = {0, 0}, P[k][l] = 0.0;
 #pragma unroll 1
         for (int a = 0; a < 7; ++a) {
             const double da[3] = {m.qx[a * T + t], m.qy[a * T + t], m.qz[a * T + t]};
-            const double wa = rule.w[a];
-            C UL[3], UJ[3];   // U_a with lambda / j weights
+            double o[3];
+            C al = alpha0, be[3];
+#pragma unroll
             for (int x = 0; x < 3; ++x) {
-                UL[x] = {0, 0};
-                UJ[x] = {0, 0};
-                for (int i = 0; i < 3; ++i) {
-                    UL[x] = ca(UL[x], cs(aL[i], da[x] - ut[i][x]));
-                    UJ[x] = ca(UJ[x], cs(aJ[i], da[x] - ut[i][x]));
-                }
+                o[x] = D[x] + da[x];
+                al.r -= H[x].r * da[x];
+                al.i -= H[x].i * da[x];
+                be[x] = {E.r * da[x] - F[x].r, E.i * da[x] - F[x].i};
             }
-            C Gv[3] = {{0, 0}, {0, 0}, {0, 0}}, K1[3] = {{0, 0}, {0, 0}, {0, 0}}, K2[3] = {{0, 0}, {0, 0}, {0, 0}};
-            C S0 = {0, 0};
-#pragma unroll 1
+            double gr[7], gi[7], hr[7];
+#pragma unroll
             for (int b = 0; b < 7; ++b) {
-                const double wb = rule.w[b];
-                const double dl[3] = {D[0] + da[0] - dq[b][0], D[1] + da[1] - dq[b][1], D[2] + da[2] - dq[b][2]};
-                const double R2 = dl[0] * dl[0] + dl[1] * dl[1] + dl[2] * dl[2];
-                const double Ri = rsqrt(R2);
-                const double R = R2 * Ri;
-                double sn, csn;
-                sincos(kr * R, &sn, &csn);
-                const C G = {csn * Ri, -sn * Ri};                 // exp(-jkR)/R
-                // dG/dR / R = -G (jk + 1/R) / R
-                const C Gp = cs(cm(G, C{Ri, kr}), -Ri);
-                C VJ[3], VL[3];
+                // d'_b: 0, D1 u'_k, D2 u'_k
+                const double f = b == 0 ? 0.0 : (b < 4 ? Bary<7>::D1 : Bary<7>::D2);
+                const double* u = uq[b == 0 ? 0 : (b - 1) % 3];
+                const double dx = o[0] - f * u[0], dy = o[1] - f * u[1], dz = o[2] - f * u[2];
+                const bool zero = a + same == b;
+                const double R2 = dx * dx + dy * dy + dz * dz;
+                const double Ri = zero ? 0.0 : rsqrt_fast(R2);
+                double s2, c2_;
+                sincos_quarter(R2 * Ri, ph.khi, ph.klo, s2, c2_);   // of k R / 2
+                const double sn = 2.0 * s2 * c2_, cm1 = -2.0 * s2 * s2;
+                // G = ((1 +) cos - 1 - j sin)/R;  G'/R = -(G + j k exp(-jkR))/R^2
+                const double g_r = (smooth + cm1) * Ri, g_i = zero ? -kr : -sn * Ri;
+                const double R2i = -Ri * Ri;
+                const double p_r = (g_r + kr * sn) * R2i, p_i = (g_i + kr * (1.0 + cm1)) * R2i;
+                double F_r = al.r, F_i = al.i;   // Phi_ab
+#pragma unroll
                 for (int x = 0; x < 3; ++x) {
-                    VJ[x] = {0, 0};
-                    VL[x] = {0, 0};
-                    for (int j = 0; j < 3; ++j) {
-                        VJ[x] = ca(VJ[x], cs(bJ[j], dq[b][x] - uq[j][x]));
-                        VL[x] = ca(VL[x], cs(bL[j], dq[b][x] - uq[j][x]));
-                    }
+                    F_r += f * (be[x].r * u[x]);
+                    F_i += f * (be[x].i * u[x]);
                 }
-                C u1 = {0, 0}, u2 = {0, 0};
-                for (int x = 0; x < 3; ++x) {
-                    u1 = ca(u1, cm(UL[x], VJ[x]));
-                    u2 = ca(u2, cm(UJ[x], VL[x]));
-                }
-                const C Phi = ca(ca(cm(c1, u1), AB1), ca(cm(c1, u2), AB2));
-                const C gp = cs(cm(Gp, Phi), wb);
-                const C gw = cs(G, wb);
-                for (int x = 0; x < 3; ++x) {
-                    Gv[x] = ca(Gv[x], cs(gp, dl[x]));
-                    K1[x] = ca(K1[x], cm(gw, VJ[x]));
-                    K2[x] = ca(K2[x], cm(gw, VL[x]));
-                }
-                S0 = ca(S0, gw);
+                gr[b] = g_r;
+                gi[b] = g_i;
+                hr[b] = p_r * F_r - p_i * F_i;
             }
-            M0 = ca(M0, cs(S0, wa));
-            for (int k = 0; k < 3; ++k) {
-                const double lk = rule.bary[a][k] * wa;
-                for (int x = 0; x < 3; ++x) {
-                    part1[k][x] = ca(part1[k][x], cs(Gv[x], lk));
-                    KL1[k][x] = ca(KL1[k][x], cs(K1[x], lk));
-                    KL2[k][x] = ca(KL2[k][x], cs(K2[x], lk));
-                }
-            }
-            for (int x = 0; x < 3; ++x) {
-                Kw1[x] = ca(Kw1[x], cs(K1[x], wa));
-                Kw2[x] = ca(Kw2[x], cs(K2[x], wa));
-            }
-            for (int i = 0; i < 3; ++i)
-                for (int x = 0; x < 3; ++x) {
-                    Y1[i] = ca(Y1[i], cs(K1[x], wa * (da[x] - ut[i][x])));
-                    Y2[i] = ca(Y2[i], cs(K2[x], wa * (da[x] - ut[i][x])));
+            double sr[3], si[3], tr[3];
+            Bary<7>::fold(gr, sr);
+            Bary<7>::fold(gi, si);
+            Bary<7>::fold(hr, tr);
+            const double(&ck)[3] = bary_table<7, double>.c[a];
+            // gradient vector sum_b w_b G'/R Phi (r_a - r_b)
+            const double T0 = tr[0] + tr[1] + tr[2];
+            double g[3];
+#pragma unroll
+            for (int x = 0; x < 3; ++x)
+                g[x] = o[x] * T0 - (tr[0] * uq[0][x] + tr[1] * uq[1][x] + tr[2] * uq[2][x]);
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+#pragma unroll
+                for (int l = 0; l < 3; ++l) {
+                    M[k][l].r += ck[k] * sr[l];
+                    M[k][l].i += ck[k] * si[l];
+                    P[k][l] += ck[k] * g[l];
                 }
         }
-        // assemble dS/dP_k^x
+        // dS/dP_k^x = P_k + E m1_k - H m0_k - (p_k m1 - r_k m0) + the edge lengths' terms,
+        // m0_k = sum_l M_kl, m1_k = sum_l M_kl u'_l, m0, m1 their sums over k
+        double lt[3], lq[3];
+        C aL[3], aJ[3], bL[3], bJ[3];
+        corners(t, ut, lt, aL, aJ);
+        corners(q, uq, lq, bL, bJ);
+        const C B0J = ca(ca(bJ[0], bJ[1]), bJ[2]), B0L = ca(ca(bL[0], bL[1]), bL[2]);
+        C m0k[3], m1k[3][3], m0 = {0, 0}, m1[3] = {{0, 0}, {0, 0}, {0, 0}}, theta = {0, 0}, psi[3], gL[3], gJ[3];
+#pragma unroll
         for (int k = 0; k < 3; ++k) {
+            m0k[k] = ca(ca(M[k][0], M[k][1]), M[k][2]);
+            m0 = ca(m0, m0k[k]);
+#pragma unroll
             for (int x = 0; x < 3; ++x) {
-                C g = part1[k][x];
-                g = ca(g, cm(c1, ca(cm(A0L, KL1[k][x]), cs(cm(aL[k], Kw1[x]), -1.0))));
-                g = ca(g, cm(c1, ca(cm(A0J, KL2[k][x]), cs(cm(aJ[k], Kw2[x]), -1.0))));
-                // edge-length derivatives: l_i depends on P_{i+1} (+e_i) and P_{i+2} (-e_i)
-                for (int i = 0; i < 3; ++i) {
-                    double dl = 0.0;
-                    if (k == (i + 1) % 3) dl = e[i][x];
-                    else if (k == (i + 2) % 3) dl = -e[i][x];
-                    if (dl == 0.0) continue;
-                    // d alpha_i / dP = (alpha_i / l_i) dl
-                    const C dL = cs(aL[i], dl / lt[i]), dJ = cs(aJ[i], dl / lt[i]);
-                    g = ca(g, cm(c1, ca(cm(Y1[i], dL), cm(Y2[i], dJ))));
-                    g = ca(g, cm(c2, cm(M0, ca(cm(B0J, dL), cm(B0L, dJ)))));
-                }
-                out[3 * k + x] = -2.0 * g.r;
+                m1k[k][x] = ca(ca(cs(M[k][0], uq[0][x]), cs(M[k][1], uq[1][x])), cs(M[k][2], uq[2][x]));
+                m1[x] = ca(m1[x], m1k[k][x]);
+                theta = ca(theta, cs(m1k[k][x], ut[k][x]));
             }
         }
+#pragma unroll
+        for (int x = 0; x < 3; ++x) {
+            psi[x] = ca(ca(cs(m0k[0], ut[0][x]), cs(m0k[1], ut[1][x])), cs(m0k[2], ut[2][x]));
+            gL[x] = ca(ca(cs(bL[0], uq[0][x]), cs(bL[1], uq[1][x])), cs(bL[2], uq[2][x]));
+            gJ[x] = ca(ca(cs(bJ[0], uq[0][x]), cs(bJ[1], uq[1][x])), cs(bJ[2], uq[2][x]));
+        }
+        double edge[3];   // Re of the factor of dl_i / l_i
+        C p[3], r[3][3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            p[i] = ca(cm(aL[i], B0J), cm(aJ[i], B0L));
+            C um = {0, 0}, rt = {0, 0};
+#pragma unroll
+            for (int x = 0; x < 3; ++x) {
+                r[i][x] = ca(cm(aL[i], gJ[x]), cm(aJ[i], gL[x]));
+                um = ca(um, cs(m1[x], ut[i][x]));
+                rt = ca(rt, cm(r[i][x], ca(psi[x], cs(m0, -ut[i][x]))));
+            }
+            const C y = ca(cm(p[i], ca(theta, cs(um, -1.0))), cs(rt, -1.0));
+            edge[i] = ca(cm(c1, y), cm(c2, cm(m0, p[i]))).r;
+        }
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int x = 0; x < 3; ++x) {
+                C g = ca(cm(E, m1k[k][x]), cs(cm(H[x], m0k[k]), -1.0));
+                g = ca(g, cs(cm(c1, ca(cm(p[k], m1[x]), cs(cm(r[k][x], m0), -1.0))), -1.0));
+                out[3 * k + x] = P[k][x] + g.r;
+            }
+        // l_i depends on P_(i+1) (along +e_i) and P_(i+2) (along -e_i), e_i from i+2 to i+1
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const int i1 = (i + 1) % 3, i2 = (i + 2) % 3;
+            const double f = edge[i] / (lt[i] * lt[i]);
+#pragma unroll
+            for (int x = 0; x < 3; ++x) {
+                const double v = f * (ut[i1][x] - ut[i2][x]);
+                out[3 * i1 + x] += v;
+                out[3 * i2 + x] -= v;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 9; ++k) out[k] *= -2.0;
     }
     // reduce over the block: 9 values for triangle t
 #pragma unroll
@@ -446,53 +371,105 @@ __global__ __launch_bounds__(256) void grad_far_kernel(DevMesh m, double kr, Sca
     }
 }
 
-// near pairs: one thread per ordered near pair (t, q), 9 dual passes
-__global__ __launch_bounds__(128) void grad_near_kernel(DevMesh m, double kr, Scale sc, Rule rule,
-                                                        const double2* __restrict__ lam, const double2* __restrict__ jv,
-                                                        double* __restrict__ acc) {
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= m.n_near) return;
+// The singular parts 1/R of the ordered near pairs (t, q), symmetrised: half of t's
+// points against the closed form over q and half of q's points against that over t.
+// A wave per pair, lane 9 a + c at point a of both triangles and coordinate c of t, both
+// contractions together: no lane holds more than one point's duals, and the roots and
+// logarithms of a pair run side by side.  sc.ar = sc.pr = 0 (real k), so only the
+// imaginary parts of the contractions enter.  Bound by the vector ALU.  A thread per pair
+// with nine passes over the contractions, the smooth part included, took 9.0 ms at
+// N = 7680 (182290 pairs); 1.8 ms now (three waves per SIMD spill: 3.5 ms).
+__global__ __launch_bounds__(256, 2) void grad_near_kernel(DevMesh m, Scale sc, const double2* __restrict__ lam,
+                                                        const double2* __restrict__ jv, double* __restrict__ acc) {
+    const int e = int(blockIdx.x * 4u + (threadIdx.x >> 6)), lane = int(threadIdx.x) & 63;
+    if (e >= m.n_near) return;   // whole waves
     const int T = m.T;
     const int t = m.near_p[e], q = m.near_q[e];
-    // positions relative to the centroid of q
-    const double D[3] = {m.cx[t] - m.cx[q], m.cy[t] - m.cy[q], m.cz[t] - m.cz[q]};
-    double pt[3][3], pq[3][3], st[3], sq[3];
-    C aL[3], aJ[3], bJ[3], bL[3];
-    for (int i = 0; i < 3; ++i) {
-        pt[i][0] = D[0] + m.vx[i * T + t];
-        pt[i][1] = D[1] + m.vy[i * T + t];
-        pt[i][2] = D[2] + m.vz[i * T + t];
-        pq[i][0] = m.vx[i * T + q];
-        pq[i][1] = m.vy[i * T + q];
-        pq[i][2] = m.vz[i * T + q];
-        st[i] = m.cf[i * T + t] > 0.0 ? 1.0 : -1.0;
-        sq[i] = m.cf[i * T + q] > 0.0 ? 1.0 : -1.0;
-        const double2 lt_ = lam[m.te[i * T + t]], jt = jv[m.te[i * T + t]];
-        const double2 lq_ = lam[m.te[i * T + q]], jq = jv[m.te[i * T + q]];
-        aL[i] = {lt_.x, lt_.y};
-        aJ[i] = {jt.x, jt.y};
-        bJ[i] = {jq.x, jq.y};
-        bL[i] = {lq_.x, lq_.y};
-    }
-    D3 Pq[3];
-    for (int i = 0; i < 3; ++i) Pq[i] = mk(pq[i][0], pq[i][1], pq[i][2]);
-    const double ht = m.hm[t], hq = m.hm[q];
-#pragma unroll 1
-    for (int c = 0; c < 9; ++c) {
-        const int k = c / 3, x = c % 3;
-        D3 Pt[3];
+    const int g = lane / 9, c = lane - 9 * g;
+    double out = 0.0;
+    if (g < 7) {
+        // positions relative to the centroid of q
+        const V3<double> D = {m.cx[t] - m.cx[q], m.cy[t] - m.cy[q], m.cz[t] - m.cz[q]};
+        V3<double> Pq[3];
+        V3<Dual> Pt[3];
+#pragma unroll
         for (int i = 0; i < 3; ++i) {
-            Pt[i] = mk(pt[i][0], pt[i][1], pt[i][2]);
-            if (i == k) {
-                if (x == 0) Pt[i].x.d = 1.0;
-                else if (x == 1) Pt[i].y.d = 1.0;
-                else Pt[i].z.d = 1.0;
+            Pt[i] = {{D.x + m.vx[i * T + t], c == 3 * i ? 1.0 : 0.0},
+                     {D.y + m.vy[i * T + t], c == 3 * i + 1 ? 1.0 : 0.0},
+                     {D.z + m.vz[i * T + t], c == 3 * i + 2 ? 1.0 : 0.0}};
+            Pq[i] = {m.vx[i * T + q], m.vy[i * T + q], m.vz[i * T + q]};
+        }
+        // S_ij: imaginary part of both contractions' coefficients, without t's edge lengths
+        double S[3][3];
+        {
+            C aL[3], aJ[3];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                const double2 l = lam[m.te[i * T + t]], j = jv[m.te[i * T + t]];
+                const double s = m.cf[i * T + t] > 0.0 ? 1.0 : -1.0;
+                aL[i] = {s * l.x, s * l.y};
+                aJ[i] = {s * j.x, s * j.y};
+            }
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                const double2 l = lam[m.te[j * T + q]], v = jv[m.te[j * T + q]];
+                double w = nrm(sub(Pq[(j + 1) % 3], Pq[(j + 2) % 3]));
+                if (m.cf[j * T + q] < 0.0) w = -w;
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+                    S[i][j] = w * ((aL[i].r * v.y + aL[i].i * v.x) + (aJ[i].r * l.y + aJ[i].i * l.x));
             }
         }
-        const CD s1 = near_contract(Pt, Pq, st, sq, aL, bJ, kr, sc, rule, ht, hq);
-        const CD s2 = near_contract(Pt, Pq, st, sq, aJ, bL, kr, sc, rule, ht, hq);
-        atomicAdd(&acc[size_t(t) * 9 + c], -2.0 * (s1.r.d + s2.r.d));
+        // a_i = sum_j S_ij, v_i = sum_j S_ij Q_j; l_i the lengths of t's edges
+        double a[3];
+        V3<double> v[3];
+        Dual l[3], sum = {0, 0};
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            l[i] = nrm(sub(Pt[(i + 1) % 3], Pt[(i + 2) % 3]));
+            a[i] = S[i][0] + S[i][1] + S[i][2];
+            v[i] = add(add(scl(Pq[0], S[i][0]), scl(Pq[1], S[i][1])), scl(Pq[2], S[i][2]));
+            sum = sum + l[i] * a[i];
+        }
+        // point g: 1/3 of the vertices' sum and D1 or D2 of one vertex's offset from it
+        const double f = g == 0 ? 0.0 : (g < 4 ? Bary<7>::D1 : Bary<7>::D2), b0 = (1.0 - f) / 3.0;
+        const double wa = g == 0 ? Bary<7>::W0 : (g < 4 ? Bary<7>::W1 : Bary<7>::W2);
+        const int kv = g == 0 ? -1 : (g - 1) % 3;
+        double by[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) by[i] = b0 + (i == kv ? f : 0.0);
+        const V3<Dual> rt = add(add(scl(Pt[0], by[0]), scl(Pt[1], by[1])), scl(Pt[2], by[2]));
+        const V3<double> rq = add(add(scl(Pq[0], by[0]), scl(Pq[1], by[1])), scl(Pq[2], by[2]));
+        Dual z, I0;
+        V3<Dual> I1;
+        {   // t's point against q: sum_i l_i (r - P_i) . (a_i I1 - v_i I0)
+            V3<double> n = crs(sub(Pq[1], Pq[0]), sub(Pq[2], Pq[0]));
+            const double i2a = 1.0 / nrm(n);
+            n = scl(n, i2a);
+            potentials_d(rt, Pq, n, m.hm[q], t == q, I0, I1);
+            Dual uw = {0, 0};
+#pragma unroll
+            for (int i = 0; i < 3; ++i) uw = uw + l[i] * dot(sub(rt, Pt[i]), sub(scl(I1, a[i]), scl(v[i], I0)));
+            z = (uw * (0.25 * sc.ai) + I0 * sum * sc.pi) * i2a;
+        }
+        {   // q's point against t: sum_i l_i (I1 - P_i I0) . (a_i r - v_i)
+            V3<Dual> n = crs(sub(Pt[1], Pt[0]), sub(Pt[2], Pt[0]));
+            const Dual i2a = inverse(nrm(n));
+            n = scl(n, i2a);
+            potentials_d(rq, Pt, n, m.hm[t], t == q, I0, I1);
+            Dual uw = {0, 0};
+#pragma unroll
+            for (int i = 0; i < 3; ++i) uw = uw + l[i] * dot(sub(I1, scl(Pt[i], I0)), sub(scl(rq, a[i]), v[i]));
+            z = z + (uw * (0.25 * sc.ai) + I0 * sum * sc.pi) * i2a;
+        }
+        // -2 Re of j (j sc.. and the half of each side are in z's factors)
+        out = 2.0 * wa * z.d;
     }
+    const double u = __shfl_down(out, 36, 64);   // points 4, 5, 6 to 0, 1, 2
+    if (g < 3) out += u;
+    double v = __shfl_down(out, 18, 64);
+    const double w = __shfl_down(out, 9, 64), y = __shfl_down(out, 27, 64);
+    if (lane < 9) atomicAdd(&acc[size_t(t) * 9 + lane], (out + w) + (v + y));
 }
 
 // ------------------------------------------------ excitation and radiation terms
@@ -664,13 +641,13 @@ extern "C" int efie_vertex_grad(efie_mesh mesh, double k, double eta, const void
         EFIE_REQUIRE(size_t(m.T) * nqblk < (size_t(1) << 31), EFIE_ERR_ARG, "vertex_grad: mesh too large");
         const double tpairs = double(m.T) * double(m.T) - double(m.n_near);
         prof_begin(PROF_GRAD_FAR, stream);
-        hipLaunchKernelGGL(grad_far_kernel, dim3(unsigned(size_t(m.T) * nqblk)), dim3(256), 0, stream, m, k, sc, rule,
-                           lam, jv, acc, nqblk);
+        hipLaunchKernelGGL(grad_far_kernel, dim3(unsigned(size_t(m.T) * nqblk)), dim3(256), 0, stream, m, k, sc, lam,
+                           jv, acc, nqblk);
         prof_end(PROF_GRAD_FAR, stream, tpairs);
         if (m.n_near) {
             prof_begin(PROF_GRAD_NEAR, stream);
-            hipLaunchKernelGGL(grad_near_kernel, dim3((m.n_near + 127) / 128), dim3(128), 0, stream, m, k, sc, rule,
-                               lam, jv, acc);
+            hipLaunchKernelGGL(grad_near_kernel, dim3((m.n_near + 3) / 4), dim3(256), 0,
+                               stream, m, sc, lam, jv, acc);
             prof_end(PROF_GRAD_NEAR, stream, double(m.n_near));
         }
         prof_begin(PROF_GRAD_TRI, stream);

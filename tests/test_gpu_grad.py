@@ -80,6 +80,33 @@ def test_vertex_grad_terms(dev, level, k):
     assert max(e) <= 1e-10
 
 
+@pytest.mark.parametrize("n,axes,k", [(2, (1.0, 0.8, 0.6), 0.05), (4, (1.0, 0.5, 0.25), 9.0)])
+def test_operator_term_by_pair_class(dev, n, axes, k):
+    """The operator term for one lambda and one j: an edge with itself (point pairs at
+    R = 0), two edges of one triangle, and edges apart; 80 and 320 triangles (part of a
+    block of 256 sources, and one block and a part).
+
+    Tolerance: up to 1e4 summands of a pair's size, a few roundings each, and up to 1e2
+    of cancellation between them: 1e4 x 1e2 x 2^-53 = 1e-10."""
+    v, f = synth.ellipsoid(n, axes)
+    m = rwg.build(v, f)
+    kh, pol = synth.planewave_x_along_minus_z()
+    dirs = synth.uniform_directions(2, seed=1)
+    prob = ograd.Problem(m, k, kh[0], pol[0], dirs)
+    W = np.zeros((2, 2), dtype=np.complex128)
+    mesh = P.Mesh(v, f).upload(dev)
+    N = mesh.n
+    e = m.tri_edge[0]
+    for p, q in ((e[0], e[0]), (e[0], e[1]), (e[0], (int(e[0]) + N // 2) % N)):
+        lam, j = np.zeros(N, dtype=np.complex128), np.zeros(N, dtype=np.complex128)
+        lam[p], j[q] = 1.0 - 0.5j, 0.25 + 1.0j
+        _, exc, op = ograd.term_gradients(prob, v, j, lam, W)
+        g = P.vertex_grad(mesh, k, _c(j, dev), _c(lam, dev), _c(W, dev), prob.dirs, prob.khat, prob.pol)
+        err = _rel(g.cpu().numpy(), op + exc)
+        flush(f"operator term n={n} k={k} edges {p} {q}: rel error {err:.2e}")
+        assert err <= 1e-10
+
+
 @pytest.mark.parametrize("shape", [(1, 32, 2), (3, 700, 2)])
 def test_farfield_objective(dev, shape):
     """J = sum |F|^2 and W = conj(F) from the library against their definitions on
