@@ -265,6 +265,17 @@ int efie_zx(const void* Z, int dtype, int64_t n, const void* X, void* Y, int64_t
             hipStream_t stream);
 
 /*
+ * efie_zx with a workspace: where few tiles cover Y, the fp16 split product shares a
+ * tile among blocks that take a range of K each and adds their FP64 sums, kept in ws,
+ * in a fixed order.  efie_zx_workspace_size gives the bytes (at most 128 MiB; 0 where
+ * it would not help).  ws: dev scratch, 16-byte aligned; smaller than that, or null: the
+ * same as efie_zx.
+ */
+int efie_zx_workspace_size(int64_t n, int64_t nrhs, int dtype, size_t* bytes);
+int efie_zx_ws(const void* Z, int dtype, int64_t n, const void* X, void* Y, int64_t nrhs, void* ws,
+               size_t ws_bytes, hipStream_t stream);
+
+/*
  * The mixed solves' product as a call of its own: Y = Z X with Z complex64
  * (n x n) and X, Y complex128 (nrhs, n).  X is rounded to complex64 and
  * multiplied on the matrix cores (the default fp16 split product, or a selected FP32

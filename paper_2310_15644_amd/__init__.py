@@ -38,7 +38,7 @@ library_path = os.environ.get("EFIE_LIBRARY") or os.path.join(HERE, "libefie.so"
 EXPORTED = [
     "efie_abi_version", "efie_last_error", "efie_mesh_create", "efie_mesh_destroy", "efie_mesh_sizes",
     "efie_mesh_rwg_table", "efie_mesh_upload", "efie_mesh_set_far_rule", "efie_assemble", "efie_excite_planewave",
-    "efie_farfield_workspace_size", "efie_farfield", "efie_zx", "efie_solve_workspace_size", "efie_solve",
+    "efie_farfield_workspace_size", "efie_farfield", "efie_zx", "efie_zx_workspace_size", "efie_zx_ws", "efie_solve_workspace_size", "efie_solve",
     "efie_prof_enable", "efie_prof_reset", "efie_prof_read",
     "efie_gemm_variants", "efie_gemm_variant_info", "efie_gemm_autotune", "efie_gemm_select",
     "efie_zx_flush64_workspace_size", "efie_zx_flush64",
@@ -102,6 +102,8 @@ def lib():
         "efie_farfield_workspace_size": ([P, I64, ctypes.POINTER(ctypes.c_size_t)], ctypes.c_int),
         "efie_farfield": ([P, D, D, P, I64, P, I64, P, P, ctypes.c_size_t, P], ctypes.c_int),
         "efie_zx": ([P, ctypes.c_int, I64, P, P, I64, P], ctypes.c_int),
+        "efie_zx_workspace_size": ([I64, I64, ctypes.c_int, ctypes.POINTER(ctypes.c_size_t)], ctypes.c_int),
+        "efie_zx_ws": ([P, ctypes.c_int, I64, P, P, I64, P, ctypes.c_size_t, P], ctypes.c_int),
         "efie_zx_flush64_workspace_size": ([I64, I64, ctypes.POINTER(ctypes.c_size_t)], ctypes.c_int),
         "efie_zx_flush64": ([P, I64, P, P, I64, P, ctypes.c_size_t, P], ctypes.c_int),
         "efie_solve_workspace_size": ([I64, I64, ctypes.c_int, ctypes.POINTER(ctypes.c_size_t)], ctypes.c_int),
@@ -461,7 +463,12 @@ def zx(Z, X):
         raise ValueError("X must have the dtype of Z")
     _require_cuda(X, "X")
     Y = torch.empty_like(X)
-    _check(lib().efie_zx(_ptr(Z), code, Z.shape[0], _ptr(X), _ptr(Y), X.shape[0], _stream(Z.device)))
+    n, S = Z.shape[0], X.shape[0]
+    nb = ctypes.c_size_t()
+    _check(lib().efie_zx_workspace_size(n, S, code, ctypes.byref(nb)))
+    ws = torch.empty(nb.value, dtype=torch.uint8, device=Z.device) if nb.value else None
+    _check(lib().efie_zx_ws(_ptr(Z), code, n, _ptr(X), _ptr(Y), S, _ptr(ws) if nb.value else None, nb.value,
+                            _stream(Z.device)))
     return Y
 
 
@@ -543,7 +550,7 @@ def gemm_kernel_name(variant, acc64: bool) -> str:
     """The kernel's name as profilers print it (template arguments included)."""
     bm, bn, kc = variant[:3]
     if kc == 64:   # the fp16 split kernel, by its widest tile
-        return f"cgemm_split_kernel<{bm // 32}, {bn // 32}, 1, {kc}, {'true' if acc64 else 'false'}, 2>"
+        return f"cgemm_split_kernel<{bm // 32}, {bn // 32}, 1, {kc}, {int(acc64)}, 2>"
     return f"cgemm_planar_kernel<{bm}, {bn}, {kc}, {'true' if acc64 else 'false'}>"
 
 

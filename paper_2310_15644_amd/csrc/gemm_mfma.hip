@@ -302,8 +302,70 @@ template <int WM, int WN, int WK, int KC, bool A64, int MINW>
 static void launch_split(const void* X, const void* Z, void* Y, const int* yrow, int M, int n, hipStream_t s) {
     const size_t nblk = size_t((M + 32 * WM - 1) / (32 * WM)) * ((n + 32 * WN - 1) / (32 * WN));
     EFIE_REQUIRE(nblk < (size_t(1) << 31), EFIE_ERR_ARG, "cgemm: problem too large");
-    hipLaunchKernelGGL((cgemm_split_kernel<WM, WN, WK, KC, A64, MINW>), dim3(unsigned(nblk)), dim3(64 * WM * WN * WK), 0,
-                       s, static_cast<const float2*>(X), static_cast<const float2*>(Z), Y, M, n, yrow);
+    hipLaunchKernelGGL((cgemm_split_kernel<WM, WN, WK, KC, A64 ? OUT_C128 : OUT_C64, MINW>), dim3(unsigned(nblk)),
+                       dim3(64 * WM * WN * WK), 0, s, static_cast<const float2*>(X), static_cast<const float2*>(Z), Y, M,
+                       n, yrow, 1);
+}
+
+// Several blocks per tile, each on a range of K, where the caller has a workspace for
+// their partial sums: with 17 to 512 tiles of the in-block split one block per CU, or
+// none, is left waiting on its own loads.  The number of ranges is the one that takes
+// least by a model of the measured times: a chunk takes full us while two blocks share
+// a CU (slots = 512 blocks), last us while at most one is left on each, a partial tile
+// tile us to write and to add.  Within 12 % of the times from n = 1920 up; in us,
+// in-block / ranges:
+//   n = 4317,  M = 45:  109 /  52 (7 ranges)    n = 1920, M = 100:  39 /  27 (8)
+//   n = 7680,  M = 64:  230 / 148 (4)           n =  960, M =  64:  22 /  15 (8)
+//   n = 12000, M = 20:  345 / 238 (5)           n =  480, M =  64:  14 /  11 (8)
+//   n = 12000, M = 200: 1230 / 1134 (2)         n = 30720, M = 512: one range
+struct RangePlan {
+    int kind = 0, ranges = 1;
+    size_t bytes = 0;   // workspace; 0: in-block
+};
+constexpr size_t RANGE_WS_MAX = size_t(128) << 20;
+
+static RangePlan range_plan(int M, int n) {
+    // kinds: 64 x 64 tiles; for at most 32 right-hand sides 32 x 128 tiles, and 32 x 32
+    // with two K groups (chunks of 128 then) where those would be too few
+    struct Kind {
+        int bm, bn, kc;
+        double full, last;
+    };
+    static constexpr Kind kinds[] = {{64, 64, 64, 4.0, 3.0}, {32, 128, 32, 2.9, 1.9}, {32, 32, 128, 4.0, 3.0}};
+    RangePlan best;
+    best.kind = M > 32 ? 0 : (n > 2048 ? 1 : 2);
+    const Kind& k = kinds[best.kind];
+    const int64_t tiles = ((int64_t(M) + k.bm - 1) / k.bm) * ((int64_t(n) + k.bn - 1) / k.bn);
+    const int64_t chunks = (int64_t(n) + k.kc - 1) / k.kc;
+    const size_t tile_bytes = size_t(k.bm) * size_t(k.bn) * 16;
+    double least = 1e300;
+    for (int64_t r = 1; r <= std::min<int64_t>(32, chunks); ++r) {
+        const size_t bytes = r > 1 ? size_t(tiles * r) * tile_bytes : 0;
+        if (bytes > RANGE_WS_MAX) break;
+        const int64_t blocks = tiles * r, rest = blocks % 512;
+        const double rounds = double(blocks / 512) * k.full + (rest == 0 ? 0.0 : rest <= 256 ? k.last : k.full);
+        // and half a microsecond a range in the sum's own chain
+        const double t = double((chunks + r - 1) / r) * rounds + double(bytes) / 2.4e6 + 0.5 * double(r);
+        if (t < least) {
+            least = t;
+            best.ranges = int(r);
+            best.bytes = bytes;
+        }
+    }
+    return best;
+}
+
+size_t cgemm_ranges_bytes(int M, int n) { return range_plan(M, n).bytes; }
+
+template <int WM, int WN, int WK, int KC, bool A64, int MINW>
+static void launch_ranges(const void* X, const void* Z, void* Y, const int* yrow, int M, int n, int ranges, void* ws,
+                          hipStream_t s) {
+    const int ntile = ((M + 32 * WM - 1) / (32 * WM)) * ((n + 32 * WN - 1) / (32 * WN));
+    hipLaunchKernelGGL((cgemm_split_kernel<WM, WN, WK, KC, OUT_PART, MINW>), dim3(unsigned(ntile) * unsigned(ranges)),
+                       dim3(64 * WM * WN * WK), 0, s, static_cast<const float2*>(X), static_cast<const float2*>(Z), ws, M,
+                       n, nullptr, ranges);
+    hipLaunchKernelGGL((split_sum_kernel<WM, WN, A64>), dim3(unsigned(ntile) * (4 * WM * WN)), dim3(256), 0, s,
+                       static_cast<const double2*>(ws), Y, M, n, yrow, ntile, ranges);
 }
 
 // The tile of the split kernel by the number of blocks (256 CUs; times in us with
@@ -328,6 +390,21 @@ static void launch_split_rule(const void* X, const void* Z, void* Y, const int* 
         launch_split<2, 2, 1, 64, A64, 2>(X, Z, Y, yrow, M, n, s);
 }
 
+// the split product, over several ranges of K where ws holds their partial sums
+template <bool A64>
+static void launch_split_ws(const void* X, const void* Z, void* Y, const int* yrow, int M, int n, void* ws,
+                            size_t ws_bytes, hipStream_t s) {
+    const RangePlan p = range_plan(M, n);
+    if (p.bytes == 0 || p.bytes > ws_bytes)
+        launch_split_rule<A64>(X, Z, Y, yrow, M, n, s);
+    else if (p.kind == 0)
+        launch_ranges<2, 2, 1, 64, A64, 2>(X, Z, Y, yrow, M, n, p.ranges, ws, s);
+    else if (p.kind == 1)
+        launch_ranges<1, 4, 1, 32, A64, 2>(X, Z, Y, yrow, M, n, p.ranges, ws, s);
+    else
+        launch_ranges<1, 1, 2, 64, A64, 2>(X, Z, Y, yrow, M, n, p.ranges, ws, s);
+}
+
 template <bool A64>
 static void launch_variant(int v, const void* X, const void* Z, void* Y, const int* yrow, int M, int mcap, int n,
                            hipStream_t s) {
@@ -349,19 +426,26 @@ static void launch_variant(int v, const void* X, const void* Z, void* Y, const i
 constexpr int kSmallVariant = 4;
 static_assert(kVariants[kSmallVariant].bm == 32, "the small-M tile has 32 rows");
 
-void cgemm_mfma(const void* X, const void* Z, void* Y, int M, int n, hipStream_t s, int mcap) {
+void cgemm_mfma(const void* X, const void* Z, void* Y, int M, int n, hipStream_t s, int mcap, void* ws,
+                size_t ws_bytes) {
     prof_begin(PROF_MFMA, s);
-    launch_variant<false>(g_variant[0], X, Z, Y, nullptr, M, std::max(M, mcap), n, s);
+    if (g_variant[0] == kSplitVariant)
+        launch_split_ws<false>(X, Z, Y, nullptr, M, n, ws, ws_bytes, s);
+    else
+        launch_variant<false>(g_variant[0], X, Z, Y, nullptr, M, std::max(M, mcap), n, s);
     prof_end(PROF_MFMA, s, 8.0 * M * double(n) * n);
 }
 
 void cgemm_mfma_acc64(const void* X, const void* Z, double2* Y, const int* yrow, int M, int n, hipStream_t s,
-                      int mcap, bool small_tile) {
+                      int mcap, bool small_tile, void* ws, size_t ws_bytes) {
     const bool small = small_tile && M <= kVariants[kSmallVariant].bm;
     const int v = small && g_variant[1] != kSplitVariant ? kSmallVariant : g_variant[1];
     const ProfId id = small ? PROF_MFMA_SMALL : PROF_MFMA;   // timed apart from the selected tile
     prof_begin(id, s);
-    launch_variant<true>(v, X, Z, Y, yrow, M, std::max(M, mcap), n, s);
+    if (v == kSplitVariant)
+        launch_split_ws<true>(X, Z, Y, yrow, M, n, ws, ws_bytes, s);
+    else
+        launch_variant<true>(v, X, Z, Y, yrow, M, std::max(M, mcap), n, s);
     prof_end(id, s, 8.0 * M * double(n) * n);
 }
 
@@ -369,11 +453,12 @@ __global__ void iota_rows_kernel(int* idx, int M) {
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < M; i += gridDim.x * blockDim.x) idx[i] = i;
 }
 
-void zx_product(const void* Z, int zdt, int n, const void* X, int xdt, void* Y, int nrhs, hipStream_t s) {
+void zx_product(const void* Z, int zdt, int n, const void* X, int xdt, void* Y, int nrhs, hipStream_t s, void* ws,
+                size_t ws_bytes) {
     if (nrhs == 1) {
         gemv(Z, zdt, n, X, xdt, Y, xdt, s);
     } else if (zdt == EFIE_C64 && xdt == EFIE_C64) {
-        cgemm_mfma(X, Z, Y, nrhs, n, s);
+        cgemm_mfma(X, Z, Y, nrhs, n, s, 0, ws, ws_bytes);
     } else {
         zgemm_nt(X, xdt, Z, zdt, Y, xdt, nrhs, n, n, n, n, n, 1.0, 0.0, false, s);
     }
@@ -488,6 +573,29 @@ extern "C" int efie_zx(const void* Z, int dtype, int64_t n, const void* X, void*
         EFIE_REQUIRE(dtype == EFIE_C128 || dtype == EFIE_C64, EFIE_ERR_ARG, "zx: bad dtype");
         EFIE_REQUIRE(n >= 1 && n < (int64_t(1) << 31) && nrhs >= 1 && nrhs < 65536, EFIE_ERR_ARG, "zx: bad sizes");
         efie::zx_product(Z, dtype, int(n), X, dtype, Y, int(nrhs), stream);
+        EFIE_HIP_CHECK(hipGetLastError());
+        return int(EFIE_OK);
+    });
+}
+
+extern "C" int efie_zx_workspace_size(int64_t n, int64_t nrhs, int dtype, size_t* bytes) {
+    return efie::guarded([&]() {
+        EFIE_REQUIRE(bytes && n >= 1 && n < (int64_t(1) << 31) && nrhs >= 1 && nrhs < 65536, EFIE_ERR_ARG,
+                     "zx_workspace_size: bad argument");
+        EFIE_REQUIRE(dtype == EFIE_C128 || dtype == EFIE_C64, EFIE_ERR_ARG, "zx_workspace_size: bad dtype");
+        *bytes = dtype == EFIE_C64 && nrhs > 1 ? efie::cgemm_ranges_bytes(int(nrhs), int(n)) : 0;
+        return int(EFIE_OK);
+    });
+}
+
+extern "C" int efie_zx_ws(const void* Z, int dtype, int64_t n, const void* X, void* Y, int64_t nrhs, void* ws,
+                          size_t ws_bytes, hipStream_t stream) {
+    return efie::guarded([&]() {
+        EFIE_REQUIRE(Z && X && Y, EFIE_ERR_ARG, "zx_ws: null argument");
+        EFIE_REQUIRE(dtype == EFIE_C128 || dtype == EFIE_C64, EFIE_ERR_ARG, "zx_ws: bad dtype");
+        EFIE_REQUIRE(n >= 1 && n < (int64_t(1) << 31) && nrhs >= 1 && nrhs < 65536, EFIE_ERR_ARG, "zx_ws: bad sizes");
+        EFIE_REQUIRE((reinterpret_cast<uintptr_t>(ws) & 15) == 0, EFIE_ERR_ARG, "zx_ws: ws not 16-byte aligned");
+        efie::zx_product(Z, dtype, int(n), X, dtype, Y, int(nrhs), stream, ws, ws ? ws_bytes : 0);
         EFIE_HIP_CHECK(hipGetLastError());
         return int(EFIE_OK);
     });

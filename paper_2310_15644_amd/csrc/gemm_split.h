@@ -65,14 +65,18 @@ __device__ __forceinline__ void split2(float a, float b, float sc, halfx2& h, ha
     l = __builtin_convertvector(floatx2{__builtin_fmaf(a, sc, -float(h.x)), __builtin_fmaf(b, sc, -float(h.y))}, halfx2);
 }
 
+// where the sums of a tile go: complex64 Y, the rows yrow of complex128 Y, or (a block
+// of one of several ranges of K) the workspace that split_sum_kernel adds up
+enum SplitOut { OUT_C64, OUT_C128, OUT_PART };
+
 // Block: WK groups of WM x WN waves; a wave owns a 32 x 32 tile of complex outputs
 // (rows: right-hand sides, columns: unknowns), the groups share the block's tile and
-// take the K chunks in turn.
-template <int WM, int WN, int WK, int KC, bool OUT64, int MINW>
+// take the K chunks of the block's range in turn.
+template <int WM, int WN, int WK, int KC, int OUT, int MINW>
 __global__ __launch_bounds__(64 * WM * WN * WK, MINW) void cgemm_split_kernel(const float2* __restrict__ X,
                                                                               const float2* __restrict__ Z,
                                                                               void* __restrict__ Yv, int M, int n,
-                                                                              const int* __restrict__ yrow) {
+                                                                              const int* __restrict__ yrow, int ranges) {
     constexpr int GT = 64 * WM * WN;                  // threads of a group
     constexpr int BM = 32 * WM, BN = 32 * WN;
     constexpr int RS = KC + 8;                        // fp16 per LDS row
@@ -94,7 +98,11 @@ __global__ __launch_bounds__(64 * WM * WN * WK, MINW) void cgemm_split_kernel(co
     const int xcd = int(blockIdx.x) & 7, idx = int(blockIdx.x) >> 3;
     const int per = nblk >> 3, rem = nblk & 7;
     const int logical = xcd * per + min(xcd, rem) + idx;
-    const int bm = logical % nbm, bn = logical / nbm;
+    // the tile, rows of right-hand sides fastest, and the range of K
+    const int ntile = nblk / ranges;
+    const int range = OUT == OUT_PART ? logical / ntile : 0;
+    const int tile = logical - range * ntile;
+    const int bm = tile % nbm, bn = tile / nbm;
     const int s0 = bm * BM, i0 = bn * BN;
     _Float16* Xs = reinterpret_cast<_Float16*>(lds + g * STAGE);
     _Float16* Zs = Xs + 4 * BM * RS;
@@ -215,11 +223,13 @@ __global__ __launch_bounds__(64 * WM * WN * WK, MINW) void cgemm_split_kernel(co
             }
         }
     };
-    const int nch = (n + KC - 1) / KC;
-    const int turns = (nch + WK - 1) / WK;
-    if (g < nch) gload(g);
+    const int all = (n + KC - 1) / KC;
+    const int c0 = OUT == OUT_PART ? int(int64_t(all) * range / ranges) : 0;
+    const int nch = OUT == OUT_PART ? int(int64_t(all) * (range + 1) / ranges) : all;
+    const int turns = (nch - c0 + WK - 1) / WK;
+    if (c0 + g < nch) gload(c0 + g);
     for (int i = 0; i < turns; ++i) {
-        const int c = g + WK * i;
+        const int c = c0 + g + WK * i;
         __syncthreads();
         if (c < nch) lstore();
         __syncthreads();
@@ -245,6 +255,12 @@ __global__ __launch_bounds__(64 * WM * WN * WK, MINW) void cgemm_split_kernel(co
                 di[r] += v.y;
             }
     }
+    if constexpr (OUT == OUT_PART) {
+        double2* part = static_cast<double2*>(Yv) + size_t(logical) * (16 * GT) + tid;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) part[r * GT] = make_double2(dr[r], di[r]);
+        return;
+    }
     // D of the 32x32x16 instruction: lane l holds column l % 32, rows 8 (r / 4) + 4 (l / 32) + r % 4
     const int col = i0 + wn * 32 + l32;
     if (col >= n) return;
@@ -252,11 +268,45 @@ __global__ __launch_bounds__(64 * WM * WN * WK, MINW) void cgemm_split_kernel(co
     for (int r = 0; r < 16; ++r) {
         const int row = s0 + wm * 32 + 8 * (r >> 2) + 4 * kh + (r & 3);
         if (row >= M) continue;
-        if constexpr (OUT64)
+        if constexpr (OUT == OUT_C128)
             reinterpret_cast<double2*>(Yv)[size_t(yrow[row]) * n + col] = make_double2(dr[r], di[r]);
         else
             reinterpret_cast<float2*>(Yv)[size_t(row) * n + col] = make_float2(float(dr[r]), float(di[r]));
     }
+}
+
+// Y = the sum over the ranges of K, in order, of the partial tiles of
+// cgemm_split_kernel<WM, WN, 1, KC, OUT_PART>: a thread per output, a block per 256
+// outputs of a tile (one register index of the tile's threads, or several)
+template <int WM, int WN, bool OUT64>
+__global__ __launch_bounds__(256) void split_sum_kernel(const double2* __restrict__ part, void* __restrict__ Yv, int M,
+                                                        int n, const int* __restrict__ yrow, int ntile, int ranges) {
+    constexpr int GT = 64 * WM * WN, TS = 16 * GT;
+    const int tile = int(blockIdx.x) / (TS / 256);
+    const int e = (int(blockIdx.x) % (TS / 256)) * 256 + int(threadIdx.x);
+    const int r = e / GT, tid = e % GT, lane = tid & 63, w = tid >> 6;
+    const int nbm = (M + 32 * WM - 1) / (32 * WM);
+    const int row = (tile % nbm) * 32 * WM + (w / WN) * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+    const int col = (tile / nbm) * 32 * WN + (w % WN) * 32 + (lane & 31);
+    if (row >= M || col >= n) return;
+    double2 a = make_double2(0.0, 0.0);
+    const double2* p = part + size_t(tile) * TS + e;
+    const size_t step = size_t(ntile) * TS;
+    for (int k = 0; k < ranges; k += 8) {   // eight loads in flight
+        double2 v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = p[size_t(min(k + q, ranges - 1)) * step];
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (k + q < ranges) {
+                a.x += v[q].x;
+                a.y += v[q].y;
+            }
+    }
+    if constexpr (OUT64)
+        static_cast<double2*>(Yv)[size_t(yrow[row]) * n + col] = a;
+    else
+        static_cast<float2*>(Yv)[size_t(row) * n + col] = make_float2(float(a.x), float(a.y));
 }
 
 }  // namespace efie

@@ -549,6 +549,8 @@ struct Ws {
     double2 *res, *dlt;                     // outer refinement (CGS, mixed): residual and correction
     float2* x32;                            // complex64 staging of the product input
     int x32_rows;                           // its rows (S rounded up to 128)
+    void* ranges;                           // partial sums of the complex64 product (cgemm_ranges_bytes)
+    size_t ranges_bytes;
     float2* y32;                            // complex64 product output (FP32 accumulation)
     bool acc64;                             // FP64 flush of the matrix-core partial sums
     double2* part;                          // partial sums of the K-split product of <= 8 columns
@@ -584,6 +586,13 @@ size_t layout(int64_t n, int64_t S, int dtype, Ws* ws, char* base) {
     w.res = (double2*)take(outer); w.dlt = (double2*)take(outer);
     w.x32 = (float2*)take(vec32);
     w.y32 = (float2*)take(vec32);
+    // the largest of the column counts that take the matrix cores (the tiles change
+    // with every 32 columns; one count of each)
+    w.ranges_bytes = 0;
+    if (vec32)
+        for (int64_t m = std::min<int64_t>(S, 32); m <= S; m = m == S ? S + 1 : std::min(S, m + 32))
+            w.ranges_bytes = std::max(w.ranges_bytes, cgemm_ranges_bytes(int(std::min<int64_t>(m, 65535)), int(n)));
+    w.ranges = take(w.ranges_bytes);
     w.part = (double2*)take(gemv_multi_part_bytes(int(n)));
     w.cols = (Col*)take(sizeof(Col) * size_t(S));
     w.nrm = (double*)take(sizeof(double) * size_t(S));
@@ -610,9 +619,9 @@ void product(const void* Z, int zdt, int n, const double2* X, double2* Y, const 
     } else if (zdt == EFIE_C64 && !exact64) {
         gather_cast(X, idx, m, n, w.x32, st);
         if (w.acc64) {
-            cgemm_mfma_acc64(w.x32, Z, Y, idx, m, n, st, w.x32_rows, true);
+            cgemm_mfma_acc64(w.x32, Z, Y, idx, m, n, st, w.x32_rows, true, w.ranges, w.ranges_bytes);
         } else {
-            cgemm_mfma(w.x32, Z, w.y32, m, n, st, w.x32_rows);
+            cgemm_mfma(w.x32, Z, w.y32, m, n, st, w.x32_rows, w.ranges, w.ranges_bytes);
             scatter_cast(w.y32, idx, m, n, Y, st);
         }
     } else {

@@ -27,14 +27,18 @@ void scatter_cast(const float2* in, const int* idx, int m, int n, double2* Y, hi
 
 // Y (M x n, complex64) = X (M x n, complex64) * Z^T (Z n x n complex64) on FP32 matrix cores.
 // mcap: rows of X that may be read (>= M; the rows past M are computed and dropped).
-void cgemm_mfma(const void* X, const void* Z, void* Y, int M, int n, hipStream_t s, int mcap = 0);
+// ws: for the split product, partial sums of several ranges of K (16-byte aligned; used
+// if it holds cgemm_ranges_bytes(M, n) bytes, which are 0 where one range is best).
+void cgemm_mfma(const void* X, const void* Z, void* Y, int M, int n, hipStream_t s, int mcap = 0, void* ws = nullptr,
+                size_t ws_bytes = 0);
+size_t cgemm_ranges_bytes(int M, int n);
 bool cgemm_mfma_supported(int M, int n);
 // Y[yrow[r]] (complex128) = sum_j X[r][j] Z[i][j]: same product with the FP32 matrix-core
 // partial sums flushed into FP64 accumulators every two K chunks.  mcap: rows of X
 // that may be read (>= M; the rows past M are computed and dropped); small_tile:
 // M <= 32 takes the 32-row tile instead of the selected one.
 void cgemm_mfma_acc64(const void* X, const void* Z, double2* Y, const int* yrow, int M, int n, hipStream_t s,
-                      int mcap = 0, bool small_tile = false);
+                      int mcap = 0, bool small_tile = false, void* ws = nullptr, size_t ws_bytes = 0);
 
 void cast_c128_to_c64(const void* a, void* b, size_t n, hipStream_t s);
 void cast_c64_to_c128(const void* a, void* b, size_t n, hipStream_t s);
@@ -43,6 +47,7 @@ void fill_zero_bytes(void* p, size_t bytes, hipStream_t s);
 
 // Y = Z X with the library's product choice (GEMV for one right-hand side,
 // matrix cores for complex64, FP64 GEMM for complex128).  X, Y of dtype xdt.
-void zx_product(const void* Z, int zdt, int n, const void* X, int xdt, void* Y, int nrhs, hipStream_t s);
+void zx_product(const void* Z, int zdt, int n, const void* X, int xdt, void* Y, int nrhs, hipStream_t s,
+                void* ws = nullptr, size_t ws_bytes = 0);
 
 }  // namespace efie

@@ -4,6 +4,8 @@ Tolerance: both operands are within 2^-23 of the stored values in each part and 
 sum |z| |x| 2^-21 bounds the error of a complex output before the FP32 sums of at most 64 terms, whose roundings (three
 products of sixteen terms each, 12 per 64 terms and part) add less than 2^-20 of it: 3e-6 of sum |z| |x|.
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -47,6 +49,31 @@ def test_split_tiles(split, n, m):
     bound = Xd.abs() @ Zd.abs().T.contiguous()
     for Y in (P.zx(Z, X).to(torch.complex128), P.zx_flush64(Z, Xd)):
         assert float(((Y - ref).abs() / bound).max()) <= 3e-6
+
+
+# ranges of K: one chunk more than one, tails of a chunk, the three tiles on both sides of their lines (32 right-hand
+# sides, order 2048), rows of Y past 64 and 128
+@pytest.mark.parametrize("n,m", [(65, 33), (129, 2), (129, 64), (191, 129), (2048, 32), (2049, 32), (2050, 33), (4317, 45)])
+def test_split_ranges(split, n, m):
+    flush(f"split product over ranges of K n={n} nrhs={m}")
+    nb = ctypes.c_size_t()
+    assert P.lib().efie_zx_workspace_size(n, m, P.C64, ctypes.byref(nb)) == 0 and nb.value > 0
+    Z, X = operands(n, m, 17 * n + m, 8.0)
+    Zd, Xd = Z.to(torch.complex128), X.to(torch.complex128)
+    bound = Xd.abs() @ Zd.abs().T.contiguous()
+    Y = P.zx(Z, X)
+    assert float(((Y.to(torch.complex128) - Xd @ Zd.T.contiguous()).abs() / bound).max()) <= 3e-6
+    assert torch.equal(torch.view_as_real(Y), torch.view_as_real(P.zx(Z, X)))   # a fixed order of the sums
+    # a workspace one byte short: the product of the call without one
+    ptr = [ctypes.c_void_p(t.data_ptr()) for t in (Z, X)]
+    ws, outs = torch.empty(nb.value, dtype=torch.uint8, device="cuda"), []
+    for w, b in ((None, 0), (ctypes.c_void_p(ws.data_ptr()), nb.value - 1)):
+        outs.append(torch.empty_like(X))
+        assert P.lib().efie_zx_ws(ptr[0], P.C64, n, ptr[1], ctypes.c_void_p(outs[-1].data_ptr()), m, w, b, None) == 0
+    outs.append(torch.empty_like(X))
+    assert P.lib().efie_zx(ptr[0], P.C64, n, ptr[1], ctypes.c_void_p(outs[-1].data_ptr()), m, None) == 0
+    torch.cuda.synchronize()
+    assert all(torch.equal(torch.view_as_real(o), torch.view_as_real(outs[0])) for o in outs[1:])
 
 
 def test_split_special_values(split):
