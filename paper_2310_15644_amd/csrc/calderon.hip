@@ -11,9 +11,10 @@
 //                                (one block per BC row m touched by the chunk, from
 //                                host-built lists; no atomics);
 //   P = T_BC G_mix^{-1}       row s of P solves G_mix^T p_s = row s of T_BC = column s
-//       (T_BC is symmetric), by BiCGStab for a batch of columns at once in column
-//       layout X[j][s], so that every sparse product reads rows of the batch
-//       coalesced; the solution block is then transposed into P.
+//       (T_BC is symmetric), by a Chebyshev iteration, or BiCGStab where its
+//       spectral interval, the tolerance or maxit rule that out, for a batch of
+//       columns at once in column layout X[j][s], so that every sparse product
+//       reads rows of the batch coalesced; the solution block is then transposed into P.
 // The preconditioned operator P Z is applied as two dense products.
 #include <hip/hip_runtime.h>
 
@@ -45,6 +46,7 @@ struct DevCald {
     const int32_t* run_t0;          // runs of BC functions: first position in n_order
     const int32_t *u_ptr, *u_idx;   // per run: its distinct barycentric RWGs
     const int32_t* r_loc;           // per entry of R's CSC: local position in its run's list
+    const double* g_dinv;           // 1 / diagonal of G (and of G^T), in n_order order
 };
 
 // Yw[row][n] = sum_k (W[row][f][0] + W[row][f][1]) r_val[k], f = r_idx[k], k over
@@ -270,13 +272,14 @@ __device__ inline CgBlock cg_block(int N) {
 __device__ inline size_t cg_at(int tile, int j, int c, int N) { return (size_t(tile) * N + j) * CG_W + c; }
 
 // part[slice][s] = the block's sum over its waves of sq (a column's squared norm
-// over the slice), for s < S
-__device__ inline void cg_part(double sq, const CgBlock& k, int S, double* part) {
+// over the slice), for s < S; ps columns in a row of part
+__device__ inline void cg_part(double sq, const CgBlock& k, int S, double* part, int ps) {
     __shared__ double sh[4][CG_W];
     sh[k.wv][k.c] = sq;
     __syncthreads();
-    if (k.wv == 0 && k.s < S) part[size_t(k.slice) * S + k.s] = sh[0][k.c] + sh[1][k.c] + sh[2][k.c] + sh[3][k.c];
+    if (k.wv == 0 && k.s < S) part[size_t(k.slice) * ps + k.s] = sh[0][k.c] + sh[1][k.c] + sh[2][k.c] + sh[3][k.c];
 }
+__device__ inline void cg_part(double sq, const CgBlock& k, int S, double* part) { cg_part(sq, k, S, part, S); }
 
 // ar + j ai += sum of val[e] Xt[idx[e] CG_W] over e = kb .. min(kb + G, ke) - 1
 // (indices past ke repeat the last entry with weight 0)
@@ -518,6 +521,79 @@ __global__ __launch_bounds__(256) void bicg_p_kernel(V* __restrict__ p, const V*
         const double ux = pp.x - (wr * vv.x - wi * vv.y), uy = pp.y - (wr * vv.y + wi * vv.x);
         p[e] = st2<V>(rr.x + (br * ux - bi * uy), rr.y + (br * uy + bi * ux));
     }
+}
+
+// ------------------------------------------------- Chebyshev iteration
+// The Gram matrices scaled by their diagonals D are close to symmetric with their
+// spectrum in a short interval [lo, hi] of the positive axis, so the three-term Chebyshev
+// iteration (Golub and Varga, Numer. Math. 3, 1961) needs no inner products: a step
+// gathers x_k, reads b and x_(k-1) and writes x_(k+1) over x_(k-1), four passes over
+// a vector and one launch, where a BiCGStab step makes nineteen passes with eleven
+// launches and a host read for two sparse products.  The interval comes from a short
+// Lanczos run on the host beside the T_BC kernels; the last step returns |b - A x_k|,
+// which decides (cheb_solve).
+// N = 7680, tol 1e-13: 88 ms with BiCGStab (18 steps), 29 ms now (24 steps, bound
+// by the gathers: 2.5 of the 7 TB/s of their streams).
+
+// x1 = gamma D^-1 b; part = slice sums of |b|^2 (row stride ps).  X points at the first
+// tile and b, part at the first column of the S columns
+template <typename V>
+__global__ __launch_bounds__(256) void cheb_init_kernel(const double2* __restrict__ b, int ldb, V* __restrict__ X,
+                                                        const int32_t* __restrict__ order,
+                                                        const double* __restrict__ dinv, double gamma, int N, int S,
+                                                        double* __restrict__ part, int ps) {
+    const CgBlock k = cg_block(N);
+    if (k.tile * CG_W >= S) return;
+    double sq = 0.0;
+    for (int t = k.j0; t < k.j1; t += 4) {
+        const int j = order[t];
+        const double2 v = k.s < S ? b[size_t(j) * ldb + k.s] : make_double2(0.0, 0.0);
+        const double g = gamma * dinv[t];
+        X[cg_at(k.tile, j, k.c, N)] = st2<V>(g * v.x, g * v.y);
+        sq += v.x * v.x + v.y * v.y;
+    }
+    cg_part(sq, k, S, part, ps);
+}
+
+// Xp = x_(k+1) = x_(k-1) + omega (gamma D^-1 (b - A x_k) + x_k - x_(k-1)), X = x_k,
+// Xp = x_(k-1) on entry (first: x_0 = 0 instead); RES: part = slice sums of |b - A x_k|^2
+template <typename V, bool RES>
+__global__ __launch_bounds__(256) void cheb_step_kernel(const int32_t* __restrict__ ptr,
+                                                        const int32_t* __restrict__ idx,
+                                                        const double* __restrict__ val,
+                                                        const int32_t* __restrict__ order,
+                                                        const double* __restrict__ dinv, const double2* __restrict__ b,
+                                                        int ldb, const V* __restrict__ X, V* __restrict__ Xp,
+                                                        double omega, double gamma, int first, int N, int S,
+                                                        double* __restrict__ part, int ps) {
+    const CgBlock k = cg_block(N);
+    if (k.tile * CG_W >= S) return;
+    const V* Xt = X + cg_at(k.tile, 0, k.c, N);
+    double sq = 0.0;
+    for (int t = k.j0; t < k.j1; t += 4) {
+        const int j = order[t];
+        const size_t e = cg_at(k.tile, j, k.c, N);
+        const double2 bv = k.s < S ? b[size_t(j) * ldb + k.s] : make_double2(0.0, 0.0);
+        const double2 xk = ld2(X[e]), xp = first ? make_double2(0.0, 0.0) : ld2(Xp[e]);
+        double ar = 0, ai = 0;
+        int kb = ptr[t];
+        const int ke = ptr[t + 1];
+        for (; kb + 8 <= ke; kb += 8) csp_group<8>(idx, val, Xt, kb, ke, ar, ai);
+        for (; kb < ke; kb += 4) csp_group<4>(idx, val, Xt, kb, ke, ar, ai);
+        const double rr = bv.x - ar, ri = bv.y - ai, g = gamma * dinv[t];
+        Xp[e] = st2<V>(xp.x + omega * (g * rr + xk.x - xp.x), xp.y + omega * (g * ri + xk.y - xp.y));
+        if (RES) sq += rr * rr + ri * ri;
+    }
+    if (RES) cg_part(sq, k, S, part, ps);
+}
+
+// cols[s].rn2 from red (|b - A x|^2); nactive counts the columns above their target
+// (a NaN among them)
+__global__ void cheb_check_kernel(BicgCol* cols, const double* red, int S, int* nactive) {
+    const int s = blockIdx.x * blockDim.x + threadIdx.x;
+    if (s >= S) return;
+    cols[s].rn2 = red[s];
+    if (!(red[s] <= cols[s].tol2)) atomicAdd(nactive, 1);
 }
 
 // P[s0 + s][j] = w[j][s] for s < S, 32 x 32 tiles through LDS; grid (ceil(N / 32),
@@ -818,6 +894,7 @@ DevCald dev_cald(const efie_calderon_s& C) {
     d.u_ptr = reinterpret_cast<const int32_t*>(b + o[11]);
     d.u_idx = reinterpret_cast<const int32_t*>(b + o[12]);
     d.r_loc = reinterpret_cast<const int32_t*>(b + o[13]);
+    d.g_dinv = reinterpret_cast<const double*>(b + o[14]);
     return d;
 }
 
@@ -830,12 +907,186 @@ size_t put(std::vector<char>& blob, std::vector<size_t>& offs, const std::vector
     return off;
 }
 
-// BiCGStab on A Y = B for the columns of B (N x N, row-major) in batches of pl.Sb
+// 1 / diagonal of G in n_order order (0 where an entry is missing or zero)
+std::vector<double> gram_inverse_diagonal(const efie_calderon_s& C) {
+    std::vector<double> v(size_t(C.N), 0.0);
+    for (size_t t = 0; t < v.size(); ++t) {
+        const size_t j = size_t(C.n_order[t]);
+        for (int32_t q = C.g_ptr[j]; q < C.g_ptr[j + 1]; ++q)
+            if (size_t(C.g_idx[size_t(q)]) == j && C.g_val[size_t(q)] != 0.0) v[t] = 1.0 / C.g_val[size_t(q)];
+    }
+    return v;
+}
+
+// An interval that holds the real parts of the spectrum of D^-1 G (and of D^-1 G^T):
+// the extreme Ritz values of the symmetric part of D^-1/2 G D^-1/2 after 20 Lanczos
+// steps, widened by 2 and 1 % (values that still lie outside only converge slower).
+// lo = 0: no positive interval.
+struct GramBounds {
+    double lo = 0.0, hi = 0.0;
+};
+
+GramBounds gram_bounds(const efie_calderon_s& C) {
+    const size_t N = size_t(C.N);
+    std::vector<double> s(N, 0.0), v(N), u(N, 0.0), y(N), x(N);
+    for (size_t j = 0; j < N; ++j)
+        for (int32_t q = C.g_ptr[j]; q < C.g_ptr[j + 1]; ++q)
+            if (size_t(C.g_idx[size_t(q)]) == j) s[j] = C.g_val[size_t(q)];
+    GramBounds out;
+    for (size_t j = 0; j < N; ++j) {
+        if (!(s[j] > 0.0)) return out;
+        s[j] = 1.0 / std::sqrt(s[j]);
+    }
+    uint32_t seed = 12345u;
+    double nrm = 0.0;
+    for (size_t j = 0; j < N; ++j) {
+        seed = seed * 1664525u + 1013904223u;
+        v[j] = double(seed >> 8) / double(1u << 24) - 0.5;
+        nrm += v[j] * v[j];
+    }
+    for (double& e : v) e /= std::sqrt(nrm);
+    std::vector<double> al, be;   // the tridiagonal matrix
+    double beta = 0.0;
+    const int steps = int(std::min<size_t>(20, N));
+    for (int k = 0; k < steps; ++k) {
+        for (size_t j = 0; j < N; ++j) x[j] = s[j] * v[j];
+        double a = 0.0;
+        for (size_t j = 0; j < N; ++j) {
+            double t = 0.0;
+            for (int32_t q = C.g_ptr[j]; q < C.g_ptr[j + 1]; ++q) t += C.g_val[size_t(q)] * x[size_t(C.g_idx[size_t(q)])];
+            for (int32_t q = C.gt_ptr[j]; q < C.gt_ptr[j + 1]; ++q)
+                t += C.gt_val[size_t(q)] * x[size_t(C.gt_idx[size_t(q)])];
+            y[j] = 0.5 * s[j] * t - beta * u[j];
+            a += y[j] * v[j];
+        }
+        al.push_back(a);
+        double n2 = 0.0;
+        for (size_t j = 0; j < N; ++j) {
+            y[j] -= a * v[j];
+            n2 += y[j] * y[j];
+        }
+        beta = std::sqrt(n2);
+        if (!(beta > 1e-12)) break;
+        be.push_back(beta);
+        for (size_t j = 0; j < N; ++j) {
+            u[j] = v[j];
+            v[j] = y[j] / beta;
+        }
+    }
+    // extreme eigenvalues by bisection on the number of negative pivots
+    const int n = int(al.size());
+    double r = 0.0;
+    for (int k = 0; k < n; ++k) r = std::max(r, std::fabs(al[size_t(k)]) + (k + 1 < n ? be[size_t(k)] : 0.0) + (k ? be[size_t(k) - 1] : 0.0));
+    if (!(r > 0.0) || !std::isfinite(r)) return out;
+    auto below = [&](double z) {   // eigenvalues below z
+        int c = 0;
+        double d = 1.0;
+        for (int k = 0; k < n; ++k) {
+            d = al[size_t(k)] - z - (k ? be[size_t(k) - 1] * be[size_t(k) - 1] / d : 0.0);
+            if (d == 0.0) d = 1e-300;
+            c += d < 0.0;
+        }
+        return c;
+    };
+    auto bisect = [&](int count) {   // the largest z with at most count eigenvalues below it
+        double a = -r, b = r;
+        for (int i = 0; i < 60; ++i) {
+            const double z = 0.5 * (a + b);
+            (below(z) > count ? b : a) = z;
+        }
+        return 0.5 * (a + b);
+    };
+    const double lo = 0.98 * bisect(0), hi = 1.01 * bisect(n - 1);
+    if (lo > 0.0 && hi > lo) out = {lo, hi};
+    return out;
+}
+
+// The columns s0 .. s0 + S - 1 of A Y = B by the Chebyshev iteration: the buffer with
+// the solution, or null where the interval, the tolerance or maxit (in BiCGStab steps
+// of two products) rule it out or the residuals miss their target after all; w.cols
+// holds the residuals.  The steps are counted by the bound 2 sigma^k and up to four
+// groups of three more follow.  Columns are taken in groups whose vectors stay in the
+// last-level cache (192 MiB of 256) while that holds a multiple of the eight tiles that
+// the XCDs work on: 7 TB/s for these passes instead of 4.9 from memory.
+template <typename V>
+V* cheb_solve(const DevCald& d, const CaldWs& w, int N, int s0, int S, double tol, int maxit, const double2* B,
+              const int32_t* a_ptr, const int32_t* a_idx, const double* a_val, const GramBounds& gb,
+              hipStream_t stream) {
+    if (!(gb.lo > 0.0) || tol < (sizeof(V) == 8 ? 1e-5 : 2e-14) || tol >= 1.0) return nullptr;
+    const double mid = 0.5 * (gb.hi + gb.lo), rho = 0.5 * (gb.hi - gb.lo) / mid, gamma = 1.0 / mid;
+    const double sigma = rho / (1.0 + std::sqrt(1.0 - rho * rho));
+    const double est = std::ceil(std::log(tol / 2.0) / std::log(sigma));
+    if (!(est <= 200.0)) return nullptr;
+    int K = std::max(2, int(est));
+    if (K > 2 * int64_t(maxit)) return nullptr;
+    const size_t col = size_t(N) * (16 + 2 * sizeof(V));
+    int group = int((size_t(192) << 20) / col) / (8 * CG_W) * (8 * CG_W);
+    if (group == 0) group = S;
+    V* buf[2] = {static_cast<V*>(w.x), static_cast<V*>(w.r)};
+    const int ns = cg_slices(N);
+    const dim3 gc(unsigned((S + 255) / 256));
+    auto finish = [&]() {
+        hipLaunchKernelGGL(colsq_final_kernel, dim3(unsigned((S + 15) / 16), 1u), dim3(256), 0, stream, w.part, S, ns,
+                           w.red);
+    };
+    int k = 0, cur = 0;        // steps done; buf[cur] holds x_(k+1)
+    double omega = 1.0;
+    for (int g0 = 0; g0 < S; g0 += group) {
+        const int Sg = std::min(group, S - g0);
+        hipLaunchKernelGGL(cheb_init_kernel<V>, dim3(cg_blocks(Sg, N)), dim3(256), 0, stream, B + s0 + g0, N,
+                           buf[0] + size_t(g0) * N, d.n_order, d.g_dinv, gamma, N, Sg, w.part + g0, S);
+    }
+    finish();
+    hipLaunchKernelGGL(bicg_setup_kernel, gc, dim3(256), 0, stream, w.cols, w.red, tol, S);
+    for (int round = 0; round < 5; ++round) {
+        int k1 = k, c1 = cur;
+        double o1 = omega;
+        for (int g0 = 0; g0 < S; g0 += group) {
+            const int Sg = std::min(group, S - g0);
+            k1 = k;
+            c1 = cur;
+            o1 = omega;
+            while (k1 < K) {
+                o1 = k1 == 0 ? 1.0 / (1.0 - 0.5 * rho * rho) : 1.0 / (1.0 - 0.25 * rho * rho * o1);
+                const V* X = buf[c1] + size_t(g0) * N;
+                V* Xp = buf[1 - c1] + size_t(g0) * N;
+                if (k1 + 1 == K)
+                    hipLaunchKernelGGL((cheb_step_kernel<V, true>), dim3(cg_blocks(Sg, N)), dim3(256), 0, stream, a_ptr,
+                                       a_idx, a_val, d.n_order, d.g_dinv, B + s0 + g0, N, X, Xp, o1, gamma,
+                                       int(k1 == 0), N, Sg, w.part + g0, S);
+                else
+                    hipLaunchKernelGGL((cheb_step_kernel<V, false>), dim3(cg_blocks(Sg, N)), dim3(256), 0, stream, a_ptr,
+                                       a_idx, a_val, d.n_order, d.g_dinv, B + s0 + g0, N, X, Xp, o1, gamma,
+                                       int(k1 == 0), N, Sg, w.part + g0, S);
+                c1 = 1 - c1;
+                ++k1;
+            }
+        }
+        k = k1;
+        cur = c1;
+        omega = o1;
+        finish();
+        fill_zero_bytes(w.counter, 8, stream);
+        hipLaunchKernelGGL(cheb_check_kernel, gc, dim3(256), 0, stream, w.cols, w.red, S, w.counter);
+        int left = 0;
+        EFIE_HIP_CHECK(hipMemcpyAsync(&left, w.counter, sizeof(int), hipMemcpyDeviceToHost, stream));
+        EFIE_HIP_CHECK(hipStreamSynchronize(stream));
+        if (verbose())
+            std::fprintf(stderr, "[efie] calderon Gram Chebyshev [%.3f, %.3f] %d steps, %d of %d columns left\n", gb.lo,
+                         gb.hi, k, left, S),
+                std::fflush(stderr);
+        if (left == 0) return buf[1 - cur];   // x_k, whose residuals were taken
+        K += 3;
+    }
+    return nullptr;
+}
+
+// A Y = B for the columns of B (N x N, row-major) in batches of pl.Sb
 // (vectors stored as V), each batch transposed into the rows of Pout; A = G^T
 // (opG false) or G (opG true).  Returns the worst final relative residual.
 template <typename V>
 double cald_gram_solve(const DevCald& d, const CaldWs& w, const CaldPlan& pl, int N, double tol, int maxit,
-                       double2* Pout, const double2* B, bool opG, hipStream_t stream) {
+                       double2* Pout, const double2* B, bool opG, const GramBounds& gb, hipStream_t stream) {
     // A with the CSR of A (stored rows in n_order)
     const int32_t *a_ptr = opG ? d.g_ptr : d.gt_ptr, *a_idx = opG ? d.g_idx : d.gt_idx;
     const double* a_val = opG ? d.g_val : d.gt_val;
@@ -854,33 +1105,37 @@ double cald_gram_solve(const DevCald& d, const CaldWs& w, const CaldPlan& pl, in
             hipLaunchKernelGGL(colsq_final_kernel, dim3(unsigned((S + 15) / 16), unsigned(nred)), dim3(256), 0, stream,
                                w.part, S, ns, w.red);
         };
-        hipLaunchKernelGGL(bicg_init_kernel<V>, gs, dim3(256), 0, stream, B + s0, N, xv, rv, hv, pv, N, S, w.part);
-        finish(1);
-        hipLaunchKernelGGL(bicg_setup_kernel, gc, dim3(256), 0, stream, w.cols, w.red, tol, S);
-        int h_active = S;
-        for (int it = 0; it < maxit && h_active > 0; ++it) {
-            // v = A p, alpha = rho / <r^, v>, s = r - alpha v
-            hipLaunchKernelGGL(cspmm_dot_kernel<V>, gs, dim3(256), 0, stream, a_ptr, a_idx, a_val, pv, vv, S,
-                               d.n_order, N, hv, w.part);
-            finish(2);
-            hipLaunchKernelGGL(bicg_alpha_kernel, gc, dim3(256), 0, stream, w.cols, w.red, S);
-            hipLaunchKernelGGL(bicg_s_kernel<V>, gs, dim3(256), 0, stream, rv, vv, w.cols, N, S);
-            // t = A s, omega = <t, s> / <t, t>, x += alpha p + omega s, r = s - omega t
-            hipLaunchKernelGGL(cspmm_dot_kernel<V>, gs, dim3(256), 0, stream, a_ptr, a_idx, a_val, rv, tv, S,
-                               d.n_order, N, rv, w.part);
-            finish(3);
-            hipLaunchKernelGGL(bicg_omega_kernel, gc, dim3(256), 0, stream, w.cols, w.red, S);
-            hipLaunchKernelGGL(bicg_xr_kernel<V>, gs, dim3(256), 0, stream, xv, rv, pv, tv, hv, w.cols, N, S, w.part);
-            finish(3);
-            fill_zero_bytes(w.counter, 8, stream);
-            hipLaunchKernelGGL(bicg_check_kernel, gc, dim3(256), 0, stream, w.cols, w.red, S, w.counter);
-            // p = r + beta (p - omega v)
-            hipLaunchKernelGGL(bicg_p_kernel<V>, gs, dim3(256), 0, stream, pv, rv, vv, w.cols, N, S);
-            EFIE_HIP_CHECK(hipMemcpyAsync(&h_active, w.counter, sizeof(int), hipMemcpyDeviceToHost, stream));
-            EFIE_HIP_CHECK(hipStreamSynchronize(stream));
+        const V* sol = cheb_solve<V>(d, w, N, s0, S, tol, maxit, B, a_ptr, a_idx, a_val, gb, stream);
+        if (!sol) {
+            hipLaunchKernelGGL(bicg_init_kernel<V>, gs, dim3(256), 0, stream, B + s0, N, xv, rv, hv, pv, N, S, w.part);
+            finish(1);
+            hipLaunchKernelGGL(bicg_setup_kernel, gc, dim3(256), 0, stream, w.cols, w.red, tol, S);
+            int h_active = S;
+            for (int it = 0; it < maxit && h_active > 0; ++it) {
+                // v = A p, alpha = rho / <r^, v>, s = r - alpha v
+                hipLaunchKernelGGL(cspmm_dot_kernel<V>, gs, dim3(256), 0, stream, a_ptr, a_idx, a_val, pv, vv, S,
+                                   d.n_order, N, hv, w.part);
+                finish(2);
+                hipLaunchKernelGGL(bicg_alpha_kernel, gc, dim3(256), 0, stream, w.cols, w.red, S);
+                hipLaunchKernelGGL(bicg_s_kernel<V>, gs, dim3(256), 0, stream, rv, vv, w.cols, N, S);
+                // t = A s, omega = <t, s> / <t, t>, x += alpha p + omega s, r = s - omega t
+                hipLaunchKernelGGL(cspmm_dot_kernel<V>, gs, dim3(256), 0, stream, a_ptr, a_idx, a_val, rv, tv, S,
+                                   d.n_order, N, rv, w.part);
+                finish(3);
+                hipLaunchKernelGGL(bicg_omega_kernel, gc, dim3(256), 0, stream, w.cols, w.red, S);
+                hipLaunchKernelGGL(bicg_xr_kernel<V>, gs, dim3(256), 0, stream, xv, rv, pv, tv, hv, w.cols, N, S, w.part);
+                finish(3);
+                fill_zero_bytes(w.counter, 8, stream);
+                hipLaunchKernelGGL(bicg_check_kernel, gc, dim3(256), 0, stream, w.cols, w.red, S, w.counter);
+                // p = r + beta (p - omega v)
+                hipLaunchKernelGGL(bicg_p_kernel<V>, gs, dim3(256), 0, stream, pv, rv, vv, w.cols, N, S);
+                EFIE_HIP_CHECK(hipMemcpyAsync(&h_active, w.counter, sizeof(int), hipMemcpyDeviceToHost, stream));
+                EFIE_HIP_CHECK(hipStreamSynchronize(stream));
+            }
+            sol = xv;
         }
         hipLaunchKernelGGL(tile_out_kernel<V>, dim3(unsigned((N + 31) / 32), unsigned(cg_pad(S) / 32)), dim3(256), 0,
-                           stream, xv, S, N, Pout, s0);
+                           stream, sol, S, N, Pout, s0);
         if (verbose())
             std::fprintf(stderr, "[efie] calderon Gram solve columns %d..%d done t=%.3f\n", s0, s0 + S, now_s()),
                 std::fflush(stderr);
@@ -943,6 +1198,7 @@ int efie_calderon_create(efie_mesh mesh, efie_calderon* out) {
             efie::put(blob, offs, C->u_ptr);
             efie::put(blob, offs, C->u_idx);
             efie::put(blob, offs, C->r_loc);
+            efie::put(blob, offs, efie::gram_inverse_diagonal(*C));
             blob.resize(efie::a256(blob.size()));
             C->host_blob.swap(blob);
             C->offs.swap(offs);
@@ -1091,10 +1347,11 @@ int efie_calderon_assemble_ex(efie_calderon c, double kt_re, double kt_im, doubl
         if (Tbc_out)
             EFIE_HIP_CHECK(hipMemcpyAsync(Tbc_out, w.Tbc, size_t(N) * N * 16, hipMemcpyDeviceToDevice, stream));
         // ---- P = T_BC G^{-1}: column batches of G^T Y = T_BC (column s = row s of T_BC), P = Y^T
+        const GramBounds gb = gram_bounds(*c);   // on the host while the kernels above run
         const double worst =
             pl.vsz == 8
-                ? cald_gram_solve<float2>(d, w, pl, N, tol, maxit, static_cast<double2*>(P), w.Tbc, false, stream)
-                : cald_gram_solve<double2>(d, w, pl, N, tol, maxit, static_cast<double2*>(P), w.Tbc, false, stream);
+                ? cald_gram_solve<float2>(d, w, pl, N, tol, maxit, static_cast<double2*>(P), w.Tbc, false, gb, stream)
+                : cald_gram_solve<double2>(d, w, pl, N, tol, maxit, static_cast<double2*>(P), w.Tbc, false, gb, stream);
         if (relres) *relres = worst;
         EFIE_HIP_CHECK(hipGetLastError());
         return worst <= tol ? int(EFIE_OK) : int(EFIE_NOT_CONVERGED);
@@ -1185,10 +1442,11 @@ int efie_calderon_cfie_assemble(efie_calderon c, double k, double kt_re, double 
             hipLaunchKernelGGL(transpose_inplace_kernel, dim3(unsigned(npairs)), dim3(256), 0, stream, w.Tbc, N, nt);
         }
         // Q = M~ G^-T: row s of Q solves G y = row s of M~
+        const GramBounds gb = gram_bounds(*c);   // on the host while the kernels above run
         const double worst =
             pl.vsz == 8
-                ? cald_gram_solve<float2>(d, w, pl, N, tol, maxit, static_cast<double2*>(Q), w.Tbc, true, stream)
-                : cald_gram_solve<double2>(d, w, pl, N, tol, maxit, static_cast<double2*>(Q), w.Tbc, true, stream);
+                ? cald_gram_solve<float2>(d, w, pl, N, tol, maxit, static_cast<double2*>(Q), w.Tbc, true, gb, stream)
+                : cald_gram_solve<double2>(d, w, pl, N, tol, maxit, static_cast<double2*>(Q), w.Tbc, true, gb, stream);
         if (relres) *relres = worst;
         EFIE_HIP_CHECK(hipGetLastError());
         return worst <= tol ? int(EFIE_OK) : int(EFIE_NOT_CONVERGED);

@@ -105,6 +105,32 @@ def test_calderon_l4_iteration_counts(dev, k):
     assert err <= 1e-3
 
 
+# Chebyshev steps on one partial tile, on one group and on nine groups of columns (the last ragged), an uneven mesh, and
+# complex64 vectors; then BiCGStab: a tolerance below the Chebyshev residual's rounding, and few steps
+@pytest.mark.parametrize("n,axes,tol,maxit", [(1, (1.0, 1.0, 1.0), 1e-13, 500), (5, (1.0, 0.7, 0.15), 1e-13, 500),
+                                              (12, (1.0, 1.0, 1.0), 1e-13, 500), (5, (1.0, 1.0, 1.0), 1e-4, 500),
+                                              (4, (1.0, 1.0, 1.0), 1e-15, 500), (4, (1.0, 1.0, 1.0), 1e-13, 2)])
+def test_gram_solve_residuals(dev, n, axes, tol, maxit):
+    """Rows of P G_mix - T_BC against the tolerance.  Beyond it: the roundings of P (2^-53, or 2^-24 in complex64) and of
+    19-term sums, times a condition number of at most 100: 2e-13 and 1e-4."""
+    flush(f"Gram solve n={n} axes={axes} tol={tol} maxit={maxit}")
+    v, f = synth.ellipsoid(n, axes)
+    m = P.Mesh(v, f).upload(dev)
+    cal = P.Calderon(m).upload(dev)
+    Pm, T = cal.assemble(P.ktilde(1.0), tol=tol, maxit=maxit, with_tbc=True)
+    G = np.zeros((m.n, m.n))
+    assert P.lib().efie_calderon_host_matrices(cal._h, None, G.ctypes.data) == 0
+    G = torch.as_tensor(G, device=dev)
+    D = torch.complex(Pm.real.contiguous() @ G, Pm.imag.contiguous() @ G) - T
+    res = float((D.norm(dim=1) / T.norm(dim=1)).max())
+    flush(f"  reported {cal.gram_relres:.2e} true {res:.2e}")
+    if maxit == 2:
+        assert tol < cal.gram_relres < 1.0
+        return
+    assert cal.gram_relres <= tol
+    assert res <= tol + (1e-4 if tol >= 1e-4 else 2e-13)
+
+
 @pytest.mark.parametrize("fp32_acc", [False, True])
 def test_calderon_c64_bary_and_mixed_solve(dev, fp32_acc):
     """Level 3 (N = 1920), k = 3, 16 plane waves: P from FP32 barycentric far pairs
