@@ -170,6 +170,12 @@ int efie_assemble(efie_mesh mesh, double k_re, double k_im, double eta, int dtyp
  * Errors: EFIE_ERR_ARG if ws_bytes < min_bytes.
  */
 int efie_assemble_workspace_size(efie_mesh mesh, int dtype, size_t* min_bytes, size_t* full_bytes);
+/*
+ * Workspace with which efie_assemble_ws evaluates every pair of triangles once (rows of
+ * pair values, then a gather) instead of once per tile: 64 N^2 bytes for EFIE_C128 up to
+ * 4 GiB, else 0 (the tiles).  With less, the tiles: the same values in the same order.
+ */
+int efie_assemble_pairs_workspace_size(efie_mesh mesh, int dtype, size_t* bytes);
 int efie_assemble_ws(efie_mesh mesh, double k_re, double k_im, double eta, int dtype, void* Z,
                      void* ws, size_t ws_bytes, hipStream_t stream);
 

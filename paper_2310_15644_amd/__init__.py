@@ -46,7 +46,8 @@ EXPORTED = [
     "efie_calderon_host_matrices", "efie_calderon_assemble", "efie_calderon_set_far_rule", "efie_solve_precond_workspace_size", "efie_solve_precond",
     "efie_batch_create", "efie_batch_destroy", "efie_batch_sizes", "efie_batch_upload", "efie_batch_assemble",
     "efie_batch_solve", "efie_farfield_adjoint", "efie_vertex_grad_workspace_size", "efie_vertex_grad",
-    "efie_assemble_workspace_size", "efie_assemble_ws", "efie_calderon_assemble_ex", "efie_solve_precond_ex",
+    "efie_assemble_workspace_size", "efie_assemble_pairs_workspace_size", "efie_assemble_ws",
+    "efie_calderon_assemble_ex", "efie_solve_precond_ex",
     "efie_convert", "efie_ktilde", "efie_mesh_fp32_kmax", "efie_zx_flush64_noalloc_max", "efie_zx_flush64_noalloc",
     "efie_gemm_autotune_cached_workspace_size", "efie_gemm_autotune_cached",
     "efie_bie2d_create", "efie_bie2d_destroy", "efie_bie2d_sizes", "efie_bie2d_upload", "efie_bie2d_perimeter",
@@ -175,6 +176,7 @@ def lib():
                               ctypes.c_size_t, P], ctypes.c_int),
         "efie_farfield_adjoint": ([P, D, D, P, I64, P, I64, P, P, ctypes.c_size_t, P], ctypes.c_int),
         "efie_farfield_objective": ([P, I64, P, P, P], ctypes.c_int),
+        "efie_assemble_pairs_workspace_size": ([P, ctypes.c_int, ctypes.POINTER(ctypes.c_size_t)], ctypes.c_int),
         "efie_assemble_workspace_size": ([P, ctypes.c_int, ctypes.POINTER(ctypes.c_size_t),
                                           ctypes.POINTER(ctypes.c_size_t)], ctypes.c_int),
         "efie_assemble_ws": ([P, D, D, D, ctypes.c_int, P, P, ctypes.c_size_t, P], ctypes.c_int),
@@ -316,10 +318,11 @@ def assemble(mesh: Mesh, k, eta: float = ETA0, dtype=C128, parts: bool = False, 
              atomic: bool = False, workspace_bytes: int | None = None):
     """Dense Z (N, N) on the device; parts=True returns (T_A, T_Phi) instead.
 
-    By default Z is built by the owner-computes tiles of efie_assemble_ws (written
-    once, deterministic, exactly symmetric; the workspace holds the near-pair
-    blocks, and `workspace_bytes` is accepted for compatibility and otherwise
-    unused); atomic=True (and parts mode) use efie_assemble."""
+    By default Z is built by efie_assemble_ws, written once, deterministic and exactly
+    symmetric: complex128 up to N = 8192 from the rows of all pair values (64 N^2 bytes
+    of workspace), else by owner-computes tiles (the workspace holds the near-pair
+    blocks); `workspace_bytes` is accepted for compatibility and otherwise unused.
+    atomic=True (and parts mode) use efie_assemble."""
     torch = _torch()
     dev = mesh.device
     code, tdt = _cdtype(dtype)
@@ -332,7 +335,8 @@ def assemble(mesh: Mesh, k, eta: float = ETA0, dtype=C128, parts: bool = False, 
     if not parts and not atomic:
         lo, full = ctypes.c_size_t(), ctypes.c_size_t()
         _check(lib().efie_assemble_workspace_size(mesh._h, code, ctypes.byref(lo), ctypes.byref(full)))
-        nb = full.value
+        _check(lib().efie_assemble_pairs_workspace_size(mesh._h, code, ctypes.byref(lo)))
+        nb = max(full.value, lo.value)
         ws = torch.empty(nb + 256, dtype=torch.uint8, device=dev)
         off = (-ws.data_ptr()) % 256
         _check(lib().efie_assemble_ws(mesh._h, k.real, k.imag, float(eta), code, _ptr(Z),

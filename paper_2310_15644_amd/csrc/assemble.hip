@@ -17,18 +17,19 @@
 // The test triangle is uniform over a block (scalar loads), the source triangle
 // varies across lanes (coalesced structure-of-arrays loads).
 //
-// Without atomics (efie_assemble_ws): owner-computes tiles (tile_kernels.h).  A
-// block owns a tile of Z (64 x 64 RWGs in complex64, 32 x 32 in complex128, the
-// tiles on and above the diagonal), evaluates every triangle pair between the
+// Without atomics (efie_assemble_ws).  Complex128 with a workspace of 64 N^2 bytes
+// (up to 4 GiB): every pair q >= p once into the pair rows W[p][i][n][side], then a
+// gather of the four values of every entry (rows_kernels.h).  Otherwise owner-computes
+// tiles (tile_kernels.h): a block owns a tile of Z (the tiles on and above the
+// diagonal; edge by tile_edge), evaluates every triangle pair between the
 // triangles of its row RWGs and those of its column RWGs once, adds each entry's
 // four pair values in a fixed order and writes the tile and its mirror: Z is
 // written once, no workspace rows, no atomics, deterministic and exactly
-// symmetric.  The near pairs' FP64 blocks are computed first (one thread per
-// ordered near pair) into the caller's workspace, where the tiles read them.
-// The pair rows W[p][i][n][side] of a chunk of test triangles (far_rows_kernel,
-// near_rows_kernel: the pairs with source triangle q >= p, q = p halved) remain
-// the first step of the Calderon build, which contracts rows without forming the
-// matrix (pair_rows_chunk).
+// symmetric.  The near pairs' FP64 blocks are computed first (a group of lanes per
+// pair) into the caller's workspace, where the tiles read them.
+// The pair rows of a chunk of test triangles (far_rows_kernel, near_rows_kernel: q = p
+// halved) are also the first step of the Calderon build, which contracts rows without
+// forming the matrix (pair_rows_chunk).
 //
 // Near pairs (a shared vertex, or centroids closer than the near factor times the
 // larger longest edge; decided on the device as on the host) are skipped by the
@@ -112,12 +113,39 @@ __global__ __launch_bounds__(256) void near_blocks_kernel(DevMesh m, double kr, 
 // Bound by the vector ALU: about 55 FP64 operations per Green's function (26 FP32).
 // N = 7680 in complex128: 10.3 ms with the library's sincos, Cartesian moments and
 // 32-wide tiles of half-filled waves, 3.9 ms now; N = 30720 in complex64: 23.7 -> 22.1 ms.
-template <typename R, bool CK, int TS>
+template <typename R, bool CK, int TS, bool ORD>
 __global__ __launch_bounds__(256, sizeof(R) == 4 ? 3 : 2) void tile_kernel(DevMesh m, Tables<R> tb, Phase<R> ph, Scale sc,
                                                    const typename Cplx<R>::T* __restrict__ NB,
                                                    typename Cplx<R>::T* __restrict__ Z) {
     __shared__ TileLds<R, TS> L;
-    tile_block<R, CK, TS>(m, tb, ph, sc, NB, Z, (long long)blockIdx.x, L);
+    tile_block<R, CK, TS, ORD>(m, tb, ph, sc, NB, Z, (long long)blockIdx.x, L);
+}
+
+// The pair rows of Z: near pairs by the first nnear blocks (few, with a long chain of
+// operations each: they start first), then the far pairs.  Bound by the vector ALU:
+// every pair once, where the tiles evaluate 1.8 to 4 times as many and hold two blocks
+// per CU at their barriers.  N = 480: 36 us and 11 for the gather, against 30 + 55 for
+// near blocks and tiles; N = 7680: 1.88 and 0.82 ms against 0.14 + 4.08 (whole
+// assembly, warm: 41 us against 78 and 2.32 ms against 3.87).
+template <bool CK>
+__global__ __launch_bounds__(FAR_BLOCK, 2) void pair_rows_kernel(DevMesh m, Tables<double> tb, Phase<double> ph,
+                                                                 double kr, double ki, Scale sc,
+                                                                 double2* __restrict__ W, int nnear, int pb) {
+    if (int(blockIdx.x) < nnear) {
+        const int t = int(blockIdx.x * FAR_BLOCK + threadIdx.x), u = t / NEAR_G;
+        if (u < m.n_up) pair_near_one(m, kr, ki, sc, W, m.near_up[u], t % NEAR_G);
+    } else {
+        pair_far_block<CK>(m, tb, ph, sc, W, pb, int(blockIdx.x) - nnear);
+    }
+}
+
+// Z from the pair rows, a block per tile on and above the diagonal.  Bound by memory:
+// every row value is read once and Z written once (N = 7680: 2.9 GB, 3.5 TB/s).
+__global__ __launch_bounds__(256) void gather_kernel(DevMesh m, const double2* __restrict__ W, double2* __restrict__ Z) {
+    __shared__ GatherLds L;
+    int bi, bj;
+    tile_decode((long long)blockIdx.x, (m.N + GATHER - 1) / GATHER, bi, bj);
+    gather_tile(m, W, Z, bi, bj, L);
 }
 
 template <typename R>
@@ -202,6 +230,7 @@ static void near_beside_far(hipStream_t s, NearF near, FarF far) {
 
 // The tile edge by the order of Z, measured on geodesic spheres (microseconds for
 // the whole assembly with edge 16 / 32 / 64, complex128; complex64 in brackets):
+// Complex128 takes them only without the workspace of the pair rows (PAIR_ROWS_MAX).
 //   N =  480    78 /  104 /  310   [ 66 /  90 / 243]
 //   N = 1080   228 /  209 /  343   [124 / 132 / 269]
 //   N = 3000  1117 /  806 /  862   [490 / 448 / 503]
@@ -232,12 +261,19 @@ void launch_tiles(const DevMesh& m, double kr, double ki, const Scale& sc, void*
         constexpr int TS = decltype(edge)::value;
         const long long nt = tile_count(m.N, TS);
         EFIE_REQUIRE(nt < (1ll << 31), EFIE_ERR_ARG, "assemble_ws: N too large");
-        if (ki != 0.0)
-            hipLaunchKernelGGL((tile_kernel<R, true, TS>), dim3(unsigned(nt)), dim3(256), 0, s, m, tables_of<R>(m), ph,
-                               sc, NB, static_cast<C2*>(Z));
-        else
-            hipLaunchKernelGGL((tile_kernel<R, false, TS>), dim3(unsigned(nt)), dim3(256), 0, s, m, tables_of<R>(m), ph,
-                               sc, NB, static_cast<C2*>(Z));
+        auto launch = [&](auto ord) {
+            constexpr bool ORD = decltype(ord)::value;
+            if (ki != 0.0)
+                hipLaunchKernelGGL((tile_kernel<R, true, TS, ORD>), dim3(unsigned(nt)), dim3(256), 0, s, m,
+                                   tables_of<R>(m), ph, sc, NB, static_cast<C2*>(Z));
+            else
+                hipLaunchKernelGGL((tile_kernel<R, false, TS, ORD>), dim3(unsigned(nt)), dim3(256), 0, s, m,
+                                   tables_of<R>(m), ph, sc, NB, static_cast<C2*>(Z));
+        };
+        // the edges below TILE_LARGE are taken by orders within tile_ordered only
+        constexpr bool DP = sizeof(R) == 8;
+        if (TS < TILE_LARGE || tile_ordered<R>(m.N)) launch(std::integral_constant<bool, DP>{});
+        else launch(std::integral_constant<bool, false>{});
     };
     prof_begin(PROF_FAR, s);
     switch (tile_edge(m.N)) {
@@ -246,6 +282,29 @@ void launch_tiles(const DevMesh& m, double kr, double ki, const Scale& sc, void*
         default: tiles(std::integral_constant<int, TILE_LARGE>{}); break;
     }
     prof_end(PROF_FAR, s);
+}
+
+// Z (complex128) by the pair rows in ws and the gather
+void launch_pair_rows(const DevMesh& m, double kr, double ki, const Scale& sc, void* Z, void* ws, hipStream_t s) {
+    double2* W = static_cast<double2*>(ws);
+    // four test triangles per block where that leaves blocks enough for every CU
+    const int pb = pair_far_blocks(m.T, 4) >= 2048 ? 4 : 1;
+    const long long nnear = (int64_t(m.n_up) * NEAR_G + FAR_BLOCK - 1) / FAR_BLOCK, nfar = pair_far_blocks(m.T, pb);
+    EFIE_REQUIRE(nnear + nfar < (1ll << 31), EFIE_ERR_ARG, "assemble_ws: mesh too large");
+    const Phase<double> ph = make_phase<double>(kr, ki);
+    prof_begin(PROF_FAR, s);
+    if (ki != 0.0)
+        hipLaunchKernelGGL((pair_rows_kernel<true>), dim3(unsigned(nnear + nfar)), dim3(FAR_BLOCK), 0, s, m,
+                           tables_of<double>(m), ph, kr, ki, sc, W, int(nnear), pb);
+    else
+        hipLaunchKernelGGL((pair_rows_kernel<false>), dim3(unsigned(nnear + nfar)), dim3(FAR_BLOCK), 0, s, m,
+                           tables_of<double>(m), ph, kr, ki, sc, W, int(nnear), pb);
+    prof_end(PROF_FAR, s);
+    const long long nt = (m.N + GATHER - 1) / GATHER;
+    prof_begin(PROF_NEAR, s);
+    hipLaunchKernelGGL(gather_kernel, dim3(unsigned(nt * (nt + 1) / 2)), dim3(256), 0, s, m, W,
+                       static_cast<double2*>(Z));
+    prof_end(PROF_NEAR, s);
 }
 
 template <typename ZT, bool PARTS>
@@ -337,8 +396,10 @@ static void assemble_impl(const DevMesh& m, double kr, double ki, double eta, in
             launch_far<double, true>(m, kr, ki, sc, Z, Z2, s);
             launch_near<double, true>(m, kr, ki, sc, Z, Z2, s);
         } else {
-            if (ws) {
-                launch_tiles<double>(m, kr, ki, sc, Z, ws, ws_bytes, s);   // near pairs included
+            if (ws && tile_ordered<double>(m.N) && ws_bytes >= N * N * 64) {
+                launch_pair_rows(m, kr, ki, sc, Z, ws, s);                 // near pairs included
+            } else if (ws) {
+                launch_tiles<double>(m, kr, ki, sc, Z, ws, ws_bytes, s);
             } else {
                 launch_far<double, false>(m, kr, ki, sc, Z, Z2, s);
                 launch_near<double, false>(m, kr, ki, sc, Z, Z2, s);
@@ -391,6 +452,16 @@ extern "C" int efie_assemble_workspace_size(efie_mesh mesh, int dtype, size_t* m
         const size_t nb = std::max<size_t>(256, mesh->near_p.size() * 9 * (dtype == EFIE_C128 ? 16 : 8));
         *min_bytes = nb;
         *full_bytes = nb;
+        return int(EFIE_OK);
+    });
+}
+
+extern "C" int efie_assemble_pairs_workspace_size(efie_mesh mesh, int dtype, size_t* bytes) {
+    return efie::guarded([&]() {
+        EFIE_REQUIRE(mesh != nullptr && bytes != nullptr, EFIE_ERR_ARG, "assemble_pairs_workspace_size: null argument");
+        EFIE_REQUIRE(dtype == EFIE_C128 || dtype == EFIE_C64, EFIE_ERR_ARG, "assemble_pairs_workspace_size: bad dtype");
+        const size_t N = size_t(mesh->N);
+        *bytes = dtype == EFIE_C128 && efie::tile_ordered<double>(int(mesh->N)) ? N * N * 64 : 0;
         return int(EFIE_OK);
     });
 }

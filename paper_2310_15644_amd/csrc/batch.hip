@@ -100,8 +100,9 @@ __global__ __launch_bounds__(256) void batch_near_kernel(DevMesh cat, const Batc
     near_block_one<R>(v, it.kr, 0.0, it.sc, NB + it.nboff, v.near_up[u], int(threadIdx.x) % NEAR_G);
 }
 
-// the tiles of every mesh's Z: persistent, tile t by block t mod gridDim.x
-template <typename R>
+// the tiles of every mesh's Z: persistent, tile t by block t mod gridDim.x; the meshes
+// whose single assembly has the orientation ORD (tile_ordered)
+template <typename R, bool ORD>
 __global__ __launch_bounds__(256, sizeof(R) == 4 ? 3 : 2) void batch_tiles_kernel(
     DevMesh cat, const BatchItem* __restrict__ items, int nm, int64_t ntiles,
     const typename Cplx<R>::T* __restrict__ NB, typename Cplx<R>::T* __restrict__ Z) {
@@ -109,9 +110,11 @@ __global__ __launch_bounds__(256, sizeof(R) == 4 ? 3 : 2) void batch_tiles_kerne
     for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
         const int r = item_of<&BatchItem::tile0>(items, nm, t);
         const BatchItem& it = items[r];
+        if (tile_ordered<R>(it.N) != ORD) continue;
         const DevMesh v = mesh_view(cat, it);
         const Phase<R> ph = make_phase<R>(it.kr, 0.0);
-        tile_block<R, false, TILE_LARGE>(v, tables_of<R>(v), ph, it.sc, NB + it.nboff, Z + it.zoff, t - it.tile0, L);
+        tile_block<R, false, TILE_LARGE, ORD>(v, tables_of<R>(v), ph, it.sc, NB + it.nboff, Z + it.zoff, t - it.tile0,
+                                              L);
     }
 }
 
@@ -549,11 +552,20 @@ extern "C" int efie_batch_assemble(efie_batch b, const double* k, double eta, in
                                    int(nm), NB);
                 prof_end(PROF_NEAR, stream);
             }
-            EFIE_HIP_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_tiles_kernel<R>, 256, 0));
-            const int64_t grid = std::min<int64_t>(tile, int64_t(std::max(1, per_cu)) * std::max(1, ncu));
+            auto tiles = [&](auto ord) {
+                constexpr bool ORD = decltype(ord)::value;
+                if (std::none_of(items.begin(), items.end(),
+                                 [](const BatchItem& it) { return tile_ordered<R>(it.N) == ORD; }))
+                    return;
+                EFIE_HIP_CHECK(
+                    hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_tiles_kernel<R, ORD>, 256, 0));
+                const int64_t grid = std::min<int64_t>(tile, int64_t(std::max(1, per_cu)) * std::max(1, ncu));
+                hipLaunchKernelGGL((batch_tiles_kernel<R, ORD>), dim3(unsigned(grid)), dim3(256), 0, stream, b->cat,
+                                   w.items, int(nm), tile, NB, static_cast<C2*>(Zcat));
+            };
             prof_begin(PROF_FAR, stream);
-            hipLaunchKernelGGL(batch_tiles_kernel<R>, dim3(unsigned(grid)), dim3(256), 0, stream, b->cat, w.items,
-                               int(nm), tile, NB, static_cast<C2*>(Zcat));
+            if constexpr (sizeof(R) == 8) tiles(std::integral_constant<bool, true>{});
+            tiles(std::integral_constant<bool, false>{});
             prof_end(PROF_FAR, stream);
         };
         if (dtype == EFIE_C64) run(float{});

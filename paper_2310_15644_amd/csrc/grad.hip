@@ -58,12 +58,6 @@ __device__ __forceinline__ Dual operator-(Dual a, double b) { return {a.v - b, a
 __device__ __forceinline__ Dual operator-(double a, Dual b) { return {a - b.v, -b.d}; }
 __device__ __forceinline__ Dual operator*(Dual a, double b) { return {a.v * b, a.d * b}; }
 __device__ __forceinline__ Dual operator*(double a, Dual b) { return b * a; }
-// 1 / x: the hardware estimate and one third-order step
-__device__ __forceinline__ double rcp_fast(double x) {
-    const double y = __builtin_amdgcn_rcp(x);
-    const double e = fma(-x, y, 1.0);
-    return fma(y, fma(e, e, e), y);
-}
 __device__ __forceinline__ Dual operator/(Dual a, Dual b) {
     const double i = rcp_fast(b.v), r = a.v * i;
     return {r, (a.d - r * b.d) * i};

@@ -270,24 +270,25 @@ static __device__ void potentials(const double r[3], const double u[3][3], const
         const double* rm = u[e];
         const double* rp = u[(e + 1) % 3];
         double lt[3] = {rp[0] - rm[0], rp[1] - rm[1], rp[2] - rm[2]};
-        const double len = sqrt(lt[0] * lt[0] + lt[1] * lt[1] + lt[2] * lt[2]);
-        lt[0] /= len; lt[1] /= len; lt[2] /= len;
+        const double il = rsqrt_fast(lt[0] * lt[0] + lt[1] * lt[1] + lt[2] * lt[2]);
+        lt[0] *= il; lt[1] *= il; lt[2] *= il;
         const double uu[3] = {lt[1] * n[2] - lt[2] * n[1], lt[2] * n[0] - lt[0] * n[2], lt[0] * n[1] - lt[1] * n[0]};
         const double lp = (rp[0] - rho[0]) * lt[0] + (rp[1] - rho[1]) * lt[1] + (rp[2] - rho[2]) * lt[2];
         const double lm = (rm[0] - rho[0]) * lt[0] + (rm[1] - rho[1]) * lt[1] + (rm[2] - rho[2]) * lt[2];
         const double P0 = (rm[0] - rho[0]) * uu[0] + (rm[1] - rho[1]) * uu[1] + (rm[2] - rho[2]) * uu[2];
         const double R02 = P0 * P0 + d * d;
-        const double Rp = sqrt((r[0] - rp[0]) * (r[0] - rp[0]) + (r[1] - rp[1]) * (r[1] - rp[1]) +
-                               (r[2] - rp[2]) * (r[2] - rp[2]));
-        const double Rm = sqrt((r[0] - rm[0]) * (r[0] - rm[0]) + (r[1] - rm[1]) * (r[1] - rm[1]) +
-                               (r[2] - rm[2]) * (r[2] - rm[2]));
+        const double Rp = root_fast((r[0] - rp[0]) * (r[0] - rp[0]) + (r[1] - rp[1]) * (r[1] - rp[1]) +
+                                    (r[2] - rp[2]) * (r[2] - rp[2]));
+        const double Rm = root_fast((r[0] - rm[0]) * (r[0] - rm[0]) + (r[1] - rm[1]) * (r[1] - rm[1]) +
+                                    (r[2] - rm[2]) * (r[2] - rm[2]));
         double lg = 0.0, at = 0.0;
-        if (sqrt(R02) >= 1e-12 * h) {
-            // R + l, written as R0^2 / (R - l) for l < 0 (same value, no cancellation)
-            const double fp = lp >= 0.0 ? Rp + lp : R02 / (Rp - lp);
-            const double fm = lm >= 0.0 ? Rm + lm : R02 / (Rm - lm);
-            lg = log(fp / fm);
-            at = atan(P0 * lp / (R02 + ad * Rp)) - atan(P0 * lm / (R02 + ad * Rm));
+        if (R02 >= 1e-24 * h * h) {
+            // fp / fm, f = R + l, written as R0^2 / (R - l) for l < 0 (same value, no cancellation)
+            const double sp = Rp + fabs(lp), sm = Rm + fabs(lm);
+            const double num = (lp >= 0.0 ? sp : R02) * (lm >= 0.0 ? 1.0 : sm);
+            const double den = (lp >= 0.0 ? 1.0 : sp) * (lm >= 0.0 ? sm : R02);
+            lg = log(num * rcp_fast(den));
+            at = atan(P0 * lp * rcp_fast(R02 + ad * Rp)) - atan(P0 * lm * rcp_fast(R02 + ad * Rm));
         }
         I0 += P0 * lg - ad * at;
         const double c1 = 0.5 * (R02 * lg + lp * Rp - lm * Rm);
@@ -299,9 +300,8 @@ static __device__ void potentials(const double r[3], const double u[3][3], const
 
 // Test point a of the singular block X(i,j) = sum_a W_a f_i(r_a) . int_s f_j(r')/R dS'
 // and of the scalar s0 = sum_a W_a int_s 1/R dS' (test triangle t, source triangle
-// s): w times that point's terms added to Y[i][j] (TR: to Y[j][i]) and to s0.
-static __device__ void singular_point(const DevMesh& m, int t, int s, int a, double w, bool TR, double Y[3][3],
-                                      double& s0) {
+// s): w times that point's terms added to Y[i][j] and to s0.
+static __device__ void singular_point(const DevMesh& m, int t, int s, int a, double w, double Y[3][3], double& s0) {
     const int T = m.T;
     // everything relative to the source centroid
     const double D[3] = {m.cx[t] - m.cx[s], m.cy[t] - m.cy[s], m.cz[t] - m.cz[s]};
@@ -329,8 +329,7 @@ static __device__ void singular_point(const DevMesh& m, int t, int s, int a, dou
                              ct * (da[2] - m.vz[i * T + t])};
         for (int j = 0; j < 3; ++j) {
             const double v = wa * (f[0] * inner[j][0] + f[1] * inner[j][1] + f[2] * inner[j][2]);
-            if (TR) Y[j][i] += v;
-            else Y[i][j] += v;
+            Y[i][j] += v;
         }
     }
 }
@@ -359,16 +358,20 @@ static __device__ __forceinline__ void green_smooth(const Phase<double>& ph, dou
     gi = ni * rinv;
 }
 
-// Near pair e of the ordered list, computed by a group of NEAR_G = 8 consecutive
-// lanes (g = 0..7 its lane in the group; every lane of the group calls this with
-// the same valid e): lane g < 7 takes test point a = g of p, i.e. the smooth part's
-// row a of the 7 x 7 rule and the two singular blocks' terms at test point a (of p
-// against q, and of q against p), so all lanes of a wave run the same code.  The
-// moments are summed over the group with a butterfly of lane exchanges (a fixed
-// order: deterministic), then lane g emits entries 3 i + j = g, g + 8:
-// emit(i, j, zr, zi) receives the FP64 Z contribution of test edge i and source
-// edge j (PARTS: T_A part; emit2: T_Phi).
-constexpr int NEAR_G = 8;
+// Near pair e of the ordered list, computed by a group of NEAR_G = 16 consecutive
+// lanes (g = 0..15 its lane in the group; every lane of the group calls this with
+// the same valid e): lane g with a = g % 8 < 7 takes test point a, the lower half of
+// the group p's point in the singular block of p against q and columns 0 to 3 of the
+// smooth part's row a of the 7 x 7 rule, the upper half q's point against p and
+// columns 4 to 6, so all lanes of a wave run the same code.  The moments are summed
+// over the group with a butterfly of lane exchanges (a fixed order: deterministic),
+// then lane g < 9 emits entry 3 i + j = g: emit(i, j, zr, zi) receives the FP64 Z
+// contribution of test edge i and source edge j (PARTS: T_A part; emit2: T_Phi).
+// Bound by memory latency and a lane's chain of dependent operations for small meshes
+// (FP64 blocks alone, N = 480: 29 us, of which 18 for a single wave), by the vector ALU
+// for large ones (N = 7680: 134 us).  150 registers, three waves per SIMD, where both
+// blocks on each of 8 lanes and the library's roots and quotients took 213 (30 and 137 us).
+constexpr int NEAR_G = 16;
 
 template <bool PARTS, typename Emit, typename Emit2>
 __device__ void near_pair_group(const DevMesh& m, int e, int g, double kr, double ki, const Scale& sc, Emit emit,
@@ -382,15 +385,18 @@ __device__ void near_pair_group(const DevMesh& m, int e, int g, double kr, doubl
     for (int x = 0; x < 16; ++x) v[x] = 0.0;
     double Y[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
     double s0 = 0.0;
-    if (g < NQ) {
-        const int a = g;
+    const int a = g & 7;
+    const bool upper = g >= 8;
+    if (a < NQ) {
         const double D[3] = {m.cx[p] - m.cx[q], m.cy[p] - m.cy[q], m.cz[p] - m.cz[q]};
         const double ax = m.qx[a * T + p], ay = m.qy[a * T + p], az = m.qz[a * T + p], wa = m.qw[a * T + p];
         double s0r = 0, s0i = 0, s1r[3] = {0, 0, 0}, s1i[3] = {0, 0, 0};
         const Phase<double> ph = make_phase<double>(kr, ki);
 #pragma unroll 1
-        for (int b = 0; b < NQ; ++b) {
-            const double bx = m.qx[b * T + q], by = m.qy[b * T + q], bz = m.qz[b * T + q], wb = m.qw[b * T + q];
+        for (int c = 0; c < 4; ++c) {   // the upper half's eighth column repeats the seventh with weight 0
+            const int b = min(upper ? 4 + c : c, NQ - 1);
+            const double bx = m.qx[b * T + q], by = m.qy[b * T + q], bz = m.qz[b * T + q];
+            const double wb = upper && c == 3 ? 0.0 : m.qw[b * T + q];
             const double dx = D[0] + ax - bx, dy = D[1] + ay - by, dz = D[2] + az - bz;
             double gr, gi;
             green_smooth(ph, kr, ki, dx * dx + dy * dy + dz * dz, gr, gi);
@@ -413,8 +419,12 @@ __device__ void near_pair_group(const DevMesh& m, int e, int g, double kr, doubl
         v[14] = wa * (ax * s1r[0] + ay * s1r[1] + az * s1r[2]);
         v[15] = wa * (ax * s1i[0] + ay * s1i[1] + az * s1i[2]);
         // singular part, symmetrised: (X_pq + X_qp^T) / 2
-        singular_point(m, p, q, a, 0.5, false, Y, s0);
-        singular_point(m, q, p, a, 0.5, true, Y, s0);
+        double X[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+        singular_point(m, upper ? q : p, upper ? p : q, a, 0.5, X, s0);
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) Y[i][j] = upper ? X[j][i] : X[i][j];
     }
 #pragma unroll
     for (int o = 1; o < NEAR_G; o <<= 1) {
@@ -427,8 +437,8 @@ __device__ void near_pair_group(const DevMesh& m, int e, int g, double kr, doubl
         s0 += __shfl_xor(s0, o, NEAR_G);
     }
     const double m0r = v[0], m0i = v[1];
-    for (int idx = g; idx < 9; idx += NEAR_G) {
-        const int i = idx / 3, j = idx - 3 * (idx / 3);
+    if (g < 9) {
+        const int i = g / 3, j = g - 3 * i;
         const double ux = m.vx[i * T + p], uy = m.vy[i * T + p], uz = m.vz[i * T + p];
         const double ci = m.cf[i * T + p], gi_ = m.dv[i * T + p];
         const double vx = m.vx[j * T + q], vy = m.vy[j * T + q], vz = m.vz[j * T + q];

@@ -58,6 +58,16 @@ __device__ __forceinline__ double rsqrt_fast(double x) {
     return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 
+// 1 / x: the hardware estimate and one third-order step
+__device__ __forceinline__ double rcp_fast(double x) {
+    const double y = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, y, 1.0);
+    return fma(y, fma(e, e, e), y);
+}
+
+// sqrt(x), x = 0 included
+__device__ __forceinline__ double root_fast(double x) { return x * rsqrt_fast(fmax(x, 1e-300)); }
+
 // sine and cosine of (pi / 2) x (hi + lo)
 __device__ __forceinline__ void sincos_quarter(double x, double hi, double lo, double& sn, double& cs) {
     constexpr double SHIFT = 6755399441055744.0;   // 1.5 * 2^52

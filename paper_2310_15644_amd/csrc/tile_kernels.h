@@ -110,7 +110,9 @@ inline long long tile_count(int N, int ts) {
 // in the order of their triangle indices (row triangle first), whatever the tile
 // edge, so that Z does not depend on it.  The accumulators stay in registers; the
 // pair values pass through LDS.
-template <typename R, bool CK, int TS>
+// ORD: every far pair in the orientation of the pair rows (smaller triangle index as
+// test triangle), for Z equal to the gathered one bit for bit.
+template <typename R, bool CK, int TS, bool ORD>
 __device__ __forceinline__ void tile_block(const DevMesh& m, const Tables<R>& tb, const Phase<R>& ph, const Scale& sc,
                                            const typename Cplx<R>::T* __restrict__ NB,
                                            typename Cplx<R>::T* __restrict__ Z, long long k, TileLds<R, TS>& L) {
@@ -203,8 +205,15 @@ __device__ __forceinline__ void tile_block(const DevMesh& m, const Tables<R>& tb
             auto put = [&](int i, int j, R re, R im) { out[3 * i + j] = C2{re, im}; };
             if (CACHE && pre_ok && !(m.far3 > 0.0 && far3_pair(m, p, q)))
                 far_pair_rule<NQ, R, CK, false, true>(m, tb, tb.qx, tb.qy, tb.qz, p, q, ph, sc, put, put, pre);
-            else
+            else if constexpr (ORD) {
+                // (p, q) with q < p by its transpose
+                const bool sw = q < p;
+                const int si = sw ? 1 : 3, sj = sw ? 3 : 1;
+                auto puts = [&](int i, int j, R re, R im) { out[si * i + sj * j] = C2{re, im}; };
+                far_pair_emit<R, CK, false>(m, tb, sw ? q : p, sw ? p : q, ph, sc, puts, puts);
+            } else {
                 far_pair_emit<R, CK, false>(m, tb, p, q, ph, sc, put, put);
+            }
         }
     };
     C2* val = &L.val[0][0];

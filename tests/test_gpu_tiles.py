@@ -3,6 +3,8 @@
 Tolerances as for every assembly: max |dZ| <= 1e-11 max |Z| in FP64 (rounding order), 2e-5 in complex64 (FP32 phase and
 distance).
 """
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -35,3 +37,37 @@ def test_tile_edges_sampled_rows(f, dt, tol):
         assert bool((Z == Z.T).all())
         Zo = oefie.z_rows(m, k, rows)
         assert np.abs(Z[rows].cpu().numpy() - Zo).max() <= tol * np.abs(Zo).max()
+
+
+# The complex128 assembly by pair rows (P.assemble) against the tiles (the workspace of the near blocks only): T = 20, 80
+# and 500 triangles (parts of a block of 256 sources, one test triangle per block), 2000 and 2880 (four per block), every
+# tile edge; triangles in random order (stored transposed), the far rule, complex k.  The same values are added in the same
+# order, so the matrices are equal bit for bit.
+@pytest.mark.parametrize("f,shuffle,far,k", [(1, False, 0.0, 0.7), (2, True, 0.0, 0.7 - 0.1j), (5, True, 4.0, 2.0),
+                                             (5, False, 0.0, 0.1), (10, True, 0.0, 1.5), (12, False, 3.0, 1.0 - 0.2j)])
+def test_pair_rows_equal_tiles(f, shuffle, far, k):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    v, t = synth.ellipsoid(f, (1.0, 0.9, 1.15))
+    if shuffle:
+        t = t[np.random.default_rng(f).permutation(len(t))]
+    mesh = P.Mesh(v, t).upload("cuda")
+    mesh.set_far_rule(far)
+    flush(f"pair rows against tiles N={mesh.n} shuffle={shuffle} far={far} k={k}")
+    lo, full, rows = ctypes.c_size_t(), ctypes.c_size_t(), ctypes.c_size_t()
+    L = P.lib()
+    assert L.efie_assemble_workspace_size(mesh._h, P.C128, ctypes.byref(lo), ctypes.byref(full)) == 0
+    assert L.efie_assemble_pairs_workspace_size(mesh._h, P.C128, ctypes.byref(rows)) == 0
+    assert rows.value == 64 * mesh.n**2
+    out = []
+    k = complex(k)
+    for nb in (full.value, rows.value):
+        ws = torch.full((nb,), 0xFF, dtype=torch.uint8, device="cuda")   # NaN where nothing is written
+        Z = torch.empty((mesh.n, mesh.n), dtype=torch.complex128, device="cuda")
+        assert L.efie_assemble_ws(mesh._h, k.real, k.imag, P.ETA0, P.C128, ctypes.c_void_p(Z.data_ptr()),
+                                  ctypes.c_void_p(ws.data_ptr()), nb, None) == 0
+        torch.cuda.synchronize()
+        out.append(Z)
+    assert torch.equal(torch.view_as_real(out[0]), torch.view_as_real(out[1]))
+    assert torch.equal(out[1], out[1].T)
+    assert torch.equal(out[1], P.assemble(mesh, k))
