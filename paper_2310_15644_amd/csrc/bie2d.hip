@@ -68,6 +68,11 @@ __device__ __forceinline__ double cabs_(double2 a) { return hypot(a.x, a.y); }
 struct PairMom {
     double2 s[2][2], d[2][2], m0;
 };
+// moments of the 256 pairs of a block in LDS: [2 alpha + beta] of mS, [4 + ...] of mD,
+// [8] m0, [9 + 2 beta + alpha] the mD of the transposed pair (neighbouring threads in
+// neighbouring banks)
+constexpr int MOMS = 9, MOMS_SYM = 13;
+using PairBank = double2[256];
 
 template <bool CK>
 __device__ __forceinline__ void accum(PairMom& pm, const Kern2d& K, double rx, double ry, double px, double py,
@@ -97,7 +102,7 @@ __device__ __forceinline__ void accum(PairMom& pm, const Kern2d& K, double rx, d
 // (A call of its own: inlined, its registers would halve the waves of the regular pairs.)
 template <bool CK>
 __device__ __attribute__((noinline)) void near_moments(const DevContour c, const Kern2d& K, int a, int b, int lane,
-                                                       PairMom& out) {
+                                                       PairBank* out, int slot) {
     PairMom pm;
 #pragma unroll
     for (int al = 0; al < 2; ++al)
@@ -150,19 +155,21 @@ __device__ __attribute__((noinline)) void near_moments(const DevContour c, const
             for (int be = 0; be < 2; ++be) pm.s[al][be].x += f * (0.25 * lnL + (al == be ? -7.0 / 16.0 : -5.0 / 16.0));
         pm.m0.x += f * (lnL - 1.5);
     }
-    if (lane == 0) out = pm;
+    if (lane == 0) {
+        const double2* m = reinterpret_cast<const double2*>(&pm);
+#pragma unroll
+        for (int x = 0; x < MOMS; ++x) out[x][slot] = m[x];
+    }
 }
 
-// of two segments that share no node
-template <int Q, bool CK>
-__device__ __forceinline__ void regular_moments(const DevContour& c, const Kern2d& K, int a, int b, PairMom& out) {
-    PairMom pm;
+// of two segments that share no node (into slot t of the bank v);
+// SYM: and the mD of (b, a)
+template <int Q, bool CK, bool SYM>
+__device__ __forceinline__ void regular_moments(const DevContour& c, const Kern2d& K, int a, int b, PairBank* v, int t) {
 #pragma unroll
-    for (int al = 0; al < 2; ++al)
-#pragma unroll
-        for (int be = 0; be < 2; ++be) pm.s[al][be] = pm.d[al][be] = make_double2(0.0, 0.0);
-    pm.m0 = make_double2(0.0, 0.0);
-    const double nxa = c.nx[a], nya = c.ny[a];
+    for (int x = 0; x < (SYM ? MOMS_SYM : MOMS); ++x) v[x][t] = make_double2(0.0, 0.0);
+    auto add = [&](int x, double2 g, double w) { v[x][t] = cadd(v[x][t], cscale(g, w)); };
+    const double nxa = c.nx[a], nya = c.ny[a], nxb = c.nx[b], nyb = c.ny[b];
     const double ax = c.ax[a], ay = c.ay[a], bx = c.bx[a] - ax, by = c.by[a] - ay;
     const double qx = c.ax[b], qy = c.ay[b], sx = c.bx[b] - qx, sy = c.by[b] - qy;
     // two source points at a time (four take the registers of a third wave)
@@ -171,10 +178,10 @@ __device__ __forceinline__ void regular_moments(const DevContour& c, const Kern2
         const double xp = c.gx[p], wp = c.gw[p];
         const double rx = ax + xp * bx - qx, ry = ay + xp * by - qy;
         // sums over the source points, weighted 1 and y; then over the test points
-        double2 g0 = make_double2(0.0, 0.0), g1 = g0, h0 = g0, h1 = g0;
+        double2 g0 = make_double2(0.0, 0.0), g1 = g0, h0 = g0, h1 = g0, e0 = g0, e1 = g0;
 #pragma unroll 1
         for (int q0 = 0; q0 < Q; q0 += 2) {
-            double R2[2], ri[2], f[2];
+            double R2[2], ri[2], f[2], fb[2];
             double2 g[2], d[2];
 #pragma unroll
             for (int x = 0; x < 2; ++x) {
@@ -182,6 +189,7 @@ __device__ __forceinline__ void regular_moments(const DevContour& c, const Kern2
                 const double dx = rx - yq * sx, dy = ry - yq * sy;
                 R2[x] = dx * dx + dy * dy;
                 f[x] = dx * nxa + dy * nya;
+                if (SYM) fb[x] = -(dx * nxb + dy * nyb);
             }
             green2d<2, CK>(K, R2, g, d, ri);
 #pragma unroll
@@ -193,38 +201,97 @@ __device__ __forceinline__ void regular_moments(const DevContour& c, const Kern2
                 g1 = cadd(g1, cscale(g[x], wy));
                 h0 = cadd(h0, cscale(h, wq));
                 h1 = cadd(h1, cscale(h, wy));
+                if (SYM) {
+                    const double2 e = cscale(d[x], fb[x] * ri[x]);
+                    e0 = cadd(e0, cscale(e, wq));
+                    e1 = cadd(e1, cscale(e, wy));
+                }
             }
         }
         const double w1 = wp * xp, w0 = wp - w1;
-        pm.m0 = cadd(pm.m0, cscale(g0, wp));
+        add(8, g0, wp);
         g0 = csub(g0, g1);
         h0 = csub(h0, h1);
-        pm.s[0][0] = cadd(pm.s[0][0], cscale(g0, w0));
-        pm.s[0][1] = cadd(pm.s[0][1], cscale(g1, w0));
-        pm.s[1][0] = cadd(pm.s[1][0], cscale(g0, w1));
-        pm.s[1][1] = cadd(pm.s[1][1], cscale(g1, w1));
-        pm.d[0][0] = cadd(pm.d[0][0], cscale(h0, w0));
-        pm.d[0][1] = cadd(pm.d[0][1], cscale(h1, w0));
-        pm.d[1][0] = cadd(pm.d[1][0], cscale(h0, w1));
-        pm.d[1][1] = cadd(pm.d[1][1], cscale(h1, w1));
+        add(0, g0, w0);
+        add(1, g1, w0);
+        add(2, g0, w1);
+        add(3, g1, w1);
+        add(4, h0, w0);
+        add(5, h1, w0);
+        add(6, h0, w1);
+        add(7, h1, w1);
+        if (SYM) {
+            e0 = csub(e0, e1);
+            add(9, e0, w0);
+            add(11, e1, w0);
+            add(10, e0, w1);
+            add(12, e1, w1);
+        }
+        asm volatile("" ::: "memory");   // the moments stay in LDS between the test points
     }
-    out = pm;
+}
+
+// length and normal of the 16 segments on one side of a tile
+struct Seg16 {
+    double len[16], nx[16], ny[16];
+};
+// the entry of two nodes from the moments of their four segment pairs, in slot
+// m(da, db) of the bank v those of the test node's segment la + da of A and the source
+// node's lb + db of B
+// (da = 0: the segment that ends in the node, alpha = 1; da = 1: that starts there, alpha = 0)
+template <typename M>
+__device__ __forceinline__ void entry2d(const Seg16& A, const Seg16& B, double2 k2, int la, int lb, const PairBank* v,
+                                        M m, double2& vs, double2& vd, double2& vn) {
+    vs = vd = vn = make_double2(0.0, 0.0);
+#pragma unroll
+    for (int da = 0; da < 2; ++da) {
+        const int a = la + da, al = 1 - da;
+#pragma unroll
+        for (int db = 0; db < 2; ++db) {
+            const int b = lb + db, be = 1 - db;
+            const int t = m(da, db);
+            const double LL = A.len[a] * B.len[b];
+            const double2 sv = cscale(v[2 * al + be][t], LL);
+            vs = cadd(vs, sv);
+            vd = cadd(vd, cscale(v[4 + 2 * al + be][t], LL));
+            const double sig = (al == be) ? 1.0 : -1.0;          // lambda' = -1/L (start), +1/L (end)
+            const double nn = A.nx[a] * B.nx[b] + A.ny[a] * B.ny[b];
+            vn = cadd(vn, csub(cscale(v[8][t], sig), cscale(cmul(k2, sv), nn)));
+        }
+    }
+}
+
+// (ti, tj), ti <= tj, of block k numbered row by row of the upper triangle of nt x nt
+__device__ inline void upper_tile(int64_t k, int nt, int& ti, int& tj) {
+    auto start = [&](int64_t r) { return r * nt - r * (r - 1) / 2; };
+    const double b = 2.0 * nt + 1.0;
+    int64_t r = int64_t((b - sqrt(fmax(0.0, b * b - 8.0 * double(k)))) * 0.5);
+    r = max(int64_t(0), min(r, int64_t(nt - 1)));
+    while (r > 0 && start(r) > k) --r;
+    while (r + 1 < nt && start(r + 1) <= k) ++r;
+    ti = int(r);
+    tj = int(r + (k - start(r)));
 }
 
 // One block: entries (i, j), i in [i0, i0 + TILE), j in [j0, j0 + TILE) of the
 // requested window; its 16 x 16 segment pairs (a in i0-1 .. i0+14, b in j0-1 ..
 // j0+14, mod n) are evaluated once, one per thread, into LDS and each entry adds
 // its four.  Out: S, Dm, Nm (any may be null) at [(i - row0) * ld + (j - col0)].
+// SYM (rows and columns the same nodes): the tiles on and above the diagonal only; the
+// Green's function and its radial derivative serve (b, a) too, whose moments then take
+// the pair's place for the mirrored tile (of neighbours evaluated again).
 // Bound by the vector ALU (about 165 FP64 operations per Green's function and its
 // derivative, 16 of each per pair), at two waves per SIMD: with three the spilled
 // registers cost more than the third wave gives (16.3 against 6.0 ms).  Three operators at
 // n = 6007, 18 nodes per wavelength: 54.9 ms with asymptotic series, backward
-// recurrences and one thread per neighbouring pair; 4.1 ms now.  n = 150: 3.1 ms -> 0.12 ms.
-template <int Q, bool CK>
+// recurrences and one thread per neighbouring pair; 4.1 ms with every tile evaluated
+// and the segments' data read per entry, 2.9 ms now.  n = 150: 3.1 ms -> 0.12 ms.
+template <int Q, bool CK, bool SYM>
 __global__ __launch_bounds__(256, 2) void assemble2d_kernel(DevContour c, Kern2d Karg, double kr, double ki, int row0, int nrows,
                                                          int col0, int ncols, int ld, double2* __restrict__ S,
                                                          double2* __restrict__ Dm, double2* __restrict__ Nm) {
-    __shared__ PairMom pm[16 * 16];
+    __shared__ PairBank pm[SYM ? MOMS_SYM : MOMS];
+    __shared__ Seg16 sg[2];   // segments of the rows i0 - 1 .. and of the columns j0 - 1 ..
     __shared__ Kern2d K;
     static_assert(sizeof(Kern2d) <= 256 * sizeof(double), "one double for each thread");
     if (threadIdx.x < sizeof(Kern2d) / sizeof(double))
@@ -232,45 +299,71 @@ __global__ __launch_bounds__(256, 2) void assemble2d_kernel(DevContour c, Kern2d
     __syncthreads();
     const int n = c.n;
     const int tcols = (ncols + TILE - 1) / TILE;
-    const int ti = int(blockIdx.x) / tcols, tj = int(blockIdx.x) - ti * tcols;
+    int ti, tj;
+    if (SYM) {
+        upper_tile(int64_t(blockIdx.x), tcols, ti, tj);
+    } else {
+        ti = int(blockIdx.x) / tcols;
+        tj = int(blockIdx.x) - ti * tcols;
+    }
     const int i0 = row0 + ti * TILE, j0 = col0 + tj * TILE;
-    {
-        const int t = threadIdx.x;
-        const int a = (i0 - 1 + t / 16 + n) % n, b = (j0 - 1 + t % 16 + n) % n;
-        const bool near = a == b || b == (a + 1) % n || a == (b + 1) % n;
-        if (!near) regular_moments<Q, CK>(c, K, a, b, pm[t]);
-        for (uint64_t m = __ballot(near); m; m &= m - 1) {
-            const int src = __builtin_ctzll(m);
-            near_moments<CK>(c, K, __shfl(a, src), __shfl(b, src), t & 63, pm[(t & ~63) + src]);
-        }
+    const int t = threadIdx.x;
+    const int a = (i0 - 1 + t / 16 + n) % n, b = (j0 - 1 + t % 16 + n) % n;
+    const bool near = a == b || b == (a + 1 == n ? 0 : a + 1) || a == (b + 1 == n ? 0 : b + 1);
+    if (t % 16 == 0) {
+        sg[0].len[t / 16] = c.len[a];
+        sg[0].nx[t / 16] = c.nx[a];
+        sg[0].ny[t / 16] = c.ny[a];
+    }
+    if (t < 16) {
+        sg[1].len[t] = c.len[b];
+        sg[1].nx[t] = c.nx[b];
+        sg[1].ny[t] = c.ny[b];
+    }
+    if (!near) regular_moments<Q, CK, SYM>(c, K, a, b, pm, t);
+    for (uint64_t m = __ballot(near); m; m &= m - 1) {
+        const int src = __builtin_ctzll(m);
+        near_moments<CK>(c, K, __shfl(a, src), __shfl(b, src), t & 63, pm, (t & ~63) + src);
     }
     __syncthreads();
-    const int t = threadIdx.x;
-    if (t >= TILE * TILE) return;
-    const int li = t / TILE, lj = t - li * TILE;
-    const int i = i0 + li, j = j0 + lj;
-    if (i >= row0 + nrows || j >= col0 + ncols) return;
     const double2 k2 = make_double2(kr * kr - ki * ki, 2.0 * kr * ki);
-    double2 vs = make_double2(0.0, 0.0), vd = vs, vn = vs;
-    for (int da = 0; da < 2; ++da) {
-        // da = 0: segment i-1 (node i is its end, alpha = 1); da = 1: segment i (alpha = 0)
-        const int a = (i - 1 + da + n) % n, al = 1 - da;
-        for (int db = 0; db < 2; ++db) {
-            const int b = (j - 1 + db + n) % n, be = 1 - db;
-            const PairMom& m = pm[(li + da) * 16 + (lj + db)];
-            const double LL = c.len[a] * c.len[b];
-            const double2 sv = cscale(m.s[al][be], LL);
-            vs = cadd(vs, sv);
-            vd = cadd(vd, cscale(m.d[al][be], LL));
-            const double sig = (al == be) ? 1.0 : -1.0;          // lambda' = -1/L (start), +1/L (end)
-            const double nn = c.nx[a] * c.nx[b] + c.ny[a] * c.ny[b];
-            vn = cadd(vn, csub(cscale(m.m0, sig), cscale(cmul(k2, sv), nn)));
+    double2 vs, vd, vn;
+    {
+        const int li = t / TILE, lj = t - li * TILE;
+        const int i = i0 + li, j = j0 + lj;
+        if (t < TILE * TILE && i < row0 + nrows && j < col0 + ncols) {
+            entry2d(sg[0], sg[1], k2, li, lj, pm, [&](int da, int db) { return (li + da) * 16 + (lj + db); }, vs, vd, vn);
+            const size_t o = size_t(i - row0) * ld + (j - col0);
+            if (S) S[o] = vs;
+            if (Dm) Dm[o] = vd;
+            if (Nm) Nm[o] = vn;
         }
     }
-    const size_t o = size_t(i - row0) * ld + (j - col0);
-    if (S) S[o] = vs;
-    if (Dm) Dm[o] = vd;
-    if (Nm) Nm[o] = vn;
+    if (!SYM || ti == tj) return;
+    __syncthreads();
+    if (!near) {
+        const double2 x = pm[1][t];
+        pm[1][t] = pm[2][t];
+        pm[2][t] = x;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) pm[4 + q][t] = pm[SYM ? 9 + q : 0][t];
+    }
+    for (uint64_t m = __ballot(near); m; m &= m - 1) {
+        const int src = __builtin_ctzll(m);
+        near_moments<CK>(c, K, __shfl(b, src), __shfl(a, src), t & 63, pm, (t & ~63) + src);
+    }
+    __syncthreads();
+    {
+        const int lj = t / TILE, li = t - lj * TILE;   // entry (j, i), lanes along i
+        const int i = i0 + li, j = j0 + lj;
+        if (t < TILE * TILE && i < row0 + nrows && j < col0 + ncols) {
+            entry2d(sg[1], sg[0], k2, lj, li, pm, [&](int db, int da) { return (li + da) * 16 + (lj + db); }, vs, vd, vn);
+            const size_t o = size_t(j - row0) * ld + (i - col0);
+            if (S) S[o] = vs;
+            if (Dm) Dm[o] = vd;
+            if (Nm) Nm[o] = vn;
+        }
+    }
 }
 
 // e (and h) for plane waves exp(-j k khat . r), khat = (cos phi, sin phi): one
@@ -831,25 +924,31 @@ Layout layout(int64_t n, int64_t rmax, int64_t block, int64_t nvec) {
 
 void launch_assemble(const DevContour& c, double kr, double ki, int row0, int nrows, int col0, int ncols, int ld,
                      double2* S, double2* D, double2* N, int q, hipStream_t s) {
-    const int tr = (nrows + efie::TILE - 1) / efie::TILE, tc = (ncols + efie::TILE - 1) / efie::TILE;
-    const size_t nblk = size_t(tr) * size_t(tc);
+    const size_t tr = size_t((nrows + efie::TILE - 1) / efie::TILE), tc = size_t((ncols + efie::TILE - 1) / efie::TILE);
+    // a window of the same rows and columns: the upper triangle of tiles (half the pairs),
+    // where all tiles are more than run at once (us, triangle / every tile: n = 150
+    // 113 / 112, n = 450 122 / 132, n = 1000 200 / 272)
+    const bool sym = row0 == col0 && nrows == ncols && tr * tc > 512;
+    const size_t nblk = sym ? tr * (tr + 1) / 2 : tr * tc;
     EFIE_REQUIRE(nblk < (size_t(1) << 31), EFIE_ERR_ARG, "bie2d_assemble: window too large");
     efie::prof_begin(efie::PROF_FAR, s);
     const efie::Kern2d K = efie::make_kern2d(kr, ki);
-#define B2D_Q(QQ)                                                                                                 \
-    case QQ:                                                                                                      \
-        if (ki != 0.0)                                                                                            \
-            hipLaunchKernelGGL((efie::assemble2d_kernel<QQ, true>), dim3(unsigned(nblk)), dim3(256), 0, s, c, K,  \
-                               kr, ki, row0, nrows, col0, ncols, ld, S, D, N);                                    \
-        else                                                                                                      \
-            hipLaunchKernelGGL((efie::assemble2d_kernel<QQ, false>), dim3(unsigned(nblk)), dim3(256), 0, s, c, K, \
-                               kr, ki, row0, nrows, col0, ncols, ld, S, D, N);                                    \
+#define B2D_K(QQ, CK, SYM)                                                                                        \
+    hipLaunchKernelGGL((efie::assemble2d_kernel<QQ, CK, SYM>), dim3(unsigned(nblk)), dim3(256), 0, s, c, K, kr, ki, \
+                       row0, nrows, col0, ncols, ld, S, D, N)
+#define B2D_Q(QQ)                                            \
+    case QQ:                                                 \
+        if (ki != 0.0 && sym) B2D_K(QQ, true, true);         \
+        else if (ki != 0.0) B2D_K(QQ, true, false);          \
+        else if (sym) B2D_K(QQ, false, true);                \
+        else B2D_K(QQ, false, false);                        \
         break
     switch (q) {
         B2D_Q(2); B2D_Q(3); B2D_Q(4); B2D_Q(5); B2D_Q(6); B2D_Q(8);
         default: throw efie::Error{EFIE_ERR_ARG, "bie2d: q must be 2..6 or 8"};
     }
 #undef B2D_Q
+#undef B2D_K
     efie::prof_end(efie::PROF_FAR, s, double(nrows) * double(ncols));
     EFIE_HIP_CHECK(hipGetLastError());
 }
