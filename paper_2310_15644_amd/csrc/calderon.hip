@@ -161,8 +161,10 @@ __global__ __launch_bounds__(256) void bc_src_kernel(DevCald c, const C2* __rest
 // share a CU, one computing while the other loads, and still amortizes the run's
 // list and index loads over 10 rows (level 5, source-side contraction per P
 // build: 429 ms with 8 x 2304 and one block per CU; 387 / 392 / 406 / 455 / 470 ms
-// with 10 x 1024, 8 x 768, 12 x 768, 6 x 1024, 16 x 512)
-constexpr int BC_RRL32 = 10, BC_RRL64 = 4;
+// with 10 x 1024, 8 x 768, 12 x 768, 6 x 1024, 16 x 512).  Complex128, 1024 entries:
+// 952 / 734 / 645 / 586 / 573 us per chunk at N = 7680 with 2 / 3 / 4 / 5 / 9 rows (nine
+// leave one block per CU)
+constexpr int BC_RRL32 = 10, BC_RRL64 = 5;
 
 // Tbc[m][n] += sum_k coef[k] Yw[rows[k]][n] over the list of BC row m = ml[blockIdx.y]
 __global__ __launch_bounds__(256) void bc_test_kernel(const int32_t* __restrict__ ml, const int32_t* __restrict__ mptr,
