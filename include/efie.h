@@ -159,14 +159,11 @@ int efie_assemble(efie_mesh mesh, double k_re, double k_im, double eta, int dtyp
                   void* Z, void* Z2, int parts, hipStream_t stream);
 
 /*
- * The same Z as efie_assemble (parts = 0) without atomics: the pair values of the
- * triangle pairs with source triangle q >= p (q = p halved) are written per chunk
- * of test triangles into the caller's workspace and added row by row into U, and
- * Z = U + U^T by mirror tiles, so the result is deterministic (bit-identical
- * between runs) and exactly symmetric.  Any
- * ws_bytes >= min_bytes works (chunks of ws_bytes / min_bytes test triangles);
- * full_bytes (= T x min_bytes) holds all triangles in one chunk.
- *   min_bytes = 6 N x (16 for EFIE_C128, 8 for EFIE_C64);  ws dev, 16-byte aligned.
+ * The same Z as efie_assemble (parts = 0) without atomics, deterministic (bit-identical
+ * between runs) and exactly symmetric: by owner-computes tiles, with the FP64 blocks of
+ * the ordered near pairs in the workspace, or with a larger workspace (next call) by the
+ * rows of all pair values.  min_bytes = full_bytes = max(256, near pairs x 9 x (16 for
+ * EFIE_C128, 8 for EFIE_C64));  ws dev, 16-byte aligned.
  * Errors: EFIE_ERR_ARG if ws_bytes < min_bytes.
  */
 int efie_assemble_workspace_size(efie_mesh mesh, int dtype, size_t* min_bytes, size_t* full_bytes);
@@ -429,7 +426,8 @@ int efie_solve(const void* Z, int dtype, int64_t n, const void* V, void* J, int6
  *   dev Tbc_out (may be NULL).  T_BC is accumulated without forming T_bary: the
  *   barycentric pair values of a chunk of test triangles go to workspace rows
  *   (at most 2 GiB) that are contracted with R at once.  Rows of P solve
- *   G_mix^T p = T_BC row by BiCGStab (batches of rows, column layout) to the
+ *   G_mix^T p = T_BC row by a Chebyshev iteration, or BiCGStab where that does not
+ *   apply (batches of rows, column layout) to the
  *   relative residual tol (maxit steps); *relres (host, may be NULL) gets the worst
  *   achieved.  For tol >= 1e-4 the solver's vectors are stored in complex64 (every
  *   sum, norm and update still in FP64), which bounds the attainable residual
@@ -514,7 +512,7 @@ int efie_solve_precond_ex(const void* Z, int zdt, const void* P, int pdt, int64_
  *
  * efie_calderon_cfie_assemble: M and Q into dev buffers (N x N complex128 each),
  *   optionally K_BC(k) and K_BC(k~) (raw, N x N complex128) into K_out, Kt_out;
- *   k > 0 real, kt_im <= 0; Q by BiCGStab on G_mix to tol (maxit steps; complex64
+ *   k > 0 real, kt_im <= 0; Q by the same solver on G_mix to tol (maxit BiCGStab steps; complex64
  *   vectors when tol >= 1e-4), its worst relative residual in *relres.  Needs the
  *   mesh and the Calderon tables uploaded; ws as for efie_calderon_assemble
  *   (ws_bytes from efie_calderon_sizes).  Returns EFIE_NOT_CONVERGED if Q missed tol.
