@@ -956,8 +956,8 @@ def main():
         "config": {
             "workload": f"PEC unit sphere icosphere level {args.level} (N={N} RWG), k={args.k}, "
                         f"{S} plane waves on a {args.ntheta}x{args.nphi} (theta,phi) grid, monostatic; "
-                        + ((f"mixed precision (complex64 Z, FP32 MFMA with "
-                            f"{'FP32 accumulation' if args.fp32_acc else 'FP64 flushes'}, FP64 refinement)")
+                        + ((f"mixed precision (complex64 Z, complex64 matrix-core products with "
+                            f"{'FP32 results' if args.fp32_acc else 'FP64 sums'}, FP64 refinement)")
                            if dt == P.C64 else "FP64") + "; "
                         + ("Calderon-preconditioned CGS (P = T_BC(k~) G_mix^-1 built in the step"
                            + (f", its barycentric far pairs beyond {args.cal_far_rule} h by the 3x3 rule)"

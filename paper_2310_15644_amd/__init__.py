@@ -337,7 +337,11 @@ def assemble(mesh: Mesh, k, eta: float = ETA0, dtype=C128, parts: bool = False, 
         _check(lib().efie_assemble_workspace_size(mesh._h, code, ctypes.byref(lo), ctypes.byref(full)))
         _check(lib().efie_assemble_pairs_workspace_size(mesh._h, code, ctypes.byref(lo)))
         nb = max(full.value, lo.value)
-        ws = torch.empty(nb + 256, dtype=torch.uint8, device=dev)
+        try:
+            ws = torch.empty(nb + 256, dtype=torch.uint8, device=dev)
+        except torch.OutOfMemoryError:   # the tiles need the near-pair blocks only
+            nb = full.value
+            ws = torch.empty(nb + 256, dtype=torch.uint8, device=dev)
         off = (-ws.data_ptr()) % 256
         _check(lib().efie_assemble_ws(mesh._h, k.real, k.imag, float(eta), code, _ptr(Z),
                                       ctypes.c_void_p(ws.data_ptr() + off), nb, _stream(dev)))
@@ -470,9 +474,14 @@ def zx(Z, X):
     n, S = Z.shape[0], X.shape[0]
     nb = ctypes.c_size_t()
     _check(lib().efie_zx_workspace_size(n, S, code, ctypes.byref(nb)))
-    ws = torch.empty(nb.value, dtype=torch.uint8, device=Z.device) if nb.value else None
-    _check(lib().efie_zx_ws(_ptr(Z), code, n, _ptr(X), _ptr(Y), S, _ptr(ws) if nb.value else None, nb.value,
-                            _stream(Z.device)))
+    ws = None
+    if nb.value:
+        try:
+            ws = torch.empty(nb.value, dtype=torch.uint8, device=Z.device)
+        except torch.OutOfMemoryError:   # the product without partial sums
+            pass
+    _check(lib().efie_zx_ws(_ptr(Z), code, n, _ptr(X), _ptr(Y), S, _ptr(ws) if ws is not None else None,
+                            nb.value if ws is not None else 0, _stream(Z.device)))
     return Y
 
 
