@@ -125,7 +125,7 @@ __device__ constexpr BaryTable<NP, R> bary_table{};
 // (qx, qy, qz): the point offsets of the product rule, [NP][T].
 // PRE: the source triangle's points come from pre[3][NP] already in registers
 // instead of the tables
-template <int NP, typename R, bool CK, bool PARTS, bool PRE = false, typename Emit, typename Emit2>
+template <int NP, typename R, bool CK, bool PARTS, bool PRE = false, bool ORBIT = false, typename Emit, typename Emit2>
 __device__ __forceinline__ void far_pair_rule(const DevMesh& m, const Tables<R>& tb, const R* __restrict__ qx,
                                               const R* __restrict__ qy, const R* __restrict__ qz, int p, int q,
                                               const Phase<R>& ph, const Scale& sc, Emit emit, Emit2 emit2,
@@ -134,22 +134,51 @@ __device__ __forceinline__ void far_pair_rule(const DevMesh& m, const Tables<R>&
     const R Dx = R(m.cx[p] - m.cx[q]);
     const R Dy = R(m.cy[p] - m.cy[q]);
     const R Dz = R(m.cz[p] - m.cz[q]);
-    R sx[NP], sy[NP], sz[NP];
+    // ORBIT (7 points): the source points are D1 and D2 times the vertex offsets, so
+    // that |o - s|^2 = |o|^2 + |s|^2 - 2 o.s takes 24 operations per test point, not 42 (far
+    // pairs: |o - s| is not small against |o|).  For the FP64 rows of the Calderon build
+    // (build at N = 7680: 153.2 -> 148.0 ms); the longer chain costs a matrix of 480
+    // unknowns, which one wave per SIMD computes, 4 %, and FP32 keeps the differences
+    static_assert(!ORBIT || NP == 7, "orbits of the 7-point rule");
+    R sx[ORBIT ? 1 : NP], sy[ORBIT ? 1 : NP], sz[ORBIT ? 1 : NP], uo[3][3], c1[3], c2[3];
+    if constexpr (ORBIT) {
 #pragma unroll
-    for (int b = 0; b < NP; ++b) {
-        sx[b] = PRE ? pre[0][b] : qx[b * T + q];
-        sy[b] = PRE ? pre[1][b] : qy[b * T + q];
-        sz[b] = PRE ? pre[2][b] : qz[b * T + q];
+        for (int k = 0; k < 3; ++k) {
+            uo[k][0] = tb.vx[k * T + q];
+            uo[k][1] = tb.vy[k * T + q];
+            uo[k][2] = tb.vz[k * T + q];
+            const R u2 = uo[k][0] * uo[k][0] + uo[k][1] * uo[k][1] + uo[k][2] * uo[k][2];
+            c1[k] = R(Bary<7>::D1 * Bary<7>::D1) * u2;
+            c2[k] = R(Bary<7>::D2 * Bary<7>::D2) * u2;
+        }
+    } else {
+#pragma unroll
+        for (int b = 0; b < NP; ++b) {
+            sx[b] = PRE ? pre[0][b] : qx[b * T + q];
+            sy[b] = PRE ? pre[1][b] : qy[b * T + q];
+            sz[b] = PRE ? pre[2][b] : qz[b * T + q];
+        }
     }
     R Mr[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}}, Mi[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
 #pragma unroll 1
     for (int a = 0; a < NP; ++a) {
         const R ox = Dx + qx[a * T + p], oy = Dy + qy[a * T + p], oz = Dz + qz[a * T + p];
         R gr[NP], gi[NP];
+        if constexpr (ORBIT) {
+            const R o2 = ox * ox + oy * oy + oz * oz;
+            green_far(ph, CK, o2, gr[0], gi[0]);
 #pragma unroll
-        for (int b = 0; b < NP; ++b) {
-            const R dx = ox - sx[b], dy = oy - sy[b], dz = oz - sz[b];
-            green_far(ph, CK, dx * dx + dy * dy + dz * dz, gr[b], gi[b]);
+            for (int k = 0; k < 3; ++k) {
+                const R t = ox * uo[k][0] + oy * uo[k][1] + oz * uo[k][2];
+                green_far(ph, CK, fma(R(-2.0 * Bary<7>::D1), t, o2 + c1[k]), gr[1 + k], gi[1 + k]);
+                green_far(ph, CK, fma(R(-2.0 * Bary<7>::D2), t, o2 + c2[k]), gr[4 + k], gi[4 + k]);
+            }
+        } else {
+#pragma unroll
+            for (int b = 0; b < NP; ++b) {
+                const R dx = ox - sx[b], dy = oy - sy[b], dz = oz - sz[b];
+                green_far(ph, CK, dx * dx + dy * dy + dz * dz, gr[b], gi[b]);
+            }
         }
         R sr[3], si[3];
         Bary<NP>::fold(gr, sr);
@@ -230,13 +259,13 @@ __device__ __forceinline__ void far_pair_rule(const DevMesh& m, const Tables<R>&
 
 // The far pair (p, q) by the 7x7 rule, or by the 3x3 rule where the adaptive far
 // rule is on (m.far3 > 0) and the pair is far enough.
-template <typename R, bool CK, bool PARTS, typename Emit, typename Emit2>
+template <typename R, bool CK, bool PARTS, bool ORBIT = false, typename Emit, typename Emit2>
 __device__ __forceinline__ void far_pair_emit(const DevMesh& m, const Tables<R>& tb, int p, int q, const Phase<R>& ph,
                                               const Scale& sc, Emit emit, Emit2 emit2) {
     if (m.far3 > 0.0 && far3_pair(m, p, q))
         far_pair_rule<3, R, CK, PARTS>(m, tb, tb.q3x, tb.q3y, tb.q3z, p, q, ph, sc, emit, emit2);
     else
-        far_pair_rule<NQ, R, CK, PARTS>(m, tb, tb.qx, tb.qy, tb.qz, p, q, ph, sc, emit, emit2);
+        far_pair_rule<NQ, R, CK, PARTS, false, ORBIT>(m, tb, tb.qx, tb.qy, tb.qz, p, q, ph, sc, emit, emit2);
 }
 
 // The pair (p, q) added to Z (and Z2 in parts mode) with atomics; near pairs skipped.

@@ -89,7 +89,7 @@ __device__ __forceinline__ void far_rows_block(const DevMesh& m, const Tables<R>
                 for (int j = 0; j < 3; ++j) put(i, j, R(0), R(0));
             continue;
         }
-        far_pair_emit<R, CK, false>(m, tb, p, q, ph, sc, put, put);
+        far_pair_emit<R, CK, false, sizeof(R) == 8>(m, tb, p, q, ph, sc, put, put);
     }
 }
 
