@@ -258,9 +258,11 @@ int efie_vertex_grad(efie_mesh mesh, double k, double eta, const void* J, const 
  * nrhs vectors X (nrhs, n).  X and Y have the dtype of Z.
  *   nrhs == 1: HBM-bound GEMV (accumulation in FP64 for both dtypes);
  *   nrhs > 1 : EFIE_C64 -> matrix-core (MFMA) GEMM: by default the fp16 split product
- *              (each operand in two fp16 parts, three products, sums of at most 64
- *              terms added in FP64: an FP32 product's accuracy or better), or a
- *              selected FP32 tile with FP32 accumulation; EFIE_C128 -> FP64 GEMM.
+ *              (each operand in two fp16 parts, three products, FP32 products of
+ *              the values as stored where they span too much for that, sums of at most
+ *              64 terms added in FP64: an FP32 product's accuracy or better, whatever
+ *              the range of a row), or a selected FP32 tile with FP32 accumulation;
+ *              EFIE_C128 -> FP64 GEMM.
  *              A row of X or of Z that holds a non-finite value gives non-finite
  *              results there (an infinity may give NaN).
  */

@@ -2,25 +2,36 @@
 //
 // Splitting.  A row's chunk of KC complex elements is scaled by the power of two that
 // takes its largest real or imaginary part to [2^14, 2^15); each scaled value x is
-// h + l with h the nearest fp16 number and l the nearest to the (exact) remainder:
-// |x - h - l| <= 2^-23 |x| down to 2^-17 of the chunk's largest part, below that at most
-// 2^-40 of the largest part.  A product takes three fp16 products, h h', h l' and l h',
-// each exact in the matrix core's FP32 accumulator; l l' is below 2^-22 of the product
-// and left out.  Non-finite values stay non-finite (an infinity gives NaN).
+// h + 2^-11 l with h the nearest fp16 number and l the nearest to 2^11 times the (exact)
+// remainder: within 2^-23 |x| down to 2^-27 of the chunk's largest part, and within 2^-50
+// of the largest part below that.  A product takes three fp16 products, each exact in the
+// matrix core's FP32 accumulator: h l' and l h' of the whole chunk first, then, after a
+// factor of 2^-11, h h' on top; l l' is below 2^-22 of the product and left out.
+// Non-finite values stay non-finite (an infinity gives NaN).
+// Range.  Nonzero elements (or a lane's real or imaginary parts) below 2^-27 of the
+// largest are "wide": 64 of them err by at most 2^-42 of the product of both chunks'
+// largest.  Where every element of the other chunk is above 2^-20 of its largest, one
+// term of sum |x| |z| is 2^-20 of that product and the error is below 2^-22 of the sum.
+// Where an element of it is smaller ("thin", a zero among them), the large values may
+// meet only those, so a turn with a wide and a thin chunk is multiplied as stored, on
+// the FP32 matrix cores (39.6 against 17.6 ms where every turn is).  Share of the turns on
+// icospheres, whose symmetry leaves rounding errors for zeros, Z times plane waves: 0.33 at
+// N = 1920, 0.05 at 7680, 0.01 at 30720; on a perturbed sphere and on random dipoles, none.
 // Accumulation.  The FP32 sums of one chunk (at most 64 complex terms) are scaled back
 // and added to FP64 accumulators, for complex64 and complex128 results alike.  Measured
-// against the FP64 product of the stored values (2-norm): 1.0e-7 to 1.4e-7 for orders
-// 300 to 30720, where the FP32 matrix cores give 1.6e-7 to 2.4e-7 with FP64 flushes
-// and 4.4e-7 to 6.0e-6 with FP32 sums.
+// against the FP64 product of the stored values (2-norm): 1.1e-7 for orders 300 to 30720,
+// where the FP32 matrix cores give 1.6e-7 to 2.4e-7 with FP64 flushes and 4.4e-7 to
+// 6.0e-6 with FP32 sums; 2.9e-7 of sum |x| |z| at worst for rows of 24 decades.
 //
 // Why.  The FP32 matrix cores reach 157 TFLOP/s: the planar kernels ran at 0.85 to
 // 0.95 of that, 25.8 to 28.8 ms for 30720 x 30720 times 512.  Three fp16 products take
-// 3/16 of the time of one FP32 product.  This kernel takes 14.6 ms (265 TFLOP/s of
-// complex products, 0.32 of the fp16 peak over three).  Bound by instruction issue: of
-// the cycles of a SIMD about 0.45 hold matrix instructions and 0.45 vector ones (splits,
-// scaling back), which hardly overlap, and the clock falls below 2.4 GHz under the
-// matrix load.  Three bf16 parts need no scaling but six products: 22.4 ms at 1.9 GHz.
-// Parts by mixed-precision fused multiply-adds to fp16 (half rate): 15.4 ms.
+// 3/16 of the time of one FP32 product.  This kernel takes 16.8 ms (230 TFLOP/s of
+// complex products, 0.28 of the fp16 peak over three).  Bound by instruction issue:
+// matrix instructions and vector ones (splits, tests of the range, scaling back) take
+// about half of a SIMD's cycles each and hardly overlap.  With l unscaled it took 14.3 ms,
+// but held values below 2^-16 of a chunk's largest only to 2^-39 of that, and one large
+// value in a chunk against a zero cost all digits of the others' products.
+// Three bf16 parts need no scaling but six products: 22.4 ms at 1.9 GHz.
 //
 // Layout.  Per chunk and group: the rows' h and l planes of the real and imaginary
 // parts in LDS, rows padded by 8 values (16-byte reads without bank conflicts), one
@@ -58,12 +69,27 @@ __device__ __forceinline__ uint32_t max8(float m) {
     v = dpp_max<0x4e>(v);                                          // quad_perm [2, 3, 0, 1]
     return dpp_max<0x141>(v);                                      // row_half_mirror
 }
+__device__ __forceinline__ float max_abs(float a, float b) {
+    float r;
+    asm("v_max_f32 %0, |%1|, |%2|" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ float min3(float a, float b, float c) {
+    float r;
+    asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
 // a sc and b sc (sc a power of two) in two fp16 parts each, packed: the nearest fp16
-// values, and those of the exact remainders
+// values, and those of LSCALE times the exact remainders
+constexpr float LSCALE = 2048.f;
 __device__ __forceinline__ void split2(float a, float b, float sc, halfx2& h, halfx2& l) {
     h = __builtin_convertvector(floatx2{a * sc, b * sc}, halfx2);
-    l = __builtin_convertvector(floatx2{__builtin_fmaf(a, sc, -float(h.x)), __builtin_fmaf(b, sc, -float(h.y))}, halfx2);
+    l = __builtin_convertvector(floatx2{__builtin_fmaf(a, sc, -float(h.x)) * LSCALE, __builtin_fmaf(b, sc, -float(h.y)) * LSCALE},
+                                halfx2);
 }
+// of one row's chunk: an element the two parts do not hold to 2^-23, and one so far below the
+// largest that the other operand's WIDE elements may count against it (see above); of X, of Z
+enum SplitRange { X_WIDE = 1, X_THIN = 2, Z_WIDE = 4, Z_THIN = 8 };
 
 // where the sums of a tile go: complex64 Y, the rows yrow of complex128 Y, or (a block
 // of one of several ranges of K) the workspace that split_sum_kernel adds up
@@ -89,6 +115,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, MINW) void cgemm_split_kernel(co
     constexpr int RED = WK > 1 ? (WK - 1) * GT * 16 * 16 : 0;
     constexpr int LDSB = STAGE * WK > RED ? STAGE * WK : RED;
     __shared__ __attribute__((aligned(16))) char lds[LDSB];
+    __shared__ int range_of[2];                       // SplitRange bits of a turn's chunks, of even and odd turns
     const int tid = threadIdx.x % GT;
     const int g = WK > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / GT) : 0;
     const int lane = tid & 63, w = tid >> 6;
@@ -159,12 +186,31 @@ __global__ __launch_bounds__(64 * WM * WN * WK, MINW) void cgemm_split_kernel(co
         }
     };
     // a row's chunk, scaled by the power of two that takes its largest part to [2^14, 2^15), into the planes
-    auto put = [&](_Float16* planes, int* e, int rows, int row, const floatx4u (&v)[PC]) {
-        float m = 0.f;
+    auto put = [&](_Float16* planes, int* e, int rows, int row, const floatx4u (&v)[PC], bool& wide, bool& thin) {
+        // the lane's largest real and imaginary part and its smallest element
+        float mr = 0.f, mi = 0.f, lo = __builtin_inff();
 #pragma unroll
-        for (int p = 0; p < PC; ++p)
-            m = max3_abs(max3_abs(m, v[p].x, v[p].y), v[p].z, v[p].w);
-        const int b = max(int(max8(m) >> 23), 14);
+        for (int p = 0; p < PC; ++p) {
+            mr = max3_abs(mr, v[p].x, v[p].z);
+            mi = max3_abs(mi, v[p].y, v[p].w);
+            lo = min3(lo, max_abs(v[p].x, v[p].y), max_abs(v[p].z, v[p].w));
+        }
+        lo = min3(lo, mr, mi);
+        const uint32_t mx = max8(max_abs(mr, mi));
+        const float m = __builtin_bit_cast(float, mx);
+        thin |= lo < m * 0x1p-20f;
+        if (lo < m * 0x1p-27f) {   // rare: zeros aside?
+            const float t = m * 0x1p-27f;
+            auto below = [&](float a) { wide |= a > 0.f && a < t; };
+            below(mr);
+            below(mi);
+#pragma unroll
+            for (int p = 0; p < PC; ++p) {
+                below(max_abs(v[p].x, v[p].y));
+                below(max_abs(v[p].z, v[p].w));
+            }
+        }
+        const int b = max(int(mx >> 23), 14);
         const float sc = __builtin_bit_cast(float, uint32_t(268 - b) << 23);
         if (lc == 0) e[row] = (b - 141) * (1 << 20);
 #pragma unroll
@@ -179,34 +225,77 @@ __global__ __launch_bounds__(64 * WM * WN * WK, MINW) void cgemm_split_kernel(co
             *reinterpret_cast<halfx2*>(d + 3 * rows * RS) = il;
         }
     };
-    auto lstore = [&]() {
+    auto lstore = [&](int turn) {
+        bool xw = false, xt = false, zw = false, zt = false;
 #pragma unroll
-        for (int q = 0; q < NA; ++q) put(Xs, ex, BM, lr + RP * q, ra[q]);
+        for (int q = 0; q < NA; ++q) put(Xs, ex, BM, lr + RP * q, ra[q], xw, xt);
 #pragma unroll
-        for (int q = 0; q < NB; ++q) put(Zs, ez, BN, lr + RP * q, rb[q]);
+        for (int q = 0; q < NB; ++q) put(Zs, ez, BN, lr + RP * q, rb[q], zw, zt);
+        if (__any(xt || zt)) {   // wide elements are thin ones too
+            const int f = (__any(xw) ? X_WIDE : 0) | (__any(xt) ? X_THIN : 0) | (__any(zw) ? Z_WIDE : 0) | (__any(zt) ? Z_THIN : 0);
+            if (lane == 0) atomicOr(&range_of[turn & 1], f);
+        }
+    };
+    // the same chunk as stored, rows padded by one value, over the planes
+    constexpr int RF = KC + 1;
+    float2* Xf = reinterpret_cast<float2*>(lds + g * STAGE);
+    float2* Zf = Xf + BM * RF;
+    auto rstore = [&]() {
+        auto raw = [&](float2* row, const floatx4u (&v)[PC]) {
+#pragma unroll
+            for (int p = 0; p < PC; ++p) {
+                row[2 * lc + 16 * p] = make_float2(v[p].x, v[p].y);
+                row[2 * lc + 16 * p + 1] = make_float2(v[p].z, v[p].w);
+            }
+        };
+#pragma unroll
+        for (int q = 0; q < NA; ++q) raw(Xf + (lr + RP * q) * RF, ra[q]);
+#pragma unroll
+        for (int q = 0; q < NB; ++q) raw(Zf + (lr + RP * q) * RF, rb[q]);
     };
     const int l32 = lane & 31, kh = lane >> 5;
     const _Float16* xp = Xs + (wm * 32 + l32) * RS + 8 * kh;
     const _Float16* zp = Zs + (wn * 32 + l32) * RS + 8 * kh;
     auto multiply = [&]() {
         floatx16 rr{}, ii{}, ri{};   // sum xr zr, sum xi zi, sum xr zi + xi zr
+        // h l' + l h' of every term first, then h h' on top of them
 #pragma unroll
         for (int ks = 0; ks < KC / 16; ++ks) {
+            __builtin_amdgcn_sched_barrier(0);
             halfx8 x[4], z[4];
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
                 x[s] = *reinterpret_cast<const halfx8*>(xp + s * BM * RS + 16 * ks);
                 z[s] = *reinterpret_cast<const halfx8*>(zp + s * BN * RS + 16 * ks);
             }
-            constexpr int PI_[3] = {1, 0, 0}, PJ[3] = {0, 1, 0};   // the small products first
 #pragma unroll
-            for (int t = 0; t < 3; ++t) {
-                const int i = PI_[t], j = PJ[t];
+            for (int i = 0; i < 2; ++i) {
+                const int j = 1 - i;
                 rr = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[i], z[j], rr, 0, 0, 0);
                 ri = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[i], z[2 + j], ri, 0, 0, 0);
                 ii = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[2 + i], z[2 + j], ii, 0, 0, 0);
                 ri = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[2 + i], z[j], ri, 0, 0, 0);
             }
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            rr[r] *= 1.f / LSCALE;
+            ii[r] *= 1.f / LSCALE;
+            ri[r] *= 1.f / LSCALE;
+        }
+#pragma unroll
+        for (int ks = 0; ks < KC / 16; ++ks) {
+            __builtin_amdgcn_sched_barrier(0);
+            halfx8 x[2], z[2];
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                x[s] = *reinterpret_cast<const halfx8*>(xp + 2 * s * BM * RS + 16 * ks);
+                z[s] = *reinterpret_cast<const halfx8*>(zp + 2 * s * BN * RS + 16 * ks);
+            }
+            rr = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[0], z[0], rr, 0, 0, 0);
+            ri = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[0], z[1], ri, 0, 0, 0);
+            ii = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[1], z[1], ii, 0, 0, 0);
+            ri = __builtin_amdgcn_mfma_f32_32x32x16_f16(x[1], z[0], ri, 0, 0, 0);
         }
         // the chunk's sums, scaled back, into the FP64 accumulators: 2^e as the high
         // word of a double from the exponents kept shifted
@@ -223,6 +312,26 @@ __global__ __launch_bounds__(64 * WM * WN * WK, MINW) void cgemm_split_kernel(co
             }
         }
     };
+    // the chunk of rstore on the FP32 matrix cores
+    auto multiply32 = [&]() {
+        floatx16 rr{}, ii{}, ri{};
+        const float2* xr = Xf + (wm * 32 + l32) * RF + kh;
+        const float2* zr = Zf + (wn * 32 + l32) * RF + kh;
+#pragma unroll 4
+        for (int k = 0; k < KC; k += 2) {
+            const float2 x = xr[k], z = zr[k];
+            rr = __builtin_amdgcn_mfma_f32_32x32x2f32(x.x, z.x, rr, 0, 0, 0);
+            ri = __builtin_amdgcn_mfma_f32_32x32x2f32(x.x, z.y, ri, 0, 0, 0);
+            ii = __builtin_amdgcn_mfma_f32_32x32x2f32(x.y, z.y, ii, 0, 0, 0);
+            ri = __builtin_amdgcn_mfma_f32_32x32x2f32(x.y, z.x, ri, 0, 0, 0);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            dr[r] += double(rr[r] - ii[r]);
+            di[r] += double(ri[r]);
+        }
+    };
+    if (threadIdx.x < 2) range_of[threadIdx.x] = 0;
     const int all = (n + KC - 1) / KC;
     const int c0 = OUT == OUT_PART ? int(int64_t(all) * range / ranges) : 0;
     const int nch = OUT == OUT_PART ? int(int64_t(all) * (range + 1) / ranges) : all;
@@ -231,10 +340,20 @@ __global__ __launch_bounds__(64 * WM * WN * WK, MINW) void cgemm_split_kernel(co
     for (int i = 0; i < turns; ++i) {
         const int c = c0 + g + WK * i;
         __syncthreads();
-        if (c < nch) lstore();
+        if (c < nch) lstore(i);
         __syncthreads();
+        const int f = __builtin_amdgcn_readfirstlane(range_of[i & 1]);
+        if (threadIdx.x == 0) range_of[(i + 1) & 1] = 0;   // read before this turn's barriers, set after the next one
+        const bool full = ((f & X_WIDE) && (f & Z_THIN)) || ((f & Z_WIDE) && (f & X_THIN));
+        if (full) {
+            if (c < nch) rstore();
+            __syncthreads();
+        }
         if (c + WK < nch) gload(c + WK);
-        if (c < nch) multiply();
+        if (c < nch) {
+            if (full) multiply32();
+            else multiply();
+        }
     }
     if constexpr (WK > 1) {
         // the groups' sums into group 0, in order

@@ -93,3 +93,50 @@ def test_split_special_values(split):
     Xd, Zd = X[keep].to(torch.complex128), Z.to(torch.complex128)
     bound = Xd.abs() @ Zd.abs().T.contiguous() + 1e-36
     assert float(((Y[keep].to(torch.complex128) - Xd @ Zd.T.contiguous()).abs() / bound).max()) <= 3e-6
+
+
+def wide_operands(n, m, kind, seed):
+    """Rows whose chunks hold values of very different size, the large ones against zeros: errors of the large ones' size
+    would stand out.  zero_x / zero_z: values over 24 decades against a matrix of mostly zeros; one: a single 1e9 in every
+    chunk of Z against zeros of X; noise: 1e-17 where X would be zero; parts: Z with real parts ten decades below, X real."""
+    rng = np.random.default_rng(seed)
+    Z = rng.standard_normal((n, n)) + 1j * rng.standard_normal((n, n))
+    X = rng.standard_normal((m, n)) + 1j * rng.standard_normal((m, n))
+    if kind == "zero_x":
+        Z *= 10.0 ** rng.uniform(-12, 12, (n, n))
+        X *= rng.random((m, n)) < 0.1
+    elif kind == "zero_z":
+        X *= 10.0 ** rng.uniform(-12, 12, (m, n))
+        Z *= rng.random((n, n)) < 0.1
+    elif kind == "one":
+        Z[:, 7::32] *= 1e9
+        X[:, 7::32] = 0.0
+    elif kind == "noise":
+        Z[:, 7::32] *= 1e9
+        Z[:, 9::32] *= 1e-9
+        X[:, 7::32] *= 1e-17
+    else:
+        Z = 1e-10 * Z.real + 1j * Z.imag
+        X = X.real + 0j
+    return (torch.as_tensor(Z, device="cuda").to(torch.complex64), torch.as_tensor(X, device="cuda").to(torch.complex64))
+
+
+# the four tiles in the block and the three over ranges of K, ragged rows, unknowns and K.  A chunk that the two parts do
+# not hold takes FP32 products: 128 terms of a part, 2^-24 each of the partial sum at most, 8e-6 of sum |z| |x| (of each
+# part's own terms for "parts"), and the split bound above elsewhere.
+@pytest.mark.parametrize("kind", ["zero_x", "zero_z", "one", "noise", "parts"])
+@pytest.mark.parametrize("n,m", [(33, 32), (65, 65), (129, 2), (1025, 97), (2050, 33), (4097, 40), (8230, 20)])
+def test_split_wide_range(split, n, m, kind):
+    Z, X = wide_operands(n, m, kind, 13 * n + m)
+    Zd, Xd = Z.to(torch.complex128), X.to(torch.complex128)
+    ref = Xd @ Zd.T.contiguous()
+    if kind == "parts":
+        bound = torch.complex(Xd.real.abs() @ Zd.real.abs().T.contiguous(), Xd.real.abs() @ Zd.imag.abs().T.contiguous())
+        ratio = lambda e: max(float((e.real.abs() / bound.real).max()), float((e.imag.abs() / bound.imag).max()))
+    else:
+        bound = Xd.abs() @ Zd.abs().T.contiguous()
+        ratio = lambda e: float((e.abs() / bound.clamp(min=1e-300)).max())
+    for Y in (P.zx(Z, X).to(torch.complex128), P.zx_flush64(Z, Xd)):
+        err = ratio(Y - ref)
+        flush(f"split product of wide rows {kind} n={n} nrhs={m}: {err:.1e}")
+        assert err <= 8e-6
