@@ -109,14 +109,15 @@ __device__ __forceinline__ A nrm(const V3<A>& a) { return root(dot(a, a)); }
 
 // Closed-form I0 = int 1/R and I1 = int r'/R (Wilton et al. 1984) over the source triangle u[3]
 // (counter-clockwise, positions relative to any common origin, unit normal n) and the
-// observation point r, one of the two dual.  self: r lies on the triangle, where the
-// slope of |d| is one of two; with r moving and with the triangle moving the two cancel,
-// so none is taken.
+// observation point r, one of the two dual.  Where r lies in the triangle's plane, up to
+// rounding, the slope of |d| is one of two, whose mean is taken: none.  (It counts on the
+// triangle alone, for its own points or those of a body that touches it: off the triangle
+// the angles of the edges add up to zero.)
 template <typename TR, typename TU>
-__device__ __forceinline__ void potentials_d(const V3<TR>& r, V3<TU> (&u)[3], const V3<TU>& n, double h, bool self,
-                                             Dual& I0, V3<Dual>& I1) {
+__device__ __forceinline__ void potentials_d(const V3<TR>& r, V3<TU> (&u)[3], const V3<TU>& n, double h, Dual& I0,
+                                             V3<Dual>& I1) {
     const Dual d = dot(sub(r, u[0]), n);
-    const Dual ad = self ? Dual{0, 0} : dabs(d);
+    const Dual ad = fabs(d.v) <= 1e-14 * h ? Dual{0, 0} : dabs(d);
     const V3<Dual> rho = sub(r, scl(n, d));
     I0 = Dual{0, 0};
     I1 = {I0, I0, I0};
@@ -174,8 +175,12 @@ __global__ __launch_bounds__(256, 2) void grad_far_kernel(DevMesh m, double kr, 
 #pragma unroll
     for (int k = 0; k < 9; ++k) out[k] = 0.0;
     if (q < T) {
-        const double smooth = is_near(m, t, q) ? 0.0 : 1.0;   // 1 of the far kernel's cosine
-        const int same = t == q ? 0 : 8;   // a + same == b: one point, R = 0 (rounded apart here)
+        const bool near = is_near(m, t, q);
+        const double smooth = near ? 0.0 : 1.0;   // 1 of the far kernel's cosine
+        // Points of near triangles that coincide (of one triangle, or where two bodies touch) are
+        // rounded apart here, by some 6 units of the last place of h; and below R = 2 eps / k
+        // the rounding of the slope passes the slope itself, k^2 / 2.  R = 0 up to there.
+        const double r0 = 2e-15 * (m.hm[t] + 1.0 / kr), zero2 = near ? r0 * r0 : -1.0;
         const Phase<double> ph = make_phase<double>(0.5 * kr, 0.0);
         // a triangle's vertex offsets, s_i l_i and the two weighted coefficients
         auto corners = [&](int tri, double (&u)[3][3], double (&len)[3], C (&wl)[3], C (&wj)[3]) {
@@ -247,8 +252,8 @@ __global__ __launch_bounds__(256, 2) void grad_far_kernel(DevMesh m, double kr, 
                 const double f = b == 0 ? 0.0 : (b < 4 ? Bary<7>::D1 : Bary<7>::D2);
                 const double* u = uq[b == 0 ? 0 : (b - 1) % 3];
                 const double dx = o[0] - f * u[0], dy = o[1] - f * u[1], dz = o[2] - f * u[2];
-                const bool zero = a + same == b;
                 const double R2 = dx * dx + dy * dy + dz * dz;
+                const bool zero = R2 <= zero2;
                 const double Ri = zero ? 0.0 : rsqrt_fast(R2);
                 double s2, c2_;
                 sincos_quarter(R2 * Ri, ph.khi, ph.klo, s2, c2_);   // of k R / 2
@@ -440,7 +445,7 @@ __global__ __launch_bounds__(256, 2) void grad_near_kernel(DevMesh m, Scale sc, 
             V3<double> n = crs(sub(Pq[1], Pq[0]), sub(Pq[2], Pq[0]));
             const double i2a = 1.0 / nrm(n);
             n = scl(n, i2a);
-            potentials_d(rt, Pq, n, m.hm[q], t == q, I0, I1);
+            potentials_d(rt, Pq, n, m.hm[q], I0, I1);
             Dual uw = {0, 0};
 #pragma unroll
             for (int i = 0; i < 3; ++i) uw = uw + l[i] * dot(sub(rt, Pt[i]), sub(scl(I1, a[i]), scl(v[i], I0)));
@@ -450,7 +455,7 @@ __global__ __launch_bounds__(256, 2) void grad_near_kernel(DevMesh m, Scale sc, 
             V3<Dual> n = crs(sub(Pt[1], Pt[0]), sub(Pt[2], Pt[0]));
             const Dual i2a = inverse(nrm(n));
             n = scl(n, i2a);
-            potentials_d(rq, Pt, n, m.hm[t], t == q, I0, I1);
+            potentials_d(rq, Pt, n, m.hm[t], I0, I1);
             Dual uw = {0, 0};
 #pragma unroll
             for (int i = 0; i < 3; ++i) uw = uw + l[i] * dot(sub(I1, scl(Pt[i], I0)), sub(scl(rq, a[i]), v[i]));

@@ -107,6 +107,37 @@ def test_operator_term_by_pair_class(dev, n, axes, k):
         assert err <= 1e-10
 
 
+@pytest.mark.parametrize("k", [0.3, 4.0])
+@pytest.mark.parametrize("turned", [False, True])
+def test_operator_term_of_touching_bodies(dev, turned, k):
+    """Two tetrahedra of their own vertices with one face in common: near triangles whose points coincide (up to rounding in
+    the turned and shifted pair, whose gradient is the turned one).  In the oracle's coordinates the common points are equal
+    and in one plane, so that its terms take R = 0 and no slope of |d| there.
+
+    Tolerance: as for the pairs of one mesh above, 1e-10."""
+    v = np.array([[0, 0, 0], [1, 0, 0], [0, 1, 0], [0.2, 0.3, 1], [0, 0, 0], [1, 0, 0], [0, 1, 0], [0.3, 0.25, -0.75]])
+    f = np.array([[0, 2, 1], [0, 1, 3], [1, 2, 3], [2, 0, 3], [4, 5, 6], [5, 4, 7], [6, 5, 7], [4, 6, 7]], dtype=np.int32)
+    kh, pol = synth.planewave_x_along_minus_z()
+    dirs = synth.uniform_directions(2, seed=1)
+    prob = ograd.Problem(rwg.build(v, f), k, kh[0], pol[0], dirs)
+    Q, shift = np.eye(3), np.zeros(3)
+    if turned:
+        Q = np.linalg.qr(np.random.default_rng(4).standard_normal((3, 3)))[0]
+        Q *= np.linalg.det(Q)
+        shift = np.array([0.3, -0.7, 0.1])
+    mesh = P.Mesh(v @ Q.T + shift, f).upload(dev)
+    rng = np.random.default_rng(8)
+    lam, j = (rng.standard_normal(mesh.n) + 1j * rng.standard_normal(mesh.n) for _ in range(2))
+    W = np.zeros((2, 2), dtype=np.complex128)
+    rad, exc, op = ograd.term_gradients(prob, v, j, lam, W)
+    zero = _c(np.zeros(mesh.n), dev)
+    args = (_c(W, dev), dirs, Q @ prob.khat, Q @ prob.pol)
+    g = P.vertex_grad(mesh, k, _c(j, dev), _c(lam, dev), *args) - P.vertex_grad(mesh, k, zero, _c(lam, dev), *args)
+    err = _rel(g.cpu().numpy(), op @ Q.T)
+    flush(f"operator term of touching bodies turned={turned} k={k}: rel error {err:.2e}")
+    assert err <= 1e-10
+
+
 @pytest.mark.parametrize("shape", [(1, 32, 2), (3, 700, 2)])
 def test_farfield_objective(dev, shape):
     """J = sum |F|^2 and W = conj(F) from the library against their definitions on
