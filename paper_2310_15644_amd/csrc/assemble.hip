@@ -73,7 +73,7 @@ __global__ __launch_bounds__(128) void near_pairs_kernel(DevMesh m, double kr, d
 
 // the pair rows of a chunk of test triangles (the first step of the Calderon
 // build): the bodies live in rows_kernels.h
-template <typename R, bool CK, bool UPPER>
+template <typename R, bool CK, bool UPPER, bool ORBIT>
 __global__ __launch_bounds__(FAR_BLOCK, sizeof(R) == 4 ? 3 : 2) void far_rows_kernel(DevMesh m, Tables<R> tb, Phase<R> ph, Scale sc,
                                                              typename Cplx<R>::T* __restrict__ W, int c0, int np,
                                                              int nqblk) {
@@ -83,7 +83,7 @@ __global__ __launch_bounds__(FAR_BLOCK, sizeof(R) == 4 ? 3 : 2) void far_rows_ke
     const int xcd = int(blockIdx.x) & 7, idx = int(blockIdx.x) >> 3;
     const int per = nblk >> 3, rem = nblk & 7;
     const int logical = xcd * per + min(xcd, rem) + idx;
-    far_rows_block<R, CK, UPPER>(m, tb, ph, sc, W, c0, np, nqblk, logical);
+    far_rows_block<R, CK, UPPER, ORBIT>(m, tb, ph, sc, W, c0, np, nqblk, logical);
 }
 
 template <typename R>
@@ -349,18 +349,24 @@ void pair_rows_chunk(const DevMesh& m, double kr, double ki, double eta, int dty
         const Phase<R> ph = make_phase<R>(kr, ki);
         C2* w = static_cast<C2*>(W);
         auto far = [&](hipStream_t st) {
-            if (ck && upper)
-                hipLaunchKernelGGL((far_rows_kernel<R, true, true>), g1, dim3(FAR_BLOCK), 0, st, m, tables_of<R>(m),
-                                   ph, sc, w, c0, np, nqblk);
-            else if (ck)
-                hipLaunchKernelGGL((far_rows_kernel<R, true, false>), g1, dim3(FAR_BLOCK), 0, st, m, tables_of<R>(m),
-                                   ph, sc, w, c0, np, nqblk);
-            else if (upper)
-                hipLaunchKernelGGL((far_rows_kernel<R, false, true>), g1, dim3(FAR_BLOCK), 0, st, m, tables_of<R>(m),
-                                   ph, sc, w, c0, np, nqblk);
-            else
-                hipLaunchKernelGGL((far_rows_kernel<R, false, false>), g1, dim3(FAR_BLOCK), 0, st, m, tables_of<R>(m),
-                                   ph, sc, w, c0, np, nqblk);
+            auto launch = [&](auto orbit) {
+                constexpr bool O = decltype(orbit)::value;
+                if (ck && upper)
+                    hipLaunchKernelGGL((far_rows_kernel<R, true, true, O>), g1, dim3(FAR_BLOCK), 0, st, m,
+                                       tables_of<R>(m), ph, sc, w, c0, np, nqblk);
+                else if (ck)
+                    hipLaunchKernelGGL((far_rows_kernel<R, true, false, O>), g1, dim3(FAR_BLOCK), 0, st, m,
+                                       tables_of<R>(m), ph, sc, w, c0, np, nqblk);
+                else if (upper)
+                    hipLaunchKernelGGL((far_rows_kernel<R, false, true, O>), g1, dim3(FAR_BLOCK), 0, st, m,
+                                       tables_of<R>(m), ph, sc, w, c0, np, nqblk);
+                else
+                    hipLaunchKernelGGL((far_rows_kernel<R, false, false, O>), g1, dim3(FAR_BLOCK), 0, st, m,
+                                       tables_of<R>(m), ph, sc, w, c0, np, nqblk);
+            };
+            constexpr bool DP = sizeof(R) == 8;
+            if (DP && orbit_distances(m.nf)) launch(std::integral_constant<bool, DP>{});
+            else launch(std::integral_constant<bool, false>{});
         };
         auto near = [&](hipStream_t st) {
             hipLaunchKernelGGL((near_rows_kernel<R>), dim3(unsigned((int64_t(e1 - e0) * NEAR_G + 127) / 128)), dim3(128),

@@ -118,6 +118,12 @@ struct BaryTable {
 template <int NP, typename R>
 __device__ constexpr BaryTable<NP, R> bary_table{};
 
+// Far pairs of near factor nf: the centroids are nf h apart, h the larger longest edge, and a
+// point is up to D2 2/3 h = 0.47 h from its centroid, so that with nf >= 1.5 |o - s| >= 0.57 h and
+// (|o| + |s|)^2 <= 6.9 |o - s|^2; with 2, the default, 3.5.  Below, triangles that share no vertex
+// may be any fraction of h apart.
+inline bool orbit_distances(double nf) { return nf >= 1.5; }
+
 // The pair (p, q) of one mesh (not near): the NP x NP Green's function moments in
 // barycentric form and the nine half-function products.  emit(i, j, zr, zi)
 // receives the Z contribution of test edge i of p and source edge j of q (PARTS:
@@ -135,8 +141,9 @@ __device__ __forceinline__ void far_pair_rule(const DevMesh& m, const Tables<R>&
     const R Dy = R(m.cy[p] - m.cy[q]);
     const R Dz = R(m.cz[p] - m.cz[q]);
     // ORBIT (7 points): the source points are D1 and D2 times the vertex offsets, so
-    // that |o - s|^2 = |o|^2 + |s|^2 - 2 o.s takes 24 operations per test point, not 42 (far
-    // pairs: |o - s| is not small against |o|).  For the FP64 rows of the Calderon build
+    // that |o - s|^2 = |o|^2 + |s|^2 - 2 o.s takes 24 operations per test point, not 42.  It
+    // loses (|o| + |s|)^2 / |o - s|^2 units of the last place: for meshes whose near factor
+    // keeps the points of far pairs apart (orbit_distances).  For the FP64 rows of the Calderon build
     // (build at N = 7680: 153.2 -> 148.0 ms); the longer chain costs a matrix of 480
     // unknowns, which one wave per SIMD computes, 4 %, and FP32 keeps the differences
     static_assert(!ORBIT || NP == 7, "orbits of the 7-point rule");

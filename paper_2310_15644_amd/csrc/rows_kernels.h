@@ -54,7 +54,8 @@ __host__ __device__ inline Tables<float> tables_of<float>(const DevMesh& m) {
 // unwritten and those of near pairs to the near rows (the reader takes only the
 // entries of triangles q >= p and restores the other half from the symmetry of
 // the operator).
-template <typename R, bool CK, bool UPPER>
+// (ORBIT: far_pair_rule)
+template <typename R, bool CK, bool UPPER, bool ORBIT>
 __device__ __forceinline__ void far_rows_block(const DevMesh& m, const Tables<R>& tb, const Phase<R>& ph, const Scale& sc,
                                                typename Cplx<R>::T* __restrict__ W, int c0, int np, int nqblk,
                                                int logical) {
@@ -89,7 +90,7 @@ __device__ __forceinline__ void far_rows_block(const DevMesh& m, const Tables<R>
                 for (int j = 0; j < 3; ++j) put(i, j, R(0), R(0));
             continue;
         }
-        far_pair_emit<R, CK, false, sizeof(R) == 8>(m, tb, p, q, ph, sc, put, put);
+        far_pair_emit<R, CK, false, ORBIT>(m, tb, p, q, ph, sc, put, put);
     }
 }
 

@@ -131,6 +131,27 @@ def test_gram_solve_residuals(dev, n, axes, tol, maxit):
     assert res <= tol + (1e-4 if tol >= 1e-4 else 2e-13)
 
 
+@pytest.mark.parametrize("kt_im", [0.0, -0.4])
+def test_rows_of_close_sheets(dev, kt_im):
+    """Two tetrahedra with parallel faces 2^-18 apart and a near factor that leaves them far pairs: the rows' distances of
+    facing points come from differences of coordinates.
+
+    Tolerance: those hold 2^-18 to 2^-53 of coordinates up to 1 (1.2e-10 for four roundings), here and in the oracle, in
+    every one of the sum's values: 1e-9 of the largest entry."""
+    gap = 2.0 ** -18
+    a = np.array([[0, 0, 0], [1, 0, 0], [0, 1, 0], [0.2, 0.3, -1]])
+    v = np.concatenate([a, a * [1, 1, -1] + [0, 0, gap]])
+    fa = np.array([[0, 1, 2], [1, 0, 3], [2, 1, 3], [0, 2, 3]], dtype=np.int32)
+    f = np.concatenate([fa, fa[:, [0, 2, 1]] + 4])
+    nf, kt = 1e-6, complex(1.0, kt_im)
+    ref = ocal.Calderon(rwg.build(v, f), 1.0, kt, near_factor=nf).Tbc
+    m = P.Mesh(v, f, near_factor=nf).upload(dev)
+    _, T = P.Calderon(m).upload(dev).assemble(kt, with_tbc=True)
+    err = rel_max(T.cpu().numpy(), ref)
+    flush(f"rows of close sheets k~={kt}: rel error {err:.2e}")
+    assert err <= 1e-9
+
+
 @pytest.mark.parametrize("fp32_acc", [False, True])
 def test_calderon_c64_bary_and_mixed_solve(dev, fp32_acc):
     """Level 3 (N = 1920), k = 3, 16 plane waves: P from FP32 barycentric far pairs
