@@ -73,8 +73,11 @@ __global__ __launch_bounds__(128) void near_pairs_kernel(DevMesh m, double kr, d
 
 // the pair rows of a chunk of test triangles (the first step of the Calderon
 // build): the bodies live in rows_kernels.h
-template <typename R, bool CK, bool UPPER, bool ORBIT>
-__global__ __launch_bounds__(FAR_BLOCK, sizeof(R) == 4 ? 3 : 2) void far_rows_kernel(DevMesh m, Tables<R> tb, Phase<R> ph, Scale sc,
+// (Complex64, level 5, tol 1e-3, whole build with the tables reread and three waves per SIMD / kept
+// and two: 951 / 996 ms with the 7 x 7 rule throughout, 881 / 846 ms with far rule 4, whose 3 x 3 pairs
+// have a fifth of the operations for the same tables.)
+template <typename R, bool CK, bool UPPER, bool ORBIT, bool KEEP>
+__global__ __launch_bounds__(FAR_BLOCK, sizeof(R) == 4 && !KEEP ? 3 : 2) void far_rows_kernel(DevMesh m, Tables<R> tb, Phase<R> ph, Scale sc,
                                                              typename Cplx<R>::T* __restrict__ W, int c0, int np,
                                                              int nqblk) {
     // blocks are dealt to the 8 XCDs round-robin: remap so that each XCD runs the
@@ -83,7 +86,7 @@ __global__ __launch_bounds__(FAR_BLOCK, sizeof(R) == 4 ? 3 : 2) void far_rows_ke
     const int xcd = int(blockIdx.x) & 7, idx = int(blockIdx.x) >> 3;
     const int per = nblk >> 3, rem = nblk & 7;
     const int logical = xcd * per + min(xcd, rem) + idx;
-    far_rows_block<R, CK, UPPER, ORBIT>(m, tb, ph, sc, W, c0, np, nqblk, logical);
+    far_rows_block<R, CK, UPPER, ORBIT, KEEP>(m, tb, ph, sc, W, c0, np, nqblk, logical);
 }
 
 template <typename R>
@@ -349,24 +352,27 @@ void pair_rows_chunk(const DevMesh& m, double kr, double ki, double eta, int dty
         const Phase<R> ph = make_phase<R>(kr, ki);
         C2* w = static_cast<C2*>(W);
         auto far = [&](hipStream_t st) {
-            auto launch = [&](auto orbit) {
-                constexpr bool O = decltype(orbit)::value;
+            auto launch = [&](auto orbit, auto keep) {
+                constexpr bool O = decltype(orbit)::value, K = decltype(keep)::value;
                 if (ck && upper)
-                    hipLaunchKernelGGL((far_rows_kernel<R, true, true, O>), g1, dim3(FAR_BLOCK), 0, st, m,
+                    hipLaunchKernelGGL((far_rows_kernel<R, true, true, O, K>), g1, dim3(FAR_BLOCK), 0, st, m,
                                        tables_of<R>(m), ph, sc, w, c0, np, nqblk);
                 else if (ck)
-                    hipLaunchKernelGGL((far_rows_kernel<R, true, false, O>), g1, dim3(FAR_BLOCK), 0, st, m,
+                    hipLaunchKernelGGL((far_rows_kernel<R, true, false, O, K>), g1, dim3(FAR_BLOCK), 0, st, m,
                                        tables_of<R>(m), ph, sc, w, c0, np, nqblk);
                 else if (upper)
-                    hipLaunchKernelGGL((far_rows_kernel<R, false, true, O>), g1, dim3(FAR_BLOCK), 0, st, m,
+                    hipLaunchKernelGGL((far_rows_kernel<R, false, true, O, K>), g1, dim3(FAR_BLOCK), 0, st, m,
                                        tables_of<R>(m), ph, sc, w, c0, np, nqblk);
                 else
-                    hipLaunchKernelGGL((far_rows_kernel<R, false, false, O>), g1, dim3(FAR_BLOCK), 0, st, m,
+                    hipLaunchKernelGGL((far_rows_kernel<R, false, false, O, K>), g1, dim3(FAR_BLOCK), 0, st, m,
                                        tables_of<R>(m), ph, sc, w, c0, np, nqblk);
             };
-            constexpr bool DP = sizeof(R) == 8;
-            if (DP && orbit_distances(m.nf)) launch(std::integral_constant<bool, DP>{});
-            else launch(std::integral_constant<bool, false>{});
+            constexpr std::false_type no{};
+            constexpr std::bool_constant<sizeof(R) == 8> fp64{};
+            constexpr std::bool_constant<sizeof(R) == 4> fp32{};
+            if (fp64 && orbit_distances(m.nf)) launch(fp64, no);
+            else if (fp32 && m.far3 > 0.0) launch(no, fp32);
+            else launch(no, no);
         };
         auto near = [&](hipStream_t st) {
             hipLaunchKernelGGL((near_rows_kernel<R>), dim3(unsigned((int64_t(e1 - e0) * NEAR_G + 127) / 128)), dim3(128),

@@ -69,10 +69,9 @@ __device__ __forceinline__ void atomic_add_c<float>(void* Z, size_t idx, float r
 }
 
 // -------------------------------------------------------- far-pair kernel
-// The two product rules in barycentric form.  The points of the 7-point rule are
-// the centroid and two orbits (1 - 2 b, b, b) and permutations, those of the
-// 3-point rule one orbit; the weight times barycentric coordinate k of a point is
-// then a constant, and the moments
+// The 7-point rule in barycentric form.  Its points are the centroid and two orbits
+// (1 - 2 b, b, b) and permutations; the weight times barycentric coordinate k of a
+// point is then a constant, and the moments
 //   M_kl = sum_ab w_a lambda_k(a) w_b lambda_l(b) G_ab
 // take the sums of an orbit first (13 operations per seven Green's functions and
 // part, against 28 with Cartesian moments and weights of the triangle).
@@ -95,17 +94,6 @@ struct Bary<7> {
         return a == 0 ? W0 / 3.0 : (a < 4 ? W1 * (B1 + (k == a - 1 ? D1 : 0.0)) : W2 * (B2 + (k == a - 4 ? D2 : 0.0)));
     }
 };
-template <>
-struct Bary<3> {
-    template <typename R>
-    static __device__ __forceinline__ void fold(const R (&g)[3], R (&s)[3]) {
-        const R t = R(1.0 / 18.0) * (g[0] + g[1] + g[2]);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) s[k] = t + R(1.0 / 6.0) * g[k];
-    }
-    static constexpr double coef(int a, int k) { return 1.0 / 18.0 + (k == a ? 1.0 / 6.0 : 0.0); }
-};
-
 // the coefficients as a table, read with scalar loads by the (uniform) test point
 template <int NP, typename R>
 struct BaryTable {
@@ -124,8 +112,8 @@ __device__ constexpr BaryTable<NP, R> bary_table{};
 // may be any fraction of h apart.
 inline bool orbit_distances(double nf) { return nf >= 1.5; }
 
-// The pair (p, q) of one mesh (not near): the NP x NP Green's function moments in
-// barycentric form and the nine half-function products.  emit(i, j, zr, zi)
+// The pair (p, q) of one mesh (not near): the NP x NP Green's function moments (NP = 7
+// in barycentric form, 3) and the nine half-function products.  emit(i, j, zr, zi)
 // receives the Z contribution of test edge i of p and source edge j of q (PARTS:
 // zr, zi are the T_A part and emit2 gets the T_Phi part).
 // (qx, qy, qz): the point offsets of the product rule, [NP][T].
@@ -166,74 +154,122 @@ __device__ __forceinline__ void far_pair_rule(const DevMesh& m, const Tables<R>&
             sz[b] = PRE ? pre[2][b] : qz[b * T + q];
         }
     }
-    R Mr[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}}, Mi[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
-#pragma unroll 1
-    for (int a = 0; a < NP; ++a) {
-        const R ox = Dx + qx[a * T + p], oy = Dy + qy[a * T + p], oz = Dz + qz[a * T + p];
-        R gr[NP], gi[NP];
-        if constexpr (ORBIT) {
-            const R o2 = ox * ox + oy * oy + oz * oz;
-            green_far(ph, CK, o2, gr[0], gi[0]);
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                const R t = ox * uo[k][0] + oy * uo[k][1] + oz * uo[k][2];
-                green_far(ph, CK, fma(R(-2.0 * Bary<7>::D1), t, o2 + c1[k]), gr[1 + k], gi[1 + k]);
-                green_far(ph, CK, fma(R(-2.0 * Bary<7>::D2), t, o2 + c2[k]), gr[4 + k], gi[4 + k]);
-            }
-        } else {
-#pragma unroll
-            for (int b = 0; b < NP; ++b) {
-                const R dx = ox - sx[b], dy = oy - sy[b], dz = oz - sz[b];
-                green_far(ph, CK, dx * dx + dy * dy + dz * dz, gr[b], gi[b]);
-            }
-        }
-        R sr[3], si[3];
-        Bary<NP>::fold(gr, sr);
-        Bary<NP>::fold(gi, si);
-        const R(&ca)[3] = bary_table<NP, R>.c[a];
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-#pragma unroll
-            for (int l = 0; l < 3; ++l) {
-                Mr[k][l] += ca[k] * sr[l];
-                Mi[k][l] += ca[k] * si[l];
-            }
-    }
-    // nine half-function products from M0 = sum M_kl, Md = sum M_kl v_k,
-    // Md' = sum M_kl v'_l and Mdd' = sum M_kl v_k . v'_l (vertex offsets)
-    R up[3][3], uq[3][3], cq[3], gq[3];
-    const R area2 = (tb.qw[p] * tb.qw[q]) * R(1.0 / (Bary<7>::W0 * Bary<7>::W0));   // the areas' product
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-        uq[j][0] = tb.vx[j * T + q];
-        uq[j][1] = tb.vy[j * T + q];
-        uq[j][2] = tb.vz[j * T + q];
-        cq[j] = tb.cf[j * T + q] * area2;
-        gq[j] = tb.dv[j * T + q] * area2;
-        up[j][0] = tb.vx[j * T + p];
-        up[j][1] = tb.vy[j * T + p];
-        up[j][2] = tb.vz[j * T + p];
-    }
+    // nine half-function products from M0 = sum G, Md = sum G d_a, Md' = sum G d'_b and
+    // Mdd' = sum G d_a . d'_b, weighted (d, d' the points' offsets from the centroids)
     R m0r = 0, m0i = 0, mmr = 0, mmi = 0;
     R mdr[3] = {0, 0, 0}, mdi[3] = {0, 0, 0}, mpr[3] = {0, 0, 0}, mpi[3] = {0, 0, 0};
+    R up[3][3], uq[3][3], cq[3], gq[3];
+    // the areas' product (and the weights, equal, of the 3-point rule)
+    const R area2 = (tb.qw[p] * tb.qw[q]) * R((NP == 3 ? 1.0 / 9.0 : 1.0) / (Bary<7>::W0 * Bary<7>::W0));
+    auto corners = [&]() {
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        const R rr = Mr[k][0] + Mr[k][1] + Mr[k][2], ri = Mi[k][0] + Mi[k][1] + Mi[k][2];
-        const R cr = Mr[0][k] + Mr[1][k] + Mr[2][k], ci = Mi[0][k] + Mi[1][k] + Mi[2][k];
-        m0r += rr;
-        m0i += ri;
+        for (int j = 0; j < 3; ++j) {
+            uq[j][0] = tb.vx[j * T + q];
+            uq[j][1] = tb.vy[j * T + q];
+            uq[j][2] = tb.vz[j * T + q];
+            cq[j] = tb.cf[j * T + q] * area2;
+            gq[j] = tb.dv[j * T + q] * area2;
+            up[j][0] = tb.vx[j * T + p];
+            up[j][1] = tb.vy[j * T + p];
+            up[j][2] = tb.vz[j * T + p];
+        }
+    };
+    if constexpr (NP == 3) {
+        // equal weights: sums over a point's row and column of the 3 x 3 table, 111
+        // operations where folds into M_kl take 200
+        R cr[3] = {0, 0, 0}, ci[3] = {0, 0, 0};
+#pragma unroll 1
+        for (int a = 0; a < 3; ++a) {
+            const R ax = qx[a * T + p], ay = qy[a * T + p], az = qz[a * T + p];
+            const R ox = Dx + ax, oy = Dy + ay, oz = Dz + az;
+            R rr = 0, ri = 0;
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            mdr[d] += rr * up[k][d];
-            mdi[d] += ri * up[k][d];
-            mpr[d] += cr * uq[k][d];
-            mpi[d] += ci * uq[k][d];
+            for (int b = 0; b < 3; ++b) {
+                const R dx = ox - sx[b], dy = oy - sy[b], dz = oz - sz[b];
+                R gr, gi;
+                green_far(ph, CK, dx * dx + dy * dy + dz * dz, gr, gi);
+                rr += gr;
+                ri += gi;
+                cr[b] += gr;
+                ci[b] += gi;
+                const R dot = ax * sx[b] + ay * sy[b] + az * sz[b];
+                mmr += gr * dot;
+                mmi += gi * dot;
+            }
+            m0r += rr;
+            m0i += ri;
+            const R av[3] = {ax, ay, az};
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                mdr[d] += rr * av[d];
+                mdi[d] += ri * av[d];
+            }
         }
 #pragma unroll
-        for (int l = 0; l < 3; ++l) {
-            const R dot = up[k][0] * uq[l][0] + up[k][1] * uq[l][1] + up[k][2] * uq[l][2];
-            mmr += Mr[k][l] * dot;
-            mmi += Mi[k][l] * dot;
+        for (int b = 0; b < 3; ++b) {
+            const R sv[3] = {sx[b], sy[b], sz[b]};
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                mpr[d] += cr[b] * sv[d];
+                mpi[d] += ci[b] * sv[d];
+            }
+        }
+        corners();
+    } else {
+        R Mr[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}}, Mi[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+#pragma unroll 1
+        for (int a = 0; a < 7; ++a) {
+            const R ox = Dx + qx[a * T + p], oy = Dy + qy[a * T + p], oz = Dz + qz[a * T + p];
+            R gr[7], gi[7];
+            if constexpr (ORBIT) {
+                const R o2 = ox * ox + oy * oy + oz * oz;
+                green_far(ph, CK, o2, gr[0], gi[0]);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    const R t = ox * uo[k][0] + oy * uo[k][1] + oz * uo[k][2];
+                    green_far(ph, CK, fma(R(-2.0 * Bary<7>::D1), t, o2 + c1[k]), gr[1 + k], gi[1 + k]);
+                    green_far(ph, CK, fma(R(-2.0 * Bary<7>::D2), t, o2 + c2[k]), gr[4 + k], gi[4 + k]);
+                }
+            } else {
+#pragma unroll
+                for (int b = 0; b < 7; ++b) {
+                    const R dx = ox - sx[b], dy = oy - sy[b], dz = oz - sz[b];
+                    green_far(ph, CK, dx * dx + dy * dy + dz * dz, gr[b], gi[b]);
+                }
+            }
+            R sr[3], si[3];
+            Bary<7>::fold(gr, sr);
+            Bary<7>::fold(gi, si);
+            const R(&ca)[3] = bary_table<7, R>.c[a];
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+#pragma unroll
+                for (int l = 0; l < 3; ++l) {
+                    Mr[k][l] += ca[k] * sr[l];
+                    Mi[k][l] += ca[k] * si[l];
+                }
+        }
+        corners();
+        // offsets as barycentric sums of the vertex offsets
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const R rr = Mr[k][0] + Mr[k][1] + Mr[k][2], ri = Mi[k][0] + Mi[k][1] + Mi[k][2];
+            const R cr = Mr[0][k] + Mr[1][k] + Mr[2][k], ci = Mi[0][k] + Mi[1][k] + Mi[2][k];
+            m0r += rr;
+            m0i += ri;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                mdr[d] += rr * up[k][d];
+                mdi[d] += ri * up[k][d];
+                mpr[d] += cr * uq[k][d];
+                mpi[d] += ci * uq[k][d];
+            }
+#pragma unroll
+            for (int l = 0; l < 3; ++l) {
+                const R dot = up[k][0] * uq[l][0] + up[k][1] * uq[l][1] + up[k][2] * uq[l][2];
+                mmr += Mr[k][l] * dot;
+                mmi += Mi[k][l] * dot;
+            }
         }
     }
 #pragma unroll

@@ -54,8 +54,9 @@ __host__ __device__ inline Tables<float> tables_of<float>(const DevMesh& m) {
 // unwritten and those of near pairs to the near rows (the reader takes only the
 // entries of triangles q >= p and restores the other half from the symmetry of
 // the operator).
-// (ORBIT: far_pair_rule)
-template <typename R, bool CK, bool UPPER, bool ORBIT>
+// (ORBIT: far_pair_rule.)  KEEP: the source triangle's tables stay in registers over the
+// FAR_PB test triangles.
+template <typename R, bool CK, bool UPPER, bool ORBIT, bool KEEP>
 __device__ __forceinline__ void far_rows_block(const DevMesh& m, const Tables<R>& tb, const Phase<R>& ph, const Scale& sc,
                                                typename Cplx<R>::T* __restrict__ W, int c0, int np, int nqblk,
                                                int logical) {
@@ -73,7 +74,7 @@ __device__ __forceinline__ void far_rows_block(const DevMesh& m, const Tables<R>
         // source triangle's tables of both rules in registers across the turns (256
         // VGPRs and one wave per SIMD in FP64; reread, they are cache hits)
         int q = q0;
-        asm volatile("" : "+v"(q));
+        if (!KEEP) asm volatile("" : "+v"(q));
         C2* rows = W + size_t(pl) * 3 * 2 * N;
         auto put = [&](int i, int j, R re, R im) {
             const size_t n = size_t(m.te[j * T + q]);

@@ -112,6 +112,23 @@ def test_far_rule_calderon_l1(dev):
     assert rel_max(Pm.cpu().numpy(), C.P) <= 1e-10
 
 
+@pytest.mark.parametrize("f3,kt", [(2.5, 1.0), (2.5, 1.0 - 0.3j), (50.0, 1.0 - 0.3j)])
+def test_far_rule_calderon_l1_c64(dev, f3, kt):
+    """Complex64 barycentric rows with the far rule on: pairs of both rules, and (ratio 50) of the 7-point rule alone.
+
+    Tolerance: some 20 roundings of 2^-24 in a pair's value, and up to 10 of cancellation between the values of an entry:
+    1.2e-5 of the largest."""
+    flush(f"calderon L1 far rule {f3} complex64 rows k~={kt}")
+    v, f = icosphere(1)
+    m = P.Mesh(v, f).upload(dev)
+    cal = P.Calderon(m).upload(dev).set_far_rule(f3)
+    _, T = cal.assemble(complex(kt), tol=1e-3, bary_dtype=P.C64, with_tbc=True)
+    ref = ocal.Calderon(oracle_mesh(1), 1.0, kt, far3=None, far3_bary=f3).Tbc
+    err = rel_max(T.cpu().numpy(), ref)
+    flush(f"  rel error {err:.2e}")
+    assert err <= 1.2e-5
+
+
 def test_calderon_own_far_rule_l1(dev):
     """A rule for the barycentric operator alone: T_BC and P follow it, Z does not."""
     flush("calderon own far rule L1")
