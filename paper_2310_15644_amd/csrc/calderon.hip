@@ -1007,7 +1007,7 @@ GramBounds gram_bounds(const efie_calderon_s& C) {
 // the solution, or null where the interval, the tolerance or maxit (in BiCGStab steps
 // of two products) rule it out or the residuals miss their target after all; w.cols
 // holds the residuals.  The steps are counted by the bound 2 sigma^k and up to four
-// groups of three more follow.  Columns are taken in groups whose vectors stay in the
+// groups of three more follow, as far as maxit allows.  Columns are taken in groups whose vectors stay in the
 // last-level cache (192 MiB of 256) while that holds a multiple of the eight tiles that
 // the XCDs work on: 7 TB/s for these passes instead of 4.9 from memory.
 template <typename V>
@@ -1079,6 +1079,7 @@ V* cheb_solve(const DevCald& d, const CaldWs& w, int N, int s0, int S, double to
                 std::fflush(stderr);
         if (left == 0) return buf[1 - cur];   // x_k, whose residuals were taken
         K += 3;
+        if (K > 2 * int64_t(maxit)) break;
     }
     return nullptr;
 }
