@@ -17,8 +17,8 @@
 // it reduces the inner products (FP64, fixed order, hence deterministic),
 // forms the scalars and updates the vectors, and clears the column's active flag
 // on convergence, breakdown or NaN.  The host reads the number of active
-// columns after each iteration (one 4-byte copy), or every 16 iterations where at most
-// 8 columns are left (run_ahead; N = 480, one column: 9.6 -> 2.3 ms a solve).
+// columns after each iteration (one 4-byte copy), or every few iterations, up to 16, where at
+// most 8 columns are left (run_ahead; N = 480, one column: 9.6 -> 2.3 ms a solve).
 //
 // Mixed precision (complex64 Z).  COCG: one Krylov solve whose Z-products run on
 // FP32 matrix cores, with reliable updates (Sleijpen and van der Vorst,
@@ -678,17 +678,29 @@ void true_residual(const void* Z, int zdt, int n, const double2* b, const double
     hipLaunchKernelGGL(residual_kernel, dim3(m), dim3(KB), 0, st, b, y, out, w.nrm, w.bnrm, n, idx);
 }
 
-// Enqueue up to AHEAD iterations without reading the column count back (products of at
-// most 8 columns, which take microseconds: a read-back each iteration took 25 to 40 us of
-// a 49 us iteration at N = 480).  The products stop when no column is active and the
-// steps leave inactive columns alone, so the iterations past the last one do nothing.
-// Returns how many were enqueued.
-constexpr int AHEAD = 16;
+// Enqueue up to `ahead` iterations without reading the column count back (products of at
+// most 8 columns).  The products stop when no column is active and the steps leave
+// inactive columns alone, so the iterations past the last one do nothing.  Returns how
+// many were enqueued.
 template <typename F>
-int run_ahead(int it, int maxit, F iteration) {
-    const int k = std::min(AHEAD, maxit - it);
+int run_ahead(int it, int maxit, int ahead, F iteration) {
+    const int k = std::min(ahead, maxit - it);
     for (int i = 0; i < k; ++i) iteration();
     return k;
+}
+
+// How many: a read-back each iteration costs 15 to 40 us (8 columns, 16 at a time / each read
+// back: N = 480 1.03 / 1.78 ms a solve, 7680 complex128 47.0 / 49.1, 30720 266 / 267), but
+// a column that stops stays in the products until the next one, 8 more of them on average.
+// One column less shortens a product by a tenth or so, so the two meet where an iteration
+// reads about 1 GiB; the number goes down with what it reads from there.  A single column
+// has none to wait for.
+int ahead_of(const Op& op, int n, int solver, int m) {
+    if (m == 1) return 16;
+    auto esz = [](const void* A, int dt) { return A ? (dt == EFIE_C64 ? 8.0 : 16.0) : 0.0; };
+    const double bytes = double(n) * n * (solver == EFIE_COCG ? 1.0 : 2.0) *
+                         (esz(op.Z, op.zdt) + esz(op.P, op.pdt) + esz(op.M, EFIE_C128) + esz(op.Q, EFIE_C128));
+    return int(std::max(1.0, std::min(16.0, 16.0 * double(1 << 30) / bytes)));
 }
 
 // One Krylov solve of Z x = b for S columns.  Returns per-column Col states in host memory.
@@ -703,7 +715,7 @@ void krylov(const Op& op, int n, const double2* b, double2* x, int S, int solver
         bool exact_regime = !reliable || m <= 8;
         for (int it = 0; it < maxit && m > 0; ++it) {
             if (!reliable && m <= 8) {
-                it += run_ahead(it, maxit, [&]() {
+                it += run_ahead(it, maxit, ahead_of(op, n, solver, m), [&]() {
                     op_product(op, n, w.p, w.q, w.idx_a, m, false, w, st, w.counters + 2);
                     launch_cocg_step(S, x, w.r, w.p, w.q, w.cols, n, w.counters, 0, st);
                 }) - 1;
@@ -747,7 +759,7 @@ void krylov(const Op& op, int n, const double2* b, double2* x, int S, int solver
                                    w.counters);
             };
             if (m <= 8)
-                it += run_ahead(it, maxit, [&]() { iteration(w.counters + 2); }) - 1;
+                it += run_ahead(it, maxit, ahead_of(op, n, solver, m), [&]() { iteration(w.counters + 2); }) - 1;
             else
                 iteration(nullptr);
             m = compact(w, S, 0, w.idx_a, st);

@@ -48,3 +48,23 @@ def test_ahead_orders(n, solver):
     for maxit in (1, 16, 17):
         _, sc = P.solve(Z, V, solver=s, tol=1e-300, maxit=maxit)
         assert sc.code == 1 and int(sc.iters[3]) == maxit
+
+
+@pytest.mark.parametrize("solver,n", [("cocg", 9001), ("cgs", 9001), ("cgs", 25001)])
+def test_ahead_large_orders(solver, n):
+    """Orders whose groups are shorter (13, 6 and one iteration: n^2 x 16 bytes once or twice an iteration against
+    16 GiB), columns that stop at different steps, and limits on both sides of a group."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    flush(f"ahead n={n} {solver}")
+    s = P.COCG if solver == "cocg" else P.CGS
+    Z, V = system(n, 3, n)
+    J, st = P.solve(Z, V, solver=s, tol=1e-10, maxit=400)
+    assert st.code == 0 and np.all(st.status == 0) and np.all(st.relres_true <= 2e-10) and st.iters[0] == 0
+    R = V - J @ Z      # Z is symmetric
+    assert float((R.norm(dim=1) / V.norm(dim=1).clamp(min=1.0)).max()) <= 4e-10
+    J1, s1 = P.solve(Z, V[2:].contiguous(), solver=s, tol=1e-10, maxit=400)
+    assert abs(int(s1.iters[0]) - int(st.iters[2])) <= 1
+    for maxit in (1, 6, 7, 13, 14):
+        _, sc = P.solve(Z, V, solver=s, tol=1e-300, maxit=maxit)
+        assert sc.code == 1 and int(sc.iters[2]) == maxit
