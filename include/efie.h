@@ -330,7 +330,9 @@ int efie_zx_flush64_noalloc(const void* Z, int64_t n, const void* X, void* Y, in
  * the fastest, so that timing noise does not flip between near-equal tiles, and
  * does not change the selection.
  * ws: dev scratch of at least M*n*(acc64 ? 16 : 8) bytes rounded up to 256, plus
- * 4*M bytes.  efie_gemm_select sets the variant used by later calls (process-wide).
+ * 4*M bytes; with efie_zx_workspace_size bytes more behind that (rounded up to 256), the
+ * split product is timed over ranges of K, as efie_zx_ws and the solves run it.
+ * efie_gemm_select sets the variant used by later calls (process-wide).
  */
 int efie_gemm_variants(int* count);
 int efie_gemm_variant_info(int variant, int* bm, int* bn, int* kc);
@@ -352,7 +354,8 @@ int efie_gemm_select(int acc64, int variant, int* previous);
  * cache_path may be NULL (always time, keep nothing).  Outputs (host):
  * variant_acc32, variant_acc64; ms_acc32 / ms_acc64 (efie_gemm_variants entries
  * each, may be NULL); from_cache (may be NULL) = 1 when the entry was reused.
- * ws: dev, 256-byte aligned, efie_gemm_autotune_cached_workspace_size bytes.
+ * ws: dev, 256-byte aligned, efie_gemm_autotune_cached_workspace_size bytes (less, down
+ * to 8 M n and 16 M n, each rounded up to 256, + 4 M: the split product without its ranges).
  * Synchronises the stream when it times.  Malformed cache lines are ignored and
  * dropped when the file is rewritten.
  */

@@ -618,7 +618,12 @@ def gemm_autotune(Z, M: int, reps: int = 3, cache: str | None = None, force: boo
         pass
     nb = ctypes.c_size_t()
     _check(lib().efie_gemm_autotune_cached_workspace_size(n, int(M), ctypes.byref(nb)))
-    ws = torch.empty(nb.value + 256, dtype=torch.uint8, device=Z.device)
+    try:
+        ws = torch.empty(nb.value + 256, dtype=torch.uint8, device=Z.device)
+    except torch.OutOfMemoryError:   # the split product timed without its partial sums
+        a256 = lambda b: (b + 255) // 256 * 256
+        nb.value = a256(8 * n * int(M)) + a256(16 * n * int(M)) + 4 * int(M)
+        ws = torch.empty(nb.value + 256, dtype=torch.uint8, device=Z.device)
     off = (-ws.data_ptr()) % 256
     tiles = gemm_variants()
     v32, v64, hit = ctypes.c_int(), ctypes.c_int(), ctypes.c_int()

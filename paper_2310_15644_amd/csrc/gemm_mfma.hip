@@ -531,6 +531,11 @@ extern "C" int efie_gemm_autotune(const void* Z, int64_t n, const void* X, int64
         const size_t need = ((ybytes + 255) & ~size_t(255)) + size_t(M) * sizeof(int);
         EFIE_REQUIRE(ws_bytes >= need, EFIE_ERR_ARG, "gemm_autotune: workspace too small");
         void* Y = ws;
+        // the split product as efie_zx_ws and the solves run it, where the rest of ws holds its partial sums
+        const size_t after = (need + 255) & ~size_t(255);
+        char* part = ws_bytes > after ? static_cast<char*>(ws) + after : nullptr;
+        if (reinterpret_cast<uintptr_t>(part) & 15) part = nullptr;
+        const size_t part_bytes = part ? ws_bytes - after : 0;
         int* idx = reinterpret_cast<int*>(static_cast<char*>(ws) + ((ybytes + 255) & ~size_t(255)));
         hipLaunchKernelGGL(efie::iota_rows_kernel, dim3(int((M + 255) / 256)), dim3(256), 0, stream, idx, int(M));
         hipEvent_t e0, e1;
@@ -540,7 +545,11 @@ extern "C" int efie_gemm_autotune(const void* Z, int64_t n, const void* X, int64
         *best = 0;
         for (int v = 0; v < efie::kNumVariants; ++v) {
             auto run = [&]() {
-                if (acc64)
+                if (v == efie::kSplitVariant && acc64)
+                    efie::launch_split_ws<true>(X, Z, Y, idx, int(M), int(n), part, part_bytes, stream);
+                else if (v == efie::kSplitVariant)
+                    efie::launch_split_ws<false>(X, Z, Y, nullptr, int(M), int(n), part, part_bytes, stream);
+                else if (acc64)
                     efie::launch_variant<true>(v, X, Z, Y, idx, int(M), int(M), int(n), stream);
                 else
                     efie::launch_variant<false>(v, X, Z, Y, nullptr, int(M), int(M), int(n), stream);

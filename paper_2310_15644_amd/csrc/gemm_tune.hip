@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "efie_internal.h"
+#include "linalg.h"
 
 // ------------------------------------------------------- tile cache on disk
 namespace efie {
@@ -36,10 +37,19 @@ int num_variants() {
 }
 
 size_t tune_x_bytes(int64_t n, int64_t M) { return (size_t(n) * size_t(M) * 8 + 255) & ~size_t(255); }
+// the least workspace, and where the split product's partial sums start behind it
+size_t tune_bytes(int64_t n, int64_t M) {
+    return tune_x_bytes(n, M) + ((size_t(M) * size_t(n) * 16 + 255) & ~size_t(255)) + size_t(M) * 4;
+}
+size_t tune_full_bytes(int64_t n, int64_t M) {
+    const size_t ranges = M > 1 ? cgemm_ranges_bytes(int(M), int(n)) : 0;
+    return ranges ? ((tune_bytes(n, M) + 255) & ~size_t(255)) + ranges : tune_bytes(n, M);
+}
 
 // key of a cache line: device, order, right-hand sides and the tile table, so a
-// rebuilt library with other tiles never reuses a stale choice
-std::string tune_key(int64_t n, int64_t M) {
+// rebuilt library with other tiles never reuses a stale choice; the split product's
+// entry says how it was timed (r: over ranges of K) and that its low parts are scaled (s)
+std::string tune_key(int64_t n, int64_t M, bool ranges) {
     int dev = 0;
     EFIE_HIP_CHECK(hipGetDevice(&dev));
     hipDeviceProp_t prop{};
@@ -55,6 +65,7 @@ std::string tune_key(int64_t n, int64_t M) {
         EFIE_REQUIRE(efie_gemm_variant_info(v, &bm, &bn, &kc) == EFIE_OK, EFIE_ERR_STATE, "autotune: tile table");
         k << (v ? "," : "") << bm << "x" << bn << "x" << kc;
     }
+    k << (ranges ? "sr" : "s");
     return k.str();
 }
 
@@ -82,7 +93,7 @@ extern "C" int efie_gemm_autotune_cached_workspace_size(int64_t n, int64_t M, si
     return efie::guarded([&]() {
         EFIE_REQUIRE(bytes && n >= 1 && n < (int64_t(1) << 31) && M >= 1 && M < 65536, EFIE_ERR_ARG,
                      "gemm_autotune_cached_workspace_size: bad argument");
-        *bytes = efie::tune_x_bytes(n, M) + ((size_t(M) * size_t(n) * 16 + 255) & ~size_t(255)) + size_t(M) * 4;
+        *bytes = efie::tune_full_bytes(n, M);
         return int(EFIE_OK);
     });
 }
@@ -96,13 +107,12 @@ extern "C" int efie_gemm_autotune_cached(const char* cache_path, const void* Z, 
                      "gemm_autotune_cached: bad argument");
         EFIE_REQUIRE(n >= 1 && n < (int64_t(1) << 31) && M >= 1 && M < 65536, EFIE_ERR_ARG,
                      "gemm_autotune_cached: bad sizes");
-        size_t need = 0;
-        EFIE_REQUIRE(efie_gemm_autotune_cached_workspace_size(n, M, &need) == EFIE_OK && ws_bytes >= need,
-                     EFIE_ERR_ARG, "gemm_autotune_cached: workspace too small");
+        EFIE_REQUIRE(ws_bytes >= efie::tune_bytes(n, M), EFIE_ERR_ARG, "gemm_autotune_cached: workspace too small");
         EFIE_REQUIRE((reinterpret_cast<uintptr_t>(ws) & 255) == 0, EFIE_ERR_ARG,
                      "gemm_autotune_cached: workspace not 256-byte aligned");
         const int nv = efie::num_variants();
-        const std::string key = efie::tune_key(n, M);
+        const size_t full = efie::tune_full_bytes(n, M);
+        const std::string key = efie::tune_key(n, M, full > efie::tune_bytes(n, M) && ws_bytes >= full);
         std::vector<std::string> lines;
         efie::TuneEntry ent;
         bool hit = false;

@@ -271,6 +271,48 @@ def test_gemm_autotune_cache(dev, tmp_path):
     assert float((Y - ref).abs().max() / ref.abs().max()) <= 1e-5
 
 
+@pytest.mark.parametrize("n,M", [(4317, 45), (1537, 40)])
+def test_gemm_autotune_split_ranges(dev, tmp_path, n, M):
+    """The split product is timed as the products run it, over ranges of K: its time is that of P.zx (within 1.5 times; in
+    the block it takes twice as long at 4317 times 45), and a workspace of the size without the ranges is still enough."""
+    import ctypes
+
+    g = torch.Generator(device=dev).manual_seed(6)
+    Z = torch.randn((n, n), dtype=torch.complex64, device=dev, generator=g)
+    X = torch.randn((M, n), dtype=torch.complex64, device=dev, generator=g)
+    prev = P.gemm_select(False, 0), P.gemm_select(True, 0)
+    try:
+        cache = str(tmp_path / "tiles.txt")
+        a = P.gemm_autotune(Z, M, reps=20, cache=cache)
+        split = len(a["tiles"]) - 1
+        P.gemm_select(False, split)
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        P.zx(Z, X)
+        e[0].record()
+        for _ in range(20):
+            P.zx(Z, X)
+        e[1].record()
+        torch.cuda.synchronize()
+        t = e[0].elapsed_time(e[1]) / 20
+        flush(f"autotune n={n} M={M}: split {a['ms']['acc32'][split]:.4f} ms, zx {t:.4f} ms")
+        assert a["ms"]["acc32"][split] <= 1.5 * t
+        old = sum((b * n * M + 255) // 256 * 256 for b in (8, 16)) + 4 * M
+        nb, ranges = ctypes.c_size_t(), ctypes.c_size_t()
+        assert P.lib().efie_gemm_autotune_cached_workspace_size(n, M, ctypes.byref(nb)) == 0
+        assert P.lib().efie_zx_workspace_size(n, M, P.C64, ctypes.byref(ranges)) == 0
+        assert ranges.value > 0 and nb.value == (old + 255) // 256 * 256 + ranges.value
+        ws = torch.empty(old + 256, dtype=torch.uint8, device=dev)
+        p = ctypes.c_void_p(ws.data_ptr() + (-ws.data_ptr()) % 256)
+        v = ctypes.c_int(), ctypes.c_int()
+        call = lambda b: P.lib().efie_gemm_autotune_cached(cache.encode(), ctypes.c_void_p(Z.data_ptr()), n, M, 1, 0, p, b,
+                                                           ctypes.byref(v[0]), ctypes.byref(v[1]), None, None, None, None)
+        assert call(old - 1) == -1 and call(old) == 0
+        assert len(open(cache).read().splitlines()) == 2      # timed without the ranges: an entry of its own
+    finally:
+        P.gemm_select(False, prev[0])
+        P.gemm_select(True, prev[1])
+
+
 def test_fp32_phase_range(dev):
     """Complex64 assembly near the top of the FP32 phase range matches the FP64
     oracle to the FP32 phase error, and every complex64 assembly rejects |Re k| at
