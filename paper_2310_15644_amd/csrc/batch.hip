@@ -68,8 +68,8 @@ __device__ __forceinline__ DevMesh mesh_view(const DevMesh& c, const BatchItem& 
     v.n_up = it.n_up;
     v.near_up = c.near_up + it.uoff;
     v.et = c.et + 2 * n; v.el = c.el + 2 * n;
-    v.q3x = c.q3x + 3 * t; v.q3y = c.q3y + 3 * t; v.q3z = c.q3z + 3 * t; v.q3w = c.q3w + 3 * t;
-    v.q3x32 = c.q3x32 + 3 * t; v.q3y32 = c.q3y32 + 3 * t; v.q3z32 = c.q3z32 + 3 * t; v.q3w32 = c.q3w32 + 3 * t;
+    v.q3x = c.q3x + 3 * t; v.q3y = c.q3y + 3 * t; v.q3z = c.q3z + 3 * t;
+    v.q3x32 = c.q3x32 + 3 * t; v.q3y32 = c.q3y32 + 3 * t; v.q3z32 = c.q3z32 + 3 * t;
     return v;
 }
 

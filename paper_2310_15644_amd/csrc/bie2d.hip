@@ -40,7 +40,6 @@ namespace efie {
 namespace {
 
 constexpr double PI2D = 3.14159265358979323846;
-constexpr double EULER = 0.57721566490153286061;
 constexpr int NQN = 8;          // points of the near-pair rules
 constexpr int TILE = 15;        // entries per side of an assembly tile (16 x 16 segment pairs)
 

@@ -81,8 +81,8 @@ struct DevMesh {
     const int32_t *el;                   // RWG -> local edge index in T+ / T- [2][N]
     // distance-adaptive far rule: pairs with centroid distance D >= far3 * (larger
     // longest edge) take the 3x3 product of the interior 3-point rule (far3 = 0: off)
-    const double *q3x, *q3y, *q3z, *q3w;       // its point offsets and weights*area [3][T]
-    const float *q3x32, *q3y32, *q3z32, *q3w32;
+    const double *q3x, *q3y, *q3z;             // its point offsets [3][T]
+    const float *q3x32, *q3y32, *q3z32;
     double far3;
     const int32_t* near_up;              // indices e of the ordered near pairs with q >= p, increasing
 };

@@ -230,7 +230,7 @@ void pack_tables(efie_mesh_s& m) {
     // barycentric (2/3, 1/6, 1/6) and permutations, weights 1/3
     const double b3[3][3] = {{2.0 / 3.0, 1.0 / 6.0, 1.0 / 6.0}, {1.0 / 6.0, 2.0 / 3.0, 1.0 / 6.0},
                              {1.0 / 6.0, 1.0 / 6.0, 2.0 / 3.0}};
-    std::vector<double> q3x(3 * T), q3y(3 * T), q3z(3 * T), q3w(3 * T);
+    std::vector<double> q3x(3 * T), q3y(3 * T), q3z(3 * T);
     for (int64_t t = 0; t < T; ++t) {
         // vertex offsets from the centroid; points r = sum_k lambda_k p_k become
         // sum_k lambda_k (p_k - c) since the barycentric weights sum to one
@@ -251,7 +251,6 @@ void pack_tables(efie_mesh_s& m) {
             q3x[a * T + t] = b3[a][0] * X[0][0] + b3[a][1] * X[1][0] + b3[a][2] * X[2][0];
             q3y[a * T + t] = b3[a][0] * X[0][1] + b3[a][1] * X[1][1] + b3[a][2] * X[2][1];
             q3z[a * T + t] = b3[a][0] * X[0][2] + b3[a][1] * X[1][2] + b3[a][2] * X[2][2];
-            q3w[a * T + t] = m.area[t] / 3.0;
         }
         for (int i = 0; i < 3; ++i) {
             vx[i * T + t] = X[i][0];
@@ -290,8 +289,8 @@ void pack_tables(efie_mesh_s& m) {
     pk.add(tv);
     pk.add(m.near_p); pk.add(m.near_q);
     pk.add(et); pk.add(el);
-    pk.add(q3x); pk.add(q3y); pk.add(q3z); pk.add(q3w);
-    pk.add(f32(q3x)); pk.add(f32(q3y)); pk.add(f32(q3z)); pk.add(f32(q3w));
+    pk.add(q3x); pk.add(q3y); pk.add(q3z);
+    pk.add(f32(q3x)); pk.add(f32(q3y)); pk.add(f32(q3z));
     pk.add(m.near_up);
     pk.blob.resize((pk.blob.size() + 255) & ~size_t(255));
     m.host_blob.swap(pk.blob);
@@ -316,8 +315,8 @@ const TableSpec kTables[] = {
     {'T', 3, 4}, {'T', 3, 4},                                                         // te tv
     {'E', 1, 4}, {'E', 1, 4},                                                         // near_p near_q
     {'N', 2, 4}, {'N', 2, 4},                                                         // et el
-    {'T', 3, 8}, {'T', 3, 8}, {'T', 3, 8}, {'T', 3, 8},                               // q3 (FP64)
-    {'T', 3, 4}, {'T', 3, 4}, {'T', 3, 4}, {'T', 3, 4},                               // q3 (FP32)
+    {'T', 3, 8}, {'T', 3, 8}, {'T', 3, 8},                                            // q3 (FP64)
+    {'T', 3, 4}, {'T', 3, 4}, {'T', 3, 4},                                            // q3 (FP32)
     {'U', 1, 4},                                                                      // near_up
 };
 }  // namespace
@@ -349,8 +348,8 @@ void bind_pointers(DevMesh& d, const void* base, const std::vector<size_t>& o) {
     d.tv = I();
     d.near_p = I(); d.near_q = I();
     d.et = I(); d.el = I();
-    d.q3x = D(); d.q3y = D(); d.q3z = D(); d.q3w = D();
-    d.q3x32 = F(); d.q3y32 = F(); d.q3z32 = F(); d.q3w32 = F();
+    d.q3x = D(); d.q3y = D(); d.q3z = D();
+    d.q3x32 = F(); d.q3y32 = F(); d.q3z32 = F();
     d.near_up = I();
 }
 

@@ -24,7 +24,7 @@ struct Scale {          // Z contribution = A * T_A + P * T_Phi (complex), or pa
 template <typename R>
 struct Tables {
     const R *qx, *qy, *qz, *qw, *vx, *vy, *vz, *cf, *dv;
-    const R *q3x, *q3y, *q3z, *q3w;   // 3-point rule of the adaptive far rule (null: not used)
+    const R *q3x, *q3y, *q3z;   // 3-point rule of the adaptive far rule (null: not used)
 };
 
 // Whether the far pair (p, q) takes the 3x3 rule: D^2 >= (far3 h)^2 with h the

@@ -38,12 +38,12 @@ template <typename R>
 __host__ __device__ Tables<R> tables_of(const DevMesh& m);
 template <>
 __host__ __device__ inline Tables<double> tables_of<double>(const DevMesh& m) {
-    return {m.qx, m.qy, m.qz, m.qw, m.vx, m.vy, m.vz, m.cf, m.dv, m.q3x, m.q3y, m.q3z, m.q3w};
+    return {m.qx, m.qy, m.qz, m.qw, m.vx, m.vy, m.vz, m.cf, m.dv, m.q3x, m.q3y, m.q3z};
 }
 template <>
 __host__ __device__ inline Tables<float> tables_of<float>(const DevMesh& m) {
     return {m.qx32, m.qy32, m.qz32, m.qw32, m.vx32, m.vy32, m.vz32, m.cf32, m.dv32,
-            m.q3x32, m.q3y32, m.q3z32, m.q3w32};
+            m.q3x32, m.q3y32, m.q3z32};
 }
 
 // the far pair rows, one block (FAR_BLOCK threads) of logical index `logical` = (group of
