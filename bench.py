@@ -5,14 +5,14 @@ Workload (default): PEC unit sphere, icosphere level 5 (T = 20480 triangles,
 N = 30720 RWG unknowns), k = 10 rad/m, 512 plane waves on the uniform
 16 (theta) x 32 (phi) grid, incidence from rhat with theta-hat polarisation,
 monostatic observation.  Mixed precision: complex64 operator (far pairs in
-FP32, near pairs in FP64), COCG with Z X on FP32 matrix cores, FP64 outer
+FP32, near pairs in FP64), complex64 products on the matrix cores, FP64 outer
 refinement to ||V - Z J|| <= 1e-6 ||V|| per right-hand side.
 
 One step = the whole hot path on inputs already resident in HBM:
 assembly (far + near), excitation of the 512 right-hand sides, the Calderon
 preconditioner P = T_BC(k~) G_mix^-1 (barycentric second operator at the complex
 wavenumber, mixed Gram inverse), the preconditioned multi-RHS solve (CGS on
-P Z J = P V, complex64 Z and P on FP32 matrix cores, FP64 true-residual
+P Z J = P V, complex64 Z and P on the matrix cores, FP64 true-residual
 refinement; --solver cocg: unpreconditioned COCG instead), and the far field in
 the 512 monostatic directions.
 
@@ -42,10 +42,12 @@ PEAK_FP32_VALU = 78.6       # TFLOP/s with FMA = 2 flops, packed FP32 disabled (
 VALU_LANE_SLOTS = 256 * 64 * 2.4e9   # vector-ALU lane-instructions per second
 # Algorithmic cost model of the assembly (vector ALU): 7 x 7 Green's-function
 # evaluations per triangle pair, every ordered pair counted, i.e. 49 T^2 / N^2 per Z
-# entry (21.8 on a closed surface, T = 2N/3); one evaluation costs about 46 FP32
+# entry (21.8 on a closed surface, T = 2N/3); one evaluation is priced at 46 FP32
 # issue slots (4 transcendentals at quarter rate, about 30 FMA-class operations for
-# R^2, the kernel and the moment sums) or about 110 in FP64 (no hardware sine and
-# cosine).  The bound does not credit the symmetry Z = Z^T that the kernels use.
+# R^2, the kernel and sums of Cartesian moments) or 110 in FP64 (no hardware sine and
+# cosine).  A yardstick and no bound: the kernels use Z = Z^T (the complex64 tiles evaluate
+# 0.89 of the ordered pairs, the complex128 rows half) and barycentric moments (about 35
+# FP32 slots), so that a fraction of it may pass 1; `frac_symmetric` credits the symmetry.
 EVAL_SLOTS = {"c64": 46.0, "c128": 110.0}
 
 
@@ -469,7 +471,7 @@ def bench_gradient(args, P, synth, torch, np, dev):
 
 def bench_mixed_fp64(args, P, synth, torch, np, dev):
     """Level-5 sphere (N = 30720), k = 10, x-polarised plane wave along -z: the mixed
-    form (complex64 Z, FP32 far pairs, FP32 matrix-core products, FP64 refinement)
+    form (complex64 Z, FP32 far pairs, complex64 matrix-core products, FP64 refinement)
     against the FP64 GPU path on the same input; current difference, RCS difference
     over the 512 monostatic-grid directions, and both times-to-solve @ 1e-6
     (assembly + excitation + solve)."""
@@ -1010,6 +1012,8 @@ def main():
             "peak": round(alu_peak, 1) if alu_peak else None,
             "unit": "Mentries/s",
             "frac": round(mentries / alu_peak, 4) if alu_peak else None,
+            # against the same evaluations of each unordered pair once
+            "frac_symmetric": round(0.5 * mentries / alu_peak, 4) if alu_peak else None,
             "model": "49 T^2/N^2 Green's-function evaluations per entry x %g issue slots" % EVAL_SLOTS[args.dtype],
             "z_write_gbs": round(N * N * (8 if dt == P.C64 else 16) / (asm_ms * 1e-3) / 1e9, 1),
         },

@@ -372,9 +372,9 @@ typedef struct {
     double tol;           /* target ||V - Z J||_2 / ||V||_2 per right-hand side      */
     int32_t max_refine;   /* EFIE_C64 only: outer refinement steps (>= 1)            */
     double inner_tol;     /* EFIE_C64 only: relative tolerance of each inner solve   */
-    int32_t fp32_acc;     /* EFIE_C64 only: 0 (default) = flush the FP32 matrix-core */
-                          /* partial sums into FP64 every two K chunks; 1 = accumu-  */
-                          /* late in FP32 (more Krylov iterations)                   */
+    int32_t fp32_acc;     /* EFIE_C64 only: 0 (default) = products with FP64 sums of */
+                          /* partial sums of at most 64 terms; 1 = complex64 results */
+                          /* (a selected FP32 tile: sums in FP32, more iterations)   */
 } efie_solve_opts;
 
 typedef struct {
@@ -392,8 +392,8 @@ typedef struct {
  *   complex128 (output).  FP64 vectors and inner products in both cases.
  *   EFIE_C128: one Krylov solve with FP64 products.
  *   EFIE_C64 : mixed precision -- Z X products of more than 8 active columns run
- *              on FP32 matrix cores with FP64 accumulation of the K-chunk partial
- *              sums (opts->fp32_acc = 1: FP32 accumulation); COCG replaces its recursive residual by the true residual
+ *              on the matrix cores as by efie_zx_flush64 (opts->fp32_acc = 1: as
+ *              by efie_zx); COCG replaces its recursive residual by the true residual
  *              V - Z J (FP64 accumulation from the stored complex64 Z) whenever it
  *              has dropped tenfold (reliable updates) and converges only on it;
  *              CGS runs inner solves to inner_tol inside an outer refinement loop
@@ -445,7 +445,7 @@ int efie_solve(const void* Z, int dtype, int64_t n, const void* V, void* J, int6
  *   has to be fixed, not exact: P then differs from T_BC G^-1 by ~1e-6).
  * efie_solve_precond: CGS on P Z J = P V (complex128 Z and P, FP64 throughout).
  *   efie_solve_precond_ex: Z and P of either dtype; with a complex64 factor the
- *   CGS products of more than 8 columns run on FP32 matrix cores (FP64 flushes)
+ *   CGS products of more than 8 columns run as by efie_zx_flush64
  *   and each pass stops no lower than opts->inner_tol, the outer refinement
  *   (FP64 products, against the stored Z) making the result accurate.  CGS
  *   tests the preconditioned recurrence residual; an outer refinement on the

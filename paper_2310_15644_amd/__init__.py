@@ -496,8 +496,7 @@ class SolveStats:
 
 def solve(Z, V, solver=COCG, tol=1e-8, maxit=1000, max_refine=4, inner_tol=1e-3, fp32_acc=False, out=None):
     """Solve Z J = V for V (nrhs, N) complex128; Z complex128 (FP64) or complex64 (mixed:
-    FP32 matrix-core products with their partial sums flushed into FP64 every K chunk,
-    or with fp32_acc accumulated in FP32)."""
+    complex64 matrix-core products as by zx_flush64, or with fp32_acc as by zx)."""
     torch = _torch()
     code_dt, _ = _cdtype(Z.dtype)
     _require_cuda(Z, "Z")
@@ -569,7 +568,7 @@ def gemm_kernel_name(variant, acc64: bool) -> str:
 
 def zx_flush64(Z, X):
     """Y = Z X with Z complex64 and X complex128 (nrhs, N): the mixed solves' product
-    (FP32 matrix cores, partial sums flushed into FP64 every K chunk), Y complex128."""
+    (complex64 on the matrix cores, partial sums of at most 64 terms added in FP64), Y complex128."""
     torch = _torch()
     _require_cuda(Z, "Z")
     if Z.dtype != torch.complex64:
@@ -758,8 +757,8 @@ class Calderon:
 def solve_precond(Z, Pm, V, tol=1e-8, maxit=1000, max_refine=6, inner_tol=1e-4, fp32_acc=False, out=None):
     """CGS on P Z J = P V with outer refinement on the unpreconditioned FP64 true
     residual (up to max_refine passes); Z and P complex128 (FP64 throughout) or
-    complex64 (FP32 matrix-core products inside CGS, flushed into FP64 per K chunk
-    or with fp32_acc accumulated in FP32; each pass to at least inner_tol).  Stats report the
+    complex64 (complex64 matrix-core products inside CGS as by zx_flush64, or with
+    fp32_acc as by zx; each pass to at least inner_tol).  Stats report the
     true residual and the iterations summed over the passes."""
     torch = _torch()
     _require_cuda(Z, "Z")

@@ -5,11 +5,12 @@
 // (T_A)_mn = <f_m, G f_n>, (T_Phi)_mn = <div f_m, G div f_n>, G = exp(-jkR)/(4 pi R).
 //
 // Work decomposition.  One thread owns one triangle pair (p, q): it evaluates
-// the 7 x 7 Green's function values of the pair, reduces them to the moments
+// the 7 x 7 Green's function values of the pair, folds them into the barycentric moments
+// M_kl = sum w_a lambda_k(a) w_b lambda_l(b) G_ab (Bary in pair_kernels.h), takes from them
 //   M0 = sum W_a W_b G,   Md = sum W_a W_b G d_a,   Md' = sum W_a W_b G d'_b,
 //   Mdd' = sum W_a W_b G (d_a . d'_b)
 // (d, d' quadrature points relative to the triangle centroids), and forms the
-// nine RWG half-function products from them:
+// nine RWG half-function products:
 //   T_A(i,j)   = c_i c'_j [Mdd' - u'_j . Md - u_i . Md' + (u_i . u'_j) M0],
 //   T_Phi(i,j) = g_i g'_j M0,
 // with u the vertex offsets, c = s l/(2A), g = s l/A.  The nine results are added

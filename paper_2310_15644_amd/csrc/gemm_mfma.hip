@@ -312,12 +312,13 @@ static void launch_split(const void* X, const void* Z, void* Y, const int* yrow,
 // none, is left waiting on its own loads.  The number of ranges is the one that takes
 // least by a model of the measured times: a chunk takes full us while two blocks share
 // a CU (slots = 512 blocks), last us while at most one is left on each, a partial tile
-// tile us to write and to add.  Within 12 % of the times from n = 1920 up; in us,
-// in-block / ranges:
-//   n = 4317,  M = 45:  109 /  52 (7 ranges)    n = 1920, M = 100:  39 /  27 (8)
-//   n = 7680,  M = 64:  230 / 148 (4)           n =  960, M =  64:  22 /  15 (8)
-//   n = 12000, M = 20:  345 / 238 (5)           n =  480, M =  64:  14 /  11 (8)
-//   n = 12000, M = 200: 1230 / 1134 (2)         n = 30720, M = 512: one range
+// tile us to write and to add.  Within 10 % of the times from n = 1920 up; in us, the
+// matrix in the last-level cache from the call before where it fits (cold, 4317 x 45
+// takes 66), in-block / ranges:
+//   n = 4317,  M = 45:  124 /  59 (7 ranges)    n = 1920, M = 100:  55 /  36 (8)
+//   n = 7680,  M = 64:  240 / 167 (4)           n =  960, M =  64:  30 /  16 (8)
+//   n = 12000, M = 20:  474 / 291 (5)           n =  480, M =  64:  17 /  14 (8)
+//   n = 12000, M = 200: 1421 / 1353 (2)         n = 30720, M = 512: one range
 struct RangePlan {
     int kind = 0, ranges = 1;
     size_t bytes = 0;   // workspace; 0: in-block
@@ -331,7 +332,7 @@ static RangePlan range_plan(int M, int n) {
         int bm, bn, kc;
         double full, last;
     };
-    static constexpr Kind kinds[] = {{64, 64, 64, 4.0, 3.0}, {32, 128, 32, 2.9, 1.9}, {32, 32, 128, 4.0, 3.0}};
+    static constexpr Kind kinds[] = {{64, 64, 64, 4.7, 3.5}, {32, 128, 32, 3.4, 2.2}, {32, 32, 128, 4.7, 3.5}};
     RangePlan best;
     best.kind = M > 32 ? 0 : (n > 2048 ? 1 : 2);
     const Kind& k = kinds[best.kind];
@@ -371,10 +372,10 @@ static void launch_ranges(const void* X, const void* Z, void* Y, const int* yrow
 // The tile of the split kernel by the number of blocks (256 CUs; times in us with
 // 32 x 32 tiles and 4 K groups / 64 x 32 and 4 groups / 64 x 64 / 32 x 32 and 2 groups of
 // 64-term chunks):
-//   n = 1920,  M = 100:   41 /  48 /  80 /  56        n =  1920, M = 16:  36 /  45 /  76 /  53
-//   n = 4317,  M = 45:   172 / 102 / 176 / 121        n =  4320, M = 64: 160 /  98 / 175 / 119
-//   n = 12000, M = 33:   695 / 541 / 499 / 671        n = 12000, M = 20: 457 / 530 / 487 / 332
-//   n = 7679,  M = 200: 1062 / 712 / 489 / 840        n = 30720, M = 512: 34.5 / 20.9 / 14.6 / 25.3 ms
+//   n = 1920,  M = 100:   57 /  57 /  99 /  78        n =  1920, M = 16:  52 /  55 /  98 /  77
+//   n = 4317,  M = 45:   241 / 124 / 221 / 174        n =  4320, M = 64: 230 / 121 / 218 / 174
+//   n = 12000, M = 33:   986 / 681 / 611 / 942        n = 12000, M = 20: 652 / 679 / 608 / 473
+//   n = 7679,  M = 200: 1500 / 873 / 573 / 1188       n = 30720, M = 512: 49.4 / 27.3 / 17.2 / 35.3 ms
 // A matrix that gives at most one block per CU is split over K inside the block, by the
 // smallest tile that still does; otherwise the widest tile converts the least.
 template <bool A64>

@@ -20,13 +20,13 @@
 // columns after each iteration (one 4-byte copy), or every few iterations, up to 16, where at
 // most 8 columns are left (run_ahead; N = 480, one column: 9.6 -> 2.3 ms a solve).
 //
-// Mixed precision (complex64 Z).  COCG: one Krylov solve whose Z-products run on
-// FP32 matrix cores, with reliable updates (Sleijpen and van der Vorst,
+// Mixed precision (complex64 Z).  COCG: one Krylov solve whose Z-products are those of
+// complex64 vectors on the matrix cores (gemm_split.h), with reliable updates (Sleijpen and van der Vorst,
 // Computing 56, 1996): whenever a column's recursive residual has dropped by a
 // factor 10 since its last replacement, or claims convergence, it is replaced by
 // the true residual V - Z J accumulated in FP64 from the stored complex64 Z, and
-// only the true residual may declare convergence.  This keeps the FP32
-// accumulation error of the products (~1e-5 ||Z|| ||p||, amplified along
+// only the true residual may declare convergence.  This keeps the rounding error
+// of the products (1e-7 ||Z|| ||p||, 1e-5 with FP32 sums, amplified along
 // near-resonant directions) out of the recurrence.  CGS: an outer refinement
 // loop around inner CGS solves.
 #include <hip/hip_runtime.h>

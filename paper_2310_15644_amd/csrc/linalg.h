@@ -25,7 +25,8 @@ size_t gemv_multi_part_bytes(int n);
 void gather_cast(const double2* X, const int* idx, int m, int n, float2* out, hipStream_t s);
 void scatter_cast(const float2* in, const int* idx, int m, int n, double2* Y, hipStream_t s);
 
-// Y (M x n, complex64) = X (M x n, complex64) * Z^T (Z n x n complex64) on FP32 matrix cores.
+// Y (M x n, complex64) = X (M x n, complex64) * Z^T (Z n x n complex64) on matrix
+// cores, by the selected variant (the fp16 split product, or an FP32 tile).
 // mcap: rows of X that may be read (>= M; the rows past M are computed and dropped).
 // ws: for the split product, partial sums of several ranges of K (16-byte aligned; used
 // if it holds cgemm_ranges_bytes(M, n) bytes, which are 0 where one range is best).
@@ -33,10 +34,10 @@ void cgemm_mfma(const void* X, const void* Z, void* Y, int M, int n, hipStream_t
                 size_t ws_bytes = 0);
 size_t cgemm_ranges_bytes(int M, int n);
 bool cgemm_mfma_supported(int M, int n);
-// Y[yrow[r]] (complex128) = sum_j X[r][j] Z[i][j]: same product with the FP32 matrix-core
-// partial sums flushed into FP64 accumulators every two K chunks.  mcap: rows of X
+// Y[yrow[r]] (complex128) = sum_j X[r][j] Z[i][j]: same product, the partial sums of at
+// most 64 terms added to FP64 accumulators.  mcap: rows of X
 // that may be read (>= M; the rows past M are computed and dropped); small_tile:
-// M <= 32 takes the 32-row tile instead of the selected one.
+// M <= 32 takes the 32-row FP32 tile instead of another selected one.
 void cgemm_mfma_acc64(const void* X, const void* Z, double2* Y, const int* yrow, int M, int n, hipStream_t s,
                       int mcap = 0, bool small_tile = false, void* ws = nullptr, size_t ws_bytes = 0);
 

@@ -1,5 +1,5 @@
 // efie_zx_flush64 for callers that cannot allocate device memory: the mixed
-// solves' product (FP32 matrix cores, partial sums flushed into FP64) with its
+// solves' product (complex64 on the matrix cores, partial sums added in FP64) with its
 // scratch in a static device array instead of a caller workspace.
 #include <hip/hip_runtime.h>
 

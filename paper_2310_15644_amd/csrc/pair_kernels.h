@@ -535,7 +535,7 @@ __device__ void near_pair_group(const DevMesh& m, int e, int g, double kr, doubl
 }
 
 // near pair e added to Z (and Z2 in parts mode) with atomics, in ZT precision (by
-// the group of 8 lanes, lane g)
+// the group of NEAR_G lanes, lane g)
 template <typename ZT, bool PARTS>
 __device__ void near_pair(const DevMesh& m, int e, int g, double kr, double ki, const Scale& sc, void* Z, void* Z2) {
     const int p = m.near_p[e], q = m.near_q[e];
