@@ -25,8 +25,8 @@
 //
 // Why.  The FP32 matrix cores reach 157 TFLOP/s: the planar kernels ran at 0.85 to
 // 0.95 of that, 25.8 to 28.8 ms for 30720 x 30720 times 512.  Three fp16 products take
-// 3/16 of the time of one FP32 product.  This kernel takes 16.8 ms (230 TFLOP/s of
-// complex products, 0.28 of the fp16 peak over three).  Bound by instruction issue:
+// 3/16 of the time of one FP32 product.  This kernel takes 16.1 ms (240 TFLOP/s of
+// complex products, 0.29 of the fp16 peak over three).  Bound by instruction issue:
 // matrix instructions and vector ones (splits, tests of the range, scaling back) take
 // about half of a SIMD's cycles each and hardly overlap.  With l unscaled it took 14.3 ms,
 // but held values below 2^-16 of a chunk's largest only to 2^-39 of that, and one large
@@ -74,9 +74,9 @@ __device__ __forceinline__ float max_abs(float a, float b) {
     asm("v_max_f32 %0, |%1|, |%2|" : "=v"(r) : "v"(a), "v"(b));
     return r;
 }
-__device__ __forceinline__ float min3(float a, float b, float c) {
+__device__ __forceinline__ float min3_abs(float m, float a, float b) {
     float r;
-    asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    asm("v_min3_f32 %0, %1, |%2|, |%3|" : "=v"(r) : "v"(m), "v"(a), "v"(b));
     return r;
 }
 // a sc and b sc (sc a power of two) in two fp16 parts each, packed: the nearest fp16
@@ -187,28 +187,30 @@ __global__ __launch_bounds__(64 * WM * WN * WK, MINW) void cgemm_split_kernel(co
     };
     // a row's chunk, scaled by the power of two that takes its largest part to [2^14, 2^15), into the planes
     auto put = [&](_Float16* planes, int* e, int rows, int row, const floatx4u (&v)[PC], bool& wide, bool& thin) {
-        // the lane's largest real and imaginary part and its smallest element
-        float mr = 0.f, mi = 0.f, lo = __builtin_inff();
+        float m = 0.f, lo = __builtin_inff();   // the lane's largest and smallest part
 #pragma unroll
         for (int p = 0; p < PC; ++p) {
-            mr = max3_abs(mr, v[p].x, v[p].z);
-            mi = max3_abs(mi, v[p].y, v[p].w);
-            lo = min3(lo, max_abs(v[p].x, v[p].y), max_abs(v[p].z, v[p].w));
+            m = max3_abs(max3_abs(m, v[p].x, v[p].y), v[p].z, v[p].w);
+            lo = min3_abs(min3_abs(lo, v[p].x, v[p].y), v[p].z, v[p].w);
         }
-        lo = min3(lo, mr, mi);
-        const uint32_t mx = max8(max_abs(mr, mi));
-        const float m = __builtin_bit_cast(float, mx);
-        thin |= lo < m * 0x1p-20f;
-        if (lo < m * 0x1p-27f) {   // rare: zeros aside?
-            const float t = m * 0x1p-27f;
-            auto below = [&](float a) { wide |= a > 0.f && a < t; };
-            below(mr);
-            below(mi);
+        const uint32_t mx = max8(m);
+        m = __builtin_bit_cast(float, mx);
+        if (lo < m * 0x1p-20f) {   // a part of ordinary data now and then, zeros
+            const float tt = m * 0x1p-20f, tw = m * 0x1p-27f;
+            auto below = [&](float a) {
+                thin |= a < tt;
+                wide |= a > 0.f && a < tw;
+            };
+            float mr = 0.f, mi = 0.f;   // the lane's real and imaginary parts
 #pragma unroll
             for (int p = 0; p < PC; ++p) {
                 below(max_abs(v[p].x, v[p].y));
                 below(max_abs(v[p].z, v[p].w));
+                mr = max3_abs(mr, v[p].x, v[p].z);
+                mi = max3_abs(mi, v[p].y, v[p].w);
             }
+            below(mr);
+            below(mi);
         }
         const int b = max(int(mx >> 23), 14);
         const float sc = __builtin_bit_cast(float, uint32_t(268 - b) << 23);
@@ -285,7 +287,6 @@ __global__ __launch_bounds__(64 * WM * WN * WK, MINW) void cgemm_split_kernel(co
         }
 #pragma unroll
         for (int ks = 0; ks < KC / 16; ++ks) {
-            __builtin_amdgcn_sched_barrier(0);
             halfx8 x[2], z[2];
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
