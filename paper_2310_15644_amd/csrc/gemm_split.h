@@ -27,8 +27,8 @@
 // 0.95 of that, 25.8 to 28.8 ms for 30720 x 30720 times 512.  Three fp16 products take
 // 3/16 of the time of one FP32 product.  This kernel takes 16.1 ms (240 TFLOP/s of
 // complex products, 0.29 of the fp16 peak over three).  Bound by instruction issue:
-// matrix instructions and vector ones (splits, tests of the range, scaling back) take
-// about half of a SIMD's cycles each and hardly overlap.  With l unscaled it took 14.3 ms,
+// matrix instructions take 0.36 of a SIMD's cycles and vector ones (splits, tests of the
+// range, scaling back) 0.54, and they hardly overlap.  With l unscaled it took 14.3 ms,
 // but held values below 2^-16 of a chunk's largest only to 2^-39 of that, and one large
 // value in a chunk against a zero cost all digits of the others' products.
 // Three bf16 parts need no scaling but six products: 22.4 ms at 1.9 GHz.
